@@ -147,7 +147,7 @@ int plan_geometry(const fo_params &q, fo_plan *pl)
     pl->ntiles = (pl->ntot + kTile - 1) / kTile;
     pl->S = pl->logb < (uint32_t)kTileLog2 ? pl->logb : (uint32_t)kTileLog2;
     const uint32_t high = pl->logb - pl->S;
-    pl->npass = high == 0 ? 0 : (high <= 10 ? 1 : 2);
+    pl->npass = high == 0 ? 0 : (high <= kMaxHigh ? 1 : 2);
     pl->hb[0] = pl->npass == 2 ? (high + 1) / 2 : high;
     pl->hb[1] = high - pl->hb[0];
     // shared eps: the sum of the M sign vectors is transformed in int32, magnitudes up to M b

@@ -146,7 +146,7 @@ inline bool args_ok(const StridedArgs &s, const PtrTab &tab, int kid)
     if (kid == KID_ENC_HIGH ? (s.use_tab ? !tab.p[0] : !s.src) : !s.src) return false;
     if (kid == KID_ENC_HIGH && !s.partials) return false;
     if ((kid == KID_DEC_HIGH || kid == KID_SERVER_HIGH || kid == KID_SERVER_MFMA) && !s.scales) return false;
-    return s.hb >= 1 && s.hb <= 10 && s.ls >= (uint32_t)kTileLog2;
+    return s.hb >= 1 && (s.hb <= 10 || (s.hb <= 12 && s.ls == (uint32_t)kTileLog2)) && s.ls >= (uint32_t)kTileLog2;
 }
 template <typename... Args>
 inline bool args_ok(const Args &...) { return true; }
@@ -176,13 +176,18 @@ int launch(fo_plan *pl, int kid, Kern kernel, dim3 grid, dim3 block, hipStream_t
         if (rc_) return rc_;       \
     } while (0)
 
-// Strided kernels come in a generic form and one compiled for ten stages next to the contiguous tile.
+// Strided kernels come in a generic form and ones compiled for ten, eleven and twelve stages next to the contiguous tile
+// (the middle pass of three-pass transforms never has more than eight).
 template <int MODE, bool IN16 = false>
 int launch_strided(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const StridedArgs &s, const PtrTab &tab)
 {
     constexpr int LV = (MODE == SM_SERVER || MODE == SM_SHARED || MODE == SM_ENC_FIRST) ? 5 : 6;
     if (s.hb == 10 && s.ls == (uint32_t)kTileLog2)
         return launch(pl, kid, k_strided<MODE, 10, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
+    if constexpr (MODE != SM_MID_F32 && MODE != SM_MID_I32 && (MODE != SM_SERVER || IN16)) {
+        if (s.hb == 11) return launch(pl, kid, k_strided<MODE, 11, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
+        if (s.hb == 12) return launch(pl, kid, k_strided<MODE, 12, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
+    }
     return launch(pl, kid, k_strided<MODE, 0, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
 }
 
@@ -243,6 +248,13 @@ inline uint32_t eps_party_of(const fo_plan *pl, uint32_t party)
 
 // Row padding of the intermediates of two-pass transforms: one 128-byte line (see StridedArgs).
 constexpr uint32_t kRowPad32 = 32, kRowPad16 = 64;
+
+// Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
+// Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a
+// second strided pass moves every intermediate once more, and on the server's side in int32 instead of int16: a step of
+// n = 2^27 with four workers takes 3.60 ms with one pass of twelve stages and 5.43 ms with passes of six and six.
+// Thirteen would leave rows of 4 columns, less than one line's worth per eight tiles.
+constexpr uint32_t kMaxHigh = 12;
 
 // fo_api.hip: the small amplitude kernels
 int launch_finalize_scales(fo_plan *pl, hipStream_t st, uint32_t nslots, float coef, float *scales, uint64_t scales_stride);

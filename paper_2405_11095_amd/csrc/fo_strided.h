@@ -1,8 +1,8 @@
-// Strided-tile kernel: up to ten Walsh-Hadamard stages on index bits above the contiguous tile
+// Strided-tile kernel: up to twelve Walsh-Hadamard stages on index bits above the contiguous tile
 // (transform lengths above 2^15).  A tile is R = 2^hb rows by 2^(15-hb) consecutive columns, rows
 // 2^ls coordinates apart; the stages act along the rows' axis only.
 //
-// Tile coordinate u = row << cb | col (cb = 15 - hb >= 5).  A thread holds 2^LV values as pairs of
+// Tile coordinate u = row << cb | col (cb = 15 - hb >= 3).  A thread holds 2^LV values as pairs of
 // neighbouring columns (LV = 6: 512 threads x 64 values; LV = 5: 1024 threads x 32 values), so every global
 // access moves a pair: 8 bytes per lane for fp32, 4 bytes per lane for the int16 intermediate that the decode
 // side reads.  With NW = 9 - LV wave bits (see SL<LV>):
@@ -11,7 +11,10 @@
 // The exchange swaps the wave bits with register bits 1..NW through LDS (in two halves, one per pair member;
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
-// v_permlane16_swap / v_permlane32_swap.
+// v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
+// M = 4): encode 1.16 ms for 3.75 GB, server 1.11 ms for 1.6 GB, decode 0.49 ms for 1.1 GB; the encode is bound by its
+// 32-byte row segments, the server by its instruction count (38 vector instructions per value and worker) next to the
+// latency of 16-byte ones.
 // Modes
 //   SM_ENC_FIRST : fp32 gradient (zero padded), eps flip on load, tile sum of squares -> fp32 intermediate
 //   SM_DEC_LAST  : integer intermediate -> lambda/sqrt(b) scaling, eps flip, store / SGD update (Def. 3.8)
@@ -38,7 +41,7 @@ struct StridedArgs {
     float *partials;       // ENC_FIRST: [slot][ntiles] tile sums of squares
     float *gbar;           // SERVER: optional fp32 [ntot] copy of the mean
     uint64_t len_in, len_out;
-    uint32_t ls, hb;       // log2 row stride, number of stages (1..10)
+    uint32_t ls, hb;       // log2 row stride, number of stages (1..12)
     uint32_t logb;
     uint32_t use_tab;
     uint32_t M;            // SERVER: workers to accumulate
@@ -124,18 +127,57 @@ __device__ __forceinline__ T &ref_at(void *uniform_base, uint32_t byte_off)
     return *reinterpret_cast<T *>(static_cast<char *>(uniform_base) + byte_off);
 }
 
-// eps words of the tile, one 32-bit word per group of 32 consecutive columns (u >> 5)
+// eps words of the tile, one 32-bit word per 32 consecutive tile coordinates (u >> 5).  Rows of 32 columns or more fill
+// a word by themselves; a word of narrower rows (cb = 3, 4) is put together from the 2^(5-cb) rows it covers.
 template <int T>
 __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, const RngKey &key, uint32_t t)
 {
 #pragma unroll
     for (int h = 0; h < 1024 / T; ++h) {
         const uint32_t grp = t + h * T;
-        const uint64_t i = g.origin + g.off(grp << 5);
-        uint32_t w[4];
-        philox((uint32_t)(i >> 7), key, w);
-        const uint32_t sel = (uint32_t)(i >> 5) & 3u;
-        epsw[grp] = sel == 0 ? w[0] : sel == 1 ? w[1] : sel == 2 ? w[2] : w[3];
+        auto word_at = [&](uint32_t u) -> uint32_t { // the 32-coordinate eps word that holds tile coordinate u
+            const uint64_t i = g.origin + g.off(u);
+            uint32_t w[4];
+            philox((uint32_t)(i >> 7), key, w);
+            const uint32_t sel = (uint32_t)(i >> 5) & 3u;
+            return sel == 0 ? w[0] : sel == 1 ? w[1] : sel == 2 ? w[2] : w[3];
+        };
+        if (g.cb >= 5u) {
+            epsw[grp] = word_at(grp << 5);
+        } else {
+            const uint32_t cols = 1u << g.cb, shift = (uint32_t)g.origin & 31u; // the tile's columns inside their word
+            uint32_t e = 0u;
+            for (uint32_t k = 0; k < 32u; k += cols)
+                e |= ((word_at((grp << 5) | k) >> shift) & ((1u << cols) - 1u)) << k;
+            epsw[grp] = e;
+        }
+    }
+}
+
+// One stage on lane bit 3 or 2 (partner = lane ^ 8: the 16-lane row rotated by 8; lane ^ 4: a quad reversed, then the
+// eight lanes mirrored).  The upper lane of a pair keeps partner - own, the lower own + partner.
+template <int LBIT, int V>
+__device__ __forceinline__ void bfly_dpp(float (&v)[V], uint32_t lane)
+{
+    const float sgn = (lane >> LBIT) & 1u ? -1.f : 1.f;
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        int o = (int)__float_as_uint(v[k]);
+        if constexpr (LBIT == 3) o = __builtin_amdgcn_mov_dpp(o, 0x128, 0xf, 0xf, true);
+        else o = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(o, 0x1B, 0xf, 0xf, true), 0x141, 0xf, 0xf, true);
+        v[k] = fmaf(v[k], sgn, __uint_as_float((uint32_t)o)); // the product is exact: one rounding, as the sum has
+    }
+}
+template <int LBIT, int V>
+__device__ __forceinline__ void bfly_dpp(int32_t (&v)[V], uint32_t lane)
+{
+    const int32_t up = (int32_t)((lane >> LBIT) & 1u), inv = -up; // -x = ~x + 1
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        int o = v[k];
+        if constexpr (LBIT == 3) o = __builtin_amdgcn_mov_dpp(o, 0x128, 0xf, 0xf, true);
+        else o = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(o, 0x1B, 0xf, 0xf, true), 0x141, 0xf, 0xf, true);
+        v[k] = (v[k] ^ inv) + up + o;
     }
 }
 
@@ -157,11 +199,13 @@ __device__ __forceinline__ void bfly_lane4(T (&v)[V])
     }
 }
 
-// stages on lane bits 4, 5 (u5, u6) and on the register bits of LA (register bit k <-> u bit 6 + NW + k)
+// stages on lane bits 2 .. 5 (u3 .. u6) and on the register bits of LA (register bit k <-> u bit 6 + NW + k)
 template <typename T, int LV>
 __device__ __forceinline__ void stages_a(T (&v)[1 << LV], uint32_t cb)
 {
     constexpr int V = 1 << LV, B1 = 7 + SL<LV>::NW; // u bit of register bit 1
+    if (cb <= 3u) bfly_dpp<2, V>(v, threadIdx.x & 63u);
+    if (cb <= 4u) bfly_dpp<3, V>(v, threadIdx.x & 63u);
     if (cb <= 5u) bfly_lane4<T, V>(v);
     if (cb <= 6u) bfly_lane5<T, V>(v);
     if (cb <= (uint32_t)B1) bfly<T, 1, V>(v);
@@ -297,7 +341,7 @@ __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const Str
         ref_at<float2>(dst + g.off(L::pa(p)) + (L::pa(p) >> cb) * a.dst_pad, otd * 4u) = make_float2(acc[2 * p], acc[2 * p + 1]);
 }
 
-// HB = 0: the number of stages and the row stride are read from the arguments.  HB > 0: compiled
+// HB = 0: the number of stages (at most ten) and the row stride are read from the arguments.  HB = 10, 11, 12: compiled
 // for exactly HB stages with rows 2^15 apart (the pass next to the contiguous tile), which turns
 // every per-register offset into a constant and removes the stage-selection branches.
 // IN16: the integer input is the contiguous kernel's int16 intermediate.
@@ -324,10 +368,14 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
     resolve_round(a.k1, a.round_lo, a.round_dev, rk1, rlo);
     const uint32_t hb = HB ? (uint32_t)HB : a.hb;
     const uint32_t cb = (uint32_t)kTileLog2 - hb;
-    // 64-byte row segments (int16 input, 32 columns): neighbouring column groups share 128-byte lines, so
-    // they are given block indices that land on the same XCD (blocks are dealt round-robin over 8 XCDs)
+    // Row segments shorter than a 128-byte line (fp32 below 32 columns, int16 below 64): the 2^gl column groups that share
+    // lines are given block indices that land on the same XCD (blocks are dealt round-robin over 8 XCDs)
     uint32_t tile = blockIdx.x;
-    if (IN16 && cb == 5u) tile = (tile & ~15u) | ((tile & 7u) << 1) | ((tile >> 3) & 1u);
+    {
+        const uint32_t line = IN16 ? 6u : 5u; // log2 of the columns in a line
+        const uint32_t gl = ((IN16 || HB > 10) && cb < line && cb <= 5u) ? line - cb : 0u;
+        tile = (tile & ~((8u << gl) - 1u)) | ((tile & 7u) << gl) | ((tile >> 3) & ((1u << gl) - 1u));
+    }
     const bool need_x = cb <= 6u + (uint32_t)L::NW; // some row bit lives in the wave index
     StridedGeom g;
     g.cb = cb;
@@ -530,12 +578,14 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         // with worker m + 1 as soon as they have been unpacked
         auto process = [&](uint32_t m, auto prefetch) {
             constexpr bool PREFETCH = decltype(prefetch)::value;
-            // fp32 butterflies: every value is an integer below 2^24 in magnitude, so each sum is exact
-            float buf[kSV];
+            // fp32 butterflies up to ten stages: every value is an integer below 2^24 in magnitude, so each sum is exact.
+            // Beyond that the stages stay in integers, as in the decoder.
+            using TB = typename std::conditional<(HB > 10), int32_t, float>::type;
+            TB buf[kSV];
 #pragma unroll
             for (int p = 0; p < kSP; ++p) {
-                buf[2 * p] = (float)(int16_t)(raw[p] & 0xFFFFu);
-                buf[2 * p + 1] = (float)((int32_t)raw[p] >> 16);
+                buf[2 * p] = (TB)(int16_t)(raw[p] & 0xFFFFu);
+                buf[2 * p + 1] = (TB)((int32_t)raw[p] >> 16);
             }
             if constexpr (PREFETCH) request(m + 1);
             const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, m };
@@ -543,11 +593,11 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
             // and it is read after this iteration's barrier, which every wave reaches only when done with m-1.
             uint32_t *const epsm = epsw + (m & 1u) * kEpsWords;
             fill_eps<L::T>(epsm, g, key_eps, t);
-            stages_a<float, LV>(buf, cb);
+            stages_a<TB, LV>(buf, cb);
             if (need_x) {
                 __syncthreads(); // the previous worker's exchange buffer is no longer read
-                exchange_wide<float, LV>(buf, xbuf, lane, wave);
-                stages_b<float, LV>(buf, cb);
+                exchange_wide<TB, LV>(buf, xbuf, lane, wave);
+                stages_b<TB, LV>(buf, cb);
             } else {
                 __syncthreads(); // publishes the eps table
             }
@@ -556,8 +606,8 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
 #pragma unroll
             for (int p = 0; p < kSP; ++p) {
                 const uint32_t w = epsm[(ut_out >> 5) + (upair_out(p) >> 5)];
-                acc[2 * p] = fmaf(buf[2 * p], __uint_as_float(((w >> eshift) << 31) + cbits), acc[2 * p]);
-                acc[2 * p + 1] = fmaf(buf[2 * p + 1], __uint_as_float(((w >> (eshift + 1u)) << 31) + cbits), acc[2 * p + 1]);
+                acc[2 * p] = fmaf((float)buf[2 * p], __uint_as_float(((w >> eshift) << 31) + cbits), acc[2 * p]);
+                acc[2 * p + 1] = fmaf((float)buf[2 * p + 1], __uint_as_float(((w >> (eshift + 1u)) << 31) + cbits), acc[2 * p + 1]);
             }
         };
         request(0);

@@ -1,0 +1,54 @@
+"""Transforms of 2^26 and 2^27 points take two passes (eleven and twelve stages over rows of 16 and 8 columns), longer
+ones three.  The first two against the oracle; the three-pass server with several workers against the decoder and
+the encoder, which test_gpu_max_size.py checks at that length."""
+import numpy as np
+import pytest
+
+from tests.parity import check_round_trip, gates
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,M,blk,kw", [
+    ((1 << 26) + 5, 2, 0, {}),                                     # twelve stages, most of the second half padding
+    ((1 << 27) - 3, 2, 27, {"eps_mode": 1, "server_scale": 1}),    # one summed transform, measured-norm amplitude
+    ((1 << 26) + 70_001, 1, 26, {"K": 3}),                         # two blocks of eleven stages, int32 intermediate
+], ids=["2p27", "2p27_shared_l2", "two_blocks_2p26_K3"])
+def test_two_pass_transforms_of_narrow_rows(oracle, d, M, blk, kw):
+    import torch
+    from paper_2405_11095_amd import binding as B, inputs
+    gs = [inputs.heavy_tailed(d, m) for m in range(M)]
+    print(f"d={d} M={M} block_log2={blk} {kw}", flush=True)
+    rep = check_round_trip(oracle, B, gs, d=d, M=M, block_log2=blk, seed=0x5A + M, rnd=3, delta=0.05,
+                           device=torch.device("cuda:0"), threads=16, **kw)
+    print(rep, flush=True)
+    gates(rep)
+
+
+def test_three_pass_server_with_several_workers():
+    """n = 2^28: the mean is the average of the decoded messages (each exact but for one rounding of 2^-24, and M + 1
+    roundings of the sum: 1e-6 covers them), and the downlink is the server's own encode of that mean."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    d, M, rnd = (1 << 27) + 9, 3, 5
+    plan = B.Plan(d=d, M=M, seed=77)
+    assert plan.ntot == 1 << 28
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(4)
+    bits_up = torch.randint(-(1 << 63), (1 << 63) - 1, (M, plan.W), generator=gen, device=dev, dtype=torch.int64)
+    lam = torch.rand(M, 1, generator=gen, device=dev) + 0.5
+    down = torch.zeros(1, plan.W, dtype=torch.int64, device=dev)
+    lam_s = torch.zeros(1, device=dev)
+    gbar = torch.zeros(plan.ntot, device=dev)
+    plan.fo_server_aggregate(bits_up, lam, rnd, down, lam_s, gbar)
+    want = torch.zeros(d, device=dev)
+    out = torch.zeros(d, device=dev)
+    for m in range(M):
+        plan.fo_decode(bits_up[m], lam[m], rnd, m, out)
+        want += out / M
+    assert float((gbar[:d] - want).norm() / want.norm()) < 1e-6
+    again = torch.zeros(plan.W, dtype=torch.int64, device=dev)
+    plan.fo_encode(gbar, rnd, B.PARTY_SERVER, again, lam_s, flags=B.FORCE_SCALE)
+    differ = (again ^ down[0]) != 0
+    assert float(differ.float().mean()) < 1e-5   # near ties only: the fused pass adds in another order
