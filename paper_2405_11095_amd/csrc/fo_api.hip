@@ -156,6 +156,15 @@ int plan_geometry(const fo_params &q, fo_plan *pl)
     while ((q.K >> pl->planes) != 0) ++pl->planes;
     // the decode side carries K b / 2 at most in int32 between its passes
     if (q.K > 1 && pl->npass > 0 && (uint64_t)q.K * (pl->b / 2) >= ((uint64_t)1 << 31)) return FO_EINVAL;
+    pl->sm_tiles = (pl->ntot + ((1u << 12) - 1)) >> 12;
+    {
+        // Short vectors (fo_small.h).  See kSmallRules for where the lines lie; the values have to be exact in fp32.
+        const SmallRule &rule = kSmallRules[pl->logb <= 12 ? 0 : pl->logb <= 15 ? 1 : pl->logb == 16 ? 2 : 3];
+        const bool exact = pl->logb <= 20 && (uint64_t)q.K * pl->b <= ((uint64_t)1 << 24) &&
+                           (q.eps_mode == FO_EPS_INDEPENDENT || (uint64_t)q.M * pl->b <= ((uint64_t)1 << 24));
+        pl->small = exact && pl->ntot <= rule.longest && q.M * pl->ntot <= rule.total;
+        pl->small_dec = exact && (pl->logb <= 12 || pl->small);
+    }
     const double bd = (double)pl->b;
     pl->coef_lambda = (float)((double)q.alpha * std::sqrt(std::log(bd) / bd));
     pl->sqrtb = (float)std::sqrt(bd);
@@ -190,10 +199,10 @@ extern "C" int fo_plan_create(const fo_params *params, fo_plan **out)
     }
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     if (pl->npass == 1) { pl->pad32 = kRowPad32; pl->pad16 = kRowPad16; }
-    const size_t sz_a = pl->npass ? up((size_t)q.M * (pl->ntot + pl->ntiles * pl->pad32) * 4) : 0;
+    const size_t sz_a = pl->npass || (pl->small && pl->logb > 12) ? up((size_t)q.M * (pl->ntot + pl->ntiles * pl->pad32) * 4) : 0;
     const size_t sz_b = up((pl->ntot + pl->ntiles * pl->pad32) * 4);
     const size_t sz_c = pl->npass == 2 ? up(pl->ntot * 4) : 0;
-    const size_t sz_part = up((size_t)q.M * pl->ntiles * 4);
+    const size_t sz_part = up((size_t)q.M * (pl->small ? pl->sm_tiles : pl->ntiles) * 4);
     const size_t sz_bu = up((size_t)q.M * pl->W * 8), sz_su = up((size_t)q.M * pl->nblocks * 4);
     const size_t sz_bd = up((size_t)pl->planes * pl->W * 8), sz_sd = up(pl->nblocks * 4);
     const size_t sz_bs = up(pl->nblocks * 8);
@@ -307,6 +316,7 @@ extern "C" int fo_step(fo_plan *pl, const float *const *g, float *x, float delta
     bool given;
     int rc = prepare_scales(pl, M, false, pl->scales_up, pl->nblocks, st, &given);
     if (rc) return rc;
+    if (pl->small) return small_step(pl, tab, x, delta, round, given, st);
     if (pl->npass == 2) {
         // three-pass transforms are encoded one worker at a time.  With a shared eps the workers must agree on one
         // amplitude per block before any of them quantises: a first round of encodes only measures the norms (its
@@ -427,7 +437,7 @@ extern "C" int fo_profile_end(fo_plan *pl, fo_kernel_time *out, size_t cap, size
 namespace {
 
 constexpr uint64_t kNoallocMaxN = (uint64_t)FO_NOALLOC_MAX_N;
-constexpr uint64_t kNoallocPartials = kNoallocMaxN >> kTileLog2;          // one sum of squares per tile
+constexpr uint64_t kNoallocPartials = kNoallocMaxN >> 12;                 // one sum of squares per tile, the smallest kind
 constexpr uint64_t kNoallocWords = kNoallocMaxN + ((kNoallocPartials + 63) & ~(uint64_t)63);
 
 } // namespace

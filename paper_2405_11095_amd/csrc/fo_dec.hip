@@ -13,6 +13,8 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
                   float *out, uint64_t len_out, uint32_t store_mode, float out_coef, float delta, float *tmp,
                   hipStream_t st)
 {
+    if (pl->small_dec) // its coefficient and length are the plan's, as every caller's
+        return small_decode(pl, bits, scales, round, party, out, store_mode, delta, tmp, st);
     const Rng r = rng_of(pl, round);
     PtrTab none;
     std::memset(&none, 0, sizeof(none));
@@ -28,8 +30,6 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
     if (pl->npass == 0) {
         c.dst = out; c.len_out = len_out; c.store_mode = store_mode; c.out_coef = out_coef; c.delta = delta;
         if (multik) FO_TRY(launch(pl, KID_DEC_SINGLE, (k_contig<IN_BITS, OUT_F32, false, false, 0, true>), grid, block, st, c, none));
-        else if (c.S == 10) FO_TRY(launch(pl, KID_DEC_SINGLE, k_decode_tile<10>, grid, block, st, c));
-        else if (c.S == 12) FO_TRY(launch(pl, KID_DEC_SINGLE, k_decode_tile<12>, grid, block, st, c));
         else if (c.S == 14) FO_TRY(launch(pl, KID_DEC_SINGLE, k_decode_tile<14>, grid, block, st, c));
         else FO_TRY(launch(pl, KID_DEC_SINGLE, k_decode_tile<0>, grid, block, st, c));
         return FO_OK;

@@ -42,6 +42,9 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
                   uint64_t bits_stride, float *scales, uint64_t scales_stride, float *tmp, uint64_t tmp_stride,
                   hipStream_t st, bool common)
 {
+    if (pl->small)
+        return small_encode(pl, tab, src, src_stride, len_in, nslots, party0, round, scales_given, bits, bits_stride, scales,
+                            scales_stride, tmp, tmp_stride, st, common);
     const Rng r = rng_of(pl, round);
     PtrTab none;
     std::memset(&none, 0, sizeof(none));

@@ -18,7 +18,8 @@
 #include "fo_server_tile.h"
 #include "fo_shall.h"
 
-// Kernel identities for the optional per-kernel timing (fo_profile_begin / fo_profile_end).
+// Kernel identities for the optional per-kernel timing (fo_profile_begin / fo_profile_end).  The kernels for short
+// vectors (fo_small.h) are recorded as the one here that runs the same stage.
 enum KernelId {
     KID_ENC_SINGLE = 0, // k_contig<IN_GRAD,OUT_PACK>
     KID_ENC_HIGH,       // k_strided<ENC_FIRST>
@@ -65,6 +66,8 @@ struct fo_plan {
     uint32_t npass;      // strided passes: 0, 1 or 2
     uint32_t hb[2];      // stages of each strided pass (pass 0 is adjacent to the contiguous tile)
     uint32_t planes;     // bit planes of the downlink message: ceil(log2(K + 1))
+    bool small, small_dec; // short vector: encoder and server, decoder on the kernels of fo_small.h (see plan_geometry)
+    uint64_t sm_tiles;   // its tiles of 2^12 coordinates
     uint32_t num_cus;    // compute units of the device the plan was made on
     uint32_t pad32, pad16; // elements between the 2^15-element rows of the fp32 / int16 intermediates (two-pass transforms)
     bool server_mfma;    // blocks of 2^25: the server pass on the matrix cores (off: the vector-unit kernel, same results)
@@ -249,6 +252,21 @@ inline uint32_t eps_party_of(const fo_plan *pl, uint32_t party)
 // Row padding of the intermediates of two-pass transforms: one 128-byte line (see StridedArgs).
 constexpr uint32_t kRowPad32 = 32, kRowPad16 = 64;
 
+// Which plans take the kernels for short vectors, by transform length: padded length at most `longest` and that times the
+// number of workers at most `total`.  Steps on the general kernels -> on these, us: b = 2^12: 2^22 x 4 workers 72 -> 52,
+// 2^22 x 8 97 -> 92, 2^21 x 32 166 -> 192, 2^24 x 4 170 -> 220.  b = 2^14: 2^20 x 2 48 -> 38, x 8 68 -> 60, x 32 133 -> 166.
+// b = 2^16: 2^21 x 8 99 -> 87, x 32 230 -> 274, 2^22 x 4 92 -> 97.  b = 2^18: 2^21 x 32 374 -> 270, 2^23 x 4 (b = 2^19) even.
+// The decoder of one pass (b <= 2^12) is the better one at every length: 252 -> 146 us for d = 2^27.
+struct SmallRule {
+    uint64_t longest, total;
+};
+constexpr SmallRule kSmallRules[4] = {
+    { (uint64_t)1 << 22, (uint64_t)1 << 24 }, // b <= 2^12
+    { (uint64_t)1 << 20, (uint64_t)1 << 23 }, // b <= 2^15: the general kernels take one pass, these two
+    { (uint64_t)1 << 21, (uint64_t)1 << 24 }, // b = 2^16: a pair of tiles on one workgroup there
+    { (uint64_t)1 << 21, (uint64_t)1 << 26 }, // b <= 2^20
+};
+
 // Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
 // Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a
 // second strided pass moves every intermediate once more, and on the server's side in int32 instead of int16: a step of
@@ -261,6 +279,16 @@ int launch_finalize_scales(fo_plan *pl, hipStream_t st, uint32_t nslots, float c
 int launch_fill_scales(fo_plan *pl, hipStream_t st, uint32_t nslots, float *scales, uint64_t scales_stride, float value);
 int launch_server_scales(fo_plan *pl, hipStream_t st, const float *scales_up, float *scales_down);
 int launch_common_scales(fo_plan *pl, hipStream_t st, float *scales, uint32_t nslots);
+
+// fo_small.hip: the same calls for short vectors (plan->small)
+int small_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride, uint64_t len_in, uint32_t nslots,
+                 uint32_t party0, uint64_t round, bool scales_given, uint64_t *bits, uint64_t bits_stride, float *scales,
+                 uint64_t scales_stride, float *tmp, uint64_t tmp_stride, hipStream_t st, bool common);
+int small_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64_t round, uint32_t party, float *out,
+                 uint32_t store_mode, float delta, float *tmp, hipStream_t st);
+int small_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, uint64_t round, uint64_t *bits_down,
+                 float *scales_down, float *gbar_or_null, hipStream_t st);
+int small_step(fo_plan *pl, const PtrTab &tab, float *x, float delta, uint64_t round, bool scales_given, hipStream_t st);
 
 // fo_enc.hip / fo_enc_stats.hip: the dither + sign + pack kernels, without / with the diagnostic counters
 template <int IN, bool STATS>

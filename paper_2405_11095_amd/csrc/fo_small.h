@@ -5,6 +5,10 @@
 // that one compute unit needs for 2^15 values (12 to 20 us a kernel, whatever the vector's length).  Here the same
 // vector occupies eight times as many workgroups, each with an eighth of the work.  Everything is fp32: on the decode
 // side the values are half integers below 2^23, so every sum is exact (the plan's rule sees to the bound).
+// Measured, general kernels before and these after: one encode of 1000 coordinates 12.0 -> 7.3 us (kernel 4.9 us), a step of
+// n = 2^16 with four workers 71.7 -> 25.8 us, n = 2^20 with eight 123 -> 64 us.  What bounds a kernel here is latency: one
+// trip to memory, two exchanges and the generator's chain of ten rounds, 4 to 6 us each with few waves per SIMD; at
+// n = 2^20 the encode is at 4 TB/s in the high pass and near its instruction count in the low one.
 //
 // Transforms of up to 2^12 points (whole or blocked) take one pass, longer ones (up to 2^20 points) two: up to eight
 // stages over rows 2^12 apart (k_small_high), twelve inside the contiguous tile (k_small_encode, k_small_decode).
@@ -69,12 +73,14 @@ struct SmallArgs {
     float in_coef;             // server: value = lambda_n * in_coef * (half integer)
     float out_coef;            // decode: the same for out
     float delta;
+    unsigned long long *stat_clipped, *stat_near; // optional diagnostic counters per slot (see ContigArgs)
 };
 
 struct SmallLds {
     alignas(16) float x[kSmXWords];
     uint32_t eps[kSmEpsWords];
-    float lam[64];             // per block of the tile
+    float lam[64];             // per block of the tile: the amplitude
+    float kq[64];              // and the slope -128 / (lambda' 2^-24) of the integer-domain comparison
     float red[64];
     double red64[4];
     uint64_t words[kSmPlanes * 64];
@@ -156,6 +162,17 @@ __device__ __forceinline__ void small_from_bits(float (&v)[16], uint32_t n, bool
     for (int r = 0; r < 16; ++r) v[r] = (float)c[r] - half;
 }
 
+// The same for a plain sign message, from this lane's four words
+__device__ __forceinline__ void small_from_signs(float (&v)[16], const uint64_t (&w)[4], uint32_t lane)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t nib = (uint32_t)(w[q] >> ((lane & 15u) * 4u));
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[4 * q + k] = flip_by_bit31(-0.5f, nib << (31 - k));
+    }
+}
+
 // Dither, sign and pack (Def. 3.2, Def. 3.7) of the tile in L2; l.lam holds the blocks' amplitudes (published).  The
 // words go to memory and, with KEEP, to l.words as well.
 template <bool DITHER, bool MULTIK, bool KEEP>
@@ -169,6 +186,26 @@ __device__ __forceinline__ void small_pack(const float (&v)[16], const SmallArgs
     const uint64_t gw = tile * 64u + at;
     uint64_t *const dst = a.bits_out + slot * a.bits_out_stride + gw;
     const bool mine = lane < 16u;
+    if (a.stat_clipped) {
+        uint32_t clipped = 0u, near = 0u;
+        static_for<4>([&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            uint32_t w[4] = { 0u, 0u, 0u, 0u };
+            if constexpr (DITHER) philox((uint32_t)((base + small_l2(4 * g, wave)) >> 8) << 6 | lane, key, w);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float z = v[4 * g + s], lam = l.lam[small_l2(4 * g + s, wave) >> a.S];
+                float tv = z;
+                if constexpr (DITHER) tv = fmaf(lam * tscale, fmaf((float)(w[s] >> 8), 2.f, -16777215.f), tv);
+                clipped += (uint32_t)__popcll(__ballot(fabsf(z) > lam * a.sqrtb));
+                near += (uint32_t)__popcll(__ballot(fabsf(tv) < 1e-6f * lam * a.sqrtb));
+            }
+        });
+        if (lane == 0u) {
+            atomicAdd(a.stat_clipped + slot, (unsigned long long)clipped);
+            atomicAdd(a.stat_near + slot, (unsigned long long)near);
+        }
+    }
     if constexpr (!MULTIK) {
         uint32_t lo = 0u, hi = 0u;
         static_for<4>([&](auto gc) {
@@ -180,7 +217,7 @@ __device__ __forceinline__ void small_pack(const float (&v)[16], const SmallArgs
                 uint64_t word;
                 if constexpr (DITHER) {
                     // the integer-domain comparison of fo_contig.h: w >= 2^31 - 128 - 128 z 2^24 / lambda'
-                    const float kq = -128.f / (l.lam[small_l2(r, wave) >> a.S] * tscale);
+                    const float kq = l.kq[small_l2(r, wave) >> a.S];
                     uint32_t thr;
                     asm("v_cvt_u32_f32 %0, %1" : "=v"(thr) : "v"(fmaf(v[r], kq, 2147483520.f)));
                     word = __ballot(w[decltype(sc)::value] >= thr) & __ballot(kq == kq);
@@ -236,6 +273,20 @@ __device__ __forceinline__ void small_pack(const float (&v)[16], const SmallArgs
     }
 }
 
+// The decoder's input from the message just packed (l.words)
+template <bool MULTIK>
+__device__ __forceinline__ void small_from_kept(float (&v)[16], const SmallArgs &a, const SmallLds &l, uint32_t lane, uint32_t wave)
+{
+    if constexpr (MULTIK) {
+        small_from_bits(v, a.planes, false, 0.5f * (float)a.K, lane, wave, [&](uint32_t p, uint32_t w) { return l.words[64u * p + w]; });
+    } else {
+        uint64_t w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = l.words[wave * 16u + (lane >> 4) + 4u * q];
+        small_from_signs(v, w, lane);
+    }
+}
+
 // Largest amplitude of the M workers for block gb, NaN if any is NaN
 __device__ __forceinline__ float small_largest(const SmallArgs &a, uint64_t gb)
 {
@@ -261,11 +312,16 @@ __device__ __forceinline__ bool small_encode_tile(float (&v)[16], const SmallArg
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             p[q] = (v[4 * q] * v[4 * q] + v[4 * q + 1] * v[4 * q + 1]) + (v[4 * q + 2] * v[4 * q + 2] + v[4 * q + 3] * v[4 * q + 3]);
-        const uint32_t ll = S < 8u ? S - 2u : 6u; // log2 of the lanes that share a block's part of 256 coordinates
+        if (S >= 10u) { // a wave's 1024 coordinates lie in one block
+            const float s = wave_sum((p[0] + p[1]) + (p[2] + p[3]), 6);
+            if (lane == 0u) l.red[wave] = s;
+        } else {
+            const uint32_t ll = S < 8u ? S - 2u : 6u; // log2 of the lanes that share a block's part of 256 coordinates
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float s = wave_sum(p[q], (int)ll);
-            if ((lane & ((1u << ll) - 1u)) == 0u) l.red[((wave * 4u + q) << (6u - ll)) + (lane >> ll)] = s;
+            for (int q = 0; q < 4; ++q) {
+                const float s = wave_sum(p[q], (int)ll);
+                if ((lane & ((1u << ll) - 1u)) == 0u) l.red[((wave * 4u + q) << (6u - ll)) + (lane >> ll)] = s;
+            }
         }
     }
     small_eps(l.eps, a, rk1, rlo, eps_party, base);
@@ -277,7 +333,7 @@ __device__ __forceinline__ bool small_encode_tile(float (&v)[16], const SmallArg
         if (gb < a.nblocks) {
             float *const out = a.scales + slot * a.scales_stride + gb;
             if (a.scale_mode == SMS_MEASURED) {
-                const uint32_t per = S > 8u ? 1u << (S - 8u) : 1u;
+                const uint32_t per = S >= 10u ? 1u << (S - 10u) : S == 9u ? 2u : 1u;
                 float s = 0.f;
                 for (uint32_t k = 0; k < per; ++k) s += l.red[t * per + k];
                 *out = lam = a.coef * sqrtf(s);
@@ -288,6 +344,7 @@ __device__ __forceinline__ bool small_encode_tile(float (&v)[16], const SmallArg
             }
         }
         l.lam[t] = lam;
+        l.kq[t] = -128.f / (lam * (a.sqrtb * 5.9604644775390625e-08f));
     }
     if (a.scales_only) return false;
 #pragma unroll
@@ -308,11 +365,10 @@ __device__ __forceinline__ float small_signed_lam(const SmallLds &l, int r, uint
     return flip_if(l.lam[c >> S], (w >> (lane & 31u)) & 1u);
 }
 
-__device__ __forceinline__ void small_store(float *dst, float y, uint32_t mode, float delta)
+// The decoder's result `y` for an element that held `old` (read ahead of the transform; unused by STORE_SET)
+__device__ __forceinline__ float small_result(float y, float old, uint32_t mode, float delta)
 {
-    if (mode == STORE_SET) *dst = y;
-    else if (mode == STORE_ACC) *dst += y;
-    else *dst -= delta * y;
+    return mode == STORE_SET ? y : mode == STORE_ACC ? old + y : old - delta * y;
 }
 
 // Encoder, low stages: tile blockIdx.x of slot blockIdx.y.  MID: the input has its high stages done (b > 2^12), the
@@ -372,6 +428,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_encode(const SmallArgs a, 
         }
         if (t == 0) {
             l.lam[0] = lam;
+            l.kq[0] = -128.f / (lam * (a.sqrtb * 5.9604644775390625e-08f));
             if (a.scale_mode != SMS_GIVEN && (base & ((1ull << a.logb) - 1u)) == 0u) a.scales[slot * a.scales_stride + gb] = lam;
         }
         small_transform(v, 12u, l.x, lane, wave); // its barrier publishes l.lam
@@ -379,7 +436,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_encode(const SmallArgs a, 
     small_pack<DITHER, MULTIK, DEC>(v, a, l, rk1, rlo, party, slot, tile, lane, wave);
     if constexpr (DEC) {
         __syncthreads(); // the words are published, l.x is free
-        small_from_bits(v, MULTIK ? a.planes : 1u, false, 0.5f * (float)a.K, lane, wave, [&](uint32_t p, uint32_t w) { return l.words[64u * p + w]; });
+        small_from_kept<MULTIK>(v, a, l, lane, wave);
         small_transform(v, a.S, l.x, lane, wave);
         float *const dst = a.mid + slot * a.mid_stride + base + lane;
 #pragma unroll
@@ -395,11 +452,24 @@ __global__ __launch_bounds__(kSmThreads) void k_small_decode(const SmallArgs a)
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, slot = blockIdx.y, S = a.S;
     const uint64_t tile = blockIdx.x, base = tile << kSmLog2;
     const uint64_t *const bits = a.bits_in + slot * a.bits_in_stride;
+    auto word = [&](uint32_t p, uint32_t w) { const uint64_t gw = tile * 64u + w; return gw < a.W ? bits[(uint64_t)p * a.W + gw] : 0ull; };
     float v[16];
-    // planes of a message, or (count) the workers' messages: both lie W words apart
-    small_from_bits(v, a.count ? a.M : a.planes_in, a.count != 0u, 0.5f * (float)(a.count ? a.M : a.Kin), lane, wave,
-                    [&](uint32_t p, uint32_t w) { const uint64_t gw = tile * 64u + w; return gw < a.W ? bits[(uint64_t)p * a.W + gw] : 0ull; });
+    if (!a.count && a.Kin == 1u) {
+        uint64_t w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = word(0u, wave * 16u + (lane >> 4) + 4u * q);
+        small_from_signs(v, w, lane);
+    } else { // planes of a message, or (count) the workers' messages: both lie W words apart
+        small_from_bits(v, a.count ? a.M : a.planes_in, a.count != 0u, 0.5f * (float)(a.count ? a.M : a.Kin), lane, wave, word);
+    }
+    float old[16];
     if constexpr (FINAL) {
+        if (a.store_mode != STORE_SET)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint64_t i = base + small_l2(r, wave) + lane;
+                old[r] = i < a.len_out ? a.out[i] : 0.f;
+            }
         uint32_t rk1, rlo;
         resolve_round(a.k1, a.round_lo, a.round_dev, rk1, rlo);
         small_eps(l.eps, a, rk1, rlo, a.eps_in, base);
@@ -414,7 +484,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_decode(const SmallArgs a)
     for (int r = 0; r < 16; ++r) {
         const uint64_t i = base + small_l2(r, wave) + lane;
         if constexpr (FINAL) {
-            if (i < a.len_out) small_store(a.out + i, v[r] * small_signed_lam(l, r, S, lane, wave), a.store_mode, a.delta);
+            if (i < a.len_out) a.out[i] = small_result(v[r] * small_signed_lam(l, r, S, lane, wave), old[r], a.store_mode, a.delta);
         } else {
             a.mid[slot * a.mid_stride + i] = v[r];
         }
@@ -436,15 +506,26 @@ __global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     const uint32_t nmsg = a.count ? 1u : a.M;
+    auto word = [&](uint32_t p, uint32_t w) { const uint64_t gw = tile * 64u + w; return gw < a.W ? a.bits_in[(uint64_t)p * a.W + gw] : 0ull; };
+    // a worker's words and amplitude are asked for one worker ahead
+    uint64_t wnext[4] = { 0ull, 0ull, 0ull, 0ull };
+    const uint64_t gb_mine = tile * nblk + t;
+    const bool lam_mine = t < nblk && gb_mine < a.nblocks;
+    float lnext = 0.f;
+    auto request = [&](uint32_t m) {
+        if (!a.count)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wnext[q] = word(m, wave * 16u + (lane >> 4) + 4u * q);
+        lnext = lam_mine ? a.scales_up[(uint64_t)m * a.nblocks + gb_mine] : 0.f;
+    };
+    request(0u);
     for (uint32_t m = 0; m < nmsg; ++m) {
-        const uint64_t *const bits = a.bits_in + (uint64_t)m * a.bits_in_stride;
-        small_from_bits(v, a.count ? a.M : 1u, true, a.count ? 0.5f * (float)a.M : 0.5f, lane, wave,
-                        [&](uint32_t p, uint32_t w) { const uint64_t gw = tile * 64u + w; return gw < a.W ? bits[(uint64_t)p * a.W + gw] : 0ull; });
+        if (a.count) small_from_bits(v, a.M, true, 0.5f * (float)a.M, lane, wave, word);
+        else small_from_signs(v, wnext, lane);
+        const float lam = lnext * a.in_coef;
+        if (m + 1u < nmsg) request(m + 1u);
         small_eps(l.eps, a, rk1, rlo, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + m, base);
-        if (t < nblk) {
-            const uint64_t gb = tile * nblk + t;
-            l.lam[t] = gb < a.nblocks ? a.scales_up[(uint64_t)m * a.nblocks + gb] * a.in_coef : 0.f;
-        }
+        if (t < nblk) l.lam[t] = lam;
         small_transform(v, S, l.x, lane, wave);
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], small_signed_lam(l, r, S, lane, wave), acc[r]);
@@ -472,13 +553,19 @@ __global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
     small_pack<DITHER, MULTIK, UPDATE>(v, a, l, rk1, rlo, 0xFFFFFFFFu, 0u, tile, lane, wave);
     if constexpr (UPDATE) {
         __syncthreads(); // the words are published; l.x and l.lam are free, l.eps is the server's own stream still
+        float old[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint64_t i = base + small_l2(r, wave) + lane;
+            old[r] = i < a.len_out ? a.out[i] : 0.f;
+        }
         if (t < nblk) l.lam[t] *= a.out_coef;
-        small_from_bits(v, MULTIK ? a.planes : 1u, false, 0.5f * (float)a.K, lane, wave, [&](uint32_t p, uint32_t w) { return l.words[64u * p + w]; });
+        small_from_kept<MULTIK>(v, a, l, lane, wave);
         small_transform(v, S, l.x, lane, wave);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const uint64_t i = base + small_l2(r, wave) + lane;
-            if (i < a.len_out) small_store(a.out + i, v[r] * small_signed_lam(l, r, S, lane, wave), a.store_mode, a.delta);
+            if (i < a.len_out) a.out[i] = small_result(v[r] * small_signed_lam(l, r, S, lane, wave), old[r], a.store_mode, a.delta);
         }
     }
 }
@@ -493,7 +580,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
     constexpr uint32_t cb = kSmLog2 - HB;
     constexpr bool X = HB > 4;
     __shared__ float xb[kSmXWords];
-    __shared__ uint32_t eps[2][kSmEpsWords];
+    __shared__ __attribute__((aligned(16))) uint32_t eps[2][kSmEpsWords];
     __shared__ float red[4];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, slot = blockIdx.y;
     const uint64_t tile = blockIdx.x;
@@ -580,6 +667,12 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
         const float *const src = a.src + origin;
 #pragma unroll
         for (int r = 0; r < 16; ++r) v[r] = src[off(ua(r))];
+        const uint64_t room = a.len_out > origin ? a.len_out - origin : 0;
+        float *const dst = a.out + origin;
+        float old[16];
+        if (a.store_mode != STORE_SET)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) old[r] = off(uo(r)) < room ? dst[off(uo(r))] : 0.f;
         fill(eps[0], a.eps_in);
         const float c = a.scales[gb] * a.out_coef;
         stages_hi(v);
@@ -589,10 +682,9 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
         } else {
             __syncthreads();
         }
-        const uint64_t room = a.len_out > origin ? a.len_out - origin : 0;
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-            if (off(uo(r)) < room) small_store(a.out + origin + off(uo(r)), flip(c * v[r], eps[0], uo(r)), a.store_mode, a.delta);
+            if (off(uo(r)) < room) dst[off(uo(r))] = small_result(flip(c * v[r], eps[0], uo(r)), old[r], a.store_mode, a.delta);
     } else {
         float acc[16], next[16];
 #pragma unroll

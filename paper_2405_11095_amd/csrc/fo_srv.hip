@@ -7,6 +7,8 @@ namespace fo_host {
 int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, uint64_t round, uint64_t *bits_down,
                   float *scales_down, float *gbar_or_null, hipStream_t st)
 {
+    if (pl->small && pl->p.eps_mode != FO_EPS_SHARED_ALL)
+        return small_server(pl, bits_up, scales_up, round, bits_down, scales_down, gbar_or_null, st);
     const Rng r = rng_of(pl, round);
     const uint32_t M = pl->p.M;
     PtrTab none;

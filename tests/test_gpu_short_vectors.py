@@ -1,0 +1,45 @@
+"""The kernels for short vectors (tiles of 2^12 coordinates) at the edges of their range: every number of stages above
+the tile, blocks from 2^6 up, ragged ends inside a tile, both quantisers, the three eps modes and server amplitudes, the
+longest plan that takes them and the first that does not.  Every stage against the oracle."""
+import pytest
+
+from tests.parity import check_round_trip, gates
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # d, M, block_log2, options
+    (4096, 3, 0, {}),                                            # one whole tile
+    (4097, 2, 0, {}),                                            # one stage above the tile
+    (10_001, 2, 0, {"K": 3}),
+    (3 * 8192 + 1, 2, 0, {"server_scale": 1}),                   # three stages, measured-norm amplitude
+    (40_000, 33, 0, {}),                                         # four: the last without an exchange
+    (70_001, 2, 0, {"eps_mode": 1}),                             # five
+    (200_003, 2, 0, {"eps_mode": 2, "server_scale": 2}),         # six
+    (300_001, 2, 0, {"K": 15}),                                  # seven
+    (1_000_003, 2, 0, {"eps_mode": 1, "server_scale": 1, "K": 4}),  # eight
+    (4096 + 63, 2, 6, {"K": 255}),                               # second tile: one block, its last coordinate padding
+    (4096 * 3 + 1, 2, 7, {"server_scale": 1}),
+    (12_345, 64, 9, {"eps_mode": 1}),
+    (9_000, 2, 12, {"eps_mode": 2, "K": 2}),
+    (50_000, 2, 11, {"scale_rule": 0, "Bnorm": 60.0}),           # amplitude from the bound
+    (60_000, 2, 14, {"scale_rule": 0, "Bnorm": 60.0}),
+    (20_000, 2, 0, {"dither": 1}),
+    (3_000, 2, 8, {"dither": 1, "K": 3}),
+    (1 << 22, 2, 12, {}),                                        # the longest one-pass plan, and one block more
+    ((1 << 22) + 1, 2, 12, {}),
+    (1 << 20, 2, 20, {}),                                        # the longest transform, and the next
+    ((1 << 20) + 1, 2, 0, {}),
+]
+
+
+@pytest.mark.parametrize("d,M,blk,kw", CASES, ids=[f"{c[0]}-{c[1]}-{c[2]}" for c in CASES])
+def test_short_vectors(oracle, d, M, blk, kw):
+    import torch
+    from paper_2405_11095_amd import binding as B, inputs
+    gs = [inputs.heavy_tailed(d, m) for m in range(M)]
+    print(f"d={d} M={M} block_log2={blk} {kw}", flush=True)
+    rep = check_round_trip(oracle, B, gs, d=d, M=M, block_log2=blk, seed=0x5E + M, rnd=(1 << 32) + 3, delta=0.05,
+                           device=torch.device("cuda:0"), threads=16, **kw)
+    print(rep, flush=True)
+    gates(rep)
