@@ -69,6 +69,14 @@ struct ContigArgs {
     unsigned long long *stat_near;    // OUT_PACK, optional: per slot, += #{i : |z_i + tau_i| < 1e-6 lambda} (first dither)
 };
 
+// Chunk C of 16 of the 4096 coordinates at wave_src (the same address in every lane), into the registers of layout L0.
+template <int C>
+__device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src, uint32_t lane, std::integral_constant<int, C>)
+{
+    const float4 x = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(wave_src + C * 256u) + lane * 16u);
+    v[4 * C + 0] = x.x; v[4 * C + 1] = x.y; v[4 * C + 2] = x.z; v[4 * C + 3] = x.w;
+}
+
 // DITHER: uniform dither on (OUT_PACK only).  SMALLB: transform length 64 or 128, where the four
 // registers that share a dither draw belong to different blocks.  Both are compile-time so that the
 // per-value code is branch free.
@@ -86,10 +94,17 @@ struct ContigArgs {
 // swap their values through LDS, the lower forms x_lo + x_hi and the upper x_lo - x_hi, and each runs the fifteen
 // remaining stages on its own tile as usual.  The 2^16-point transform then costs one pass over memory instead
 // of two.  The block's norm is the sum of the two groups' partial sums.
-template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool GUARDED = true>
+// LOOP (PAIR, GUARDED = false): the caller walks over tiles.  v holds the tile's input on entry; `next` is where this wave's
+// part of the next tile begins (any readable tile if there is none), and its loads go out while this tile is quantised, each
+// chunk into the four registers that the group of coordinates before it has left.
+template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool GUARDED = true,
+          bool LOOP = false>
 __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &tab, const uint32_t tile, const uint32_t slot,
-                                            uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner = nullptr)
+                                            uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner,
+                                            typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type (&v)[kV],
+                                            const float *const next = nullptr)
 {
+    static_assert(!LOOP || (PAIR && !GUARDED && DITHER && !MULTIK && !STATS), "the walk over whole blocks of two tiles");
     static_assert(!PAIR || (IN == IN_GRAD && OUT == OUT_PACK && SC == 15 && !SMALLB), "pair mode: gradient in, bits out");
     using T = typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type;
     uint32_t *const xbuf = lds;
@@ -100,7 +115,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const float *const red_lo = PAIR ? reinterpret_cast<const float *>(((tile & 1u) ? lds_partner : lds) + kXWords + kEpsWords + kLamWords) : nullptr;
     const float *const red_hi = PAIR ? reinterpret_cast<const float *>(((tile & 1u) ? lds : lds_partner) + kXWords + kEpsWords + kLamWords) : nullptr;
 
-    const uint32_t lane = t & 63u, wave = t >> 6;
+    const uint32_t lane = t & 63u, wave = LOOP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6)) : t >> 6;
     const uint64_t base = (uint64_t)tile << kTileLog2;
     const uint32_t S = SC ? (uint32_t)SC : a.S;
     const uint32_t party = (a.party0 == 0xFFFFFFFFu) ? a.party0 : a.party0 + slot;
@@ -110,10 +125,10 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, eps_party };
     const RngKey key_dit = { a.k0, rk1, kDomainDither, rlo, party };
 
-    T v[kV];
-
     // ------------------------------------------------------------------ input, layout L0
-    if constexpr (IN == IN_GRAD || IN == IN_F32) {
+    if constexpr (LOOP) {
+        // already in v
+    } else if constexpr (IN == IN_GRAD || IN == IN_F32) {
         const float *src = (IN == IN_GRAD && a.use_tab) ? tab.p[slot]
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
         // GUARDED = false: the caller vouches that the whole tile lies inside the input (no per-chunk checks)
@@ -193,8 +208,12 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 const uint32_t cps = 1u << (G - 8u);      // chunks per segment
 #pragma unroll
                 for (int c = 0; c < 16; ++c) {
-                    acc += (v[4 * c] * v[4 * c] + v[4 * c + 1] * v[4 * c + 1]) +
-                           (v[4 * c + 2] * v[4 * c + 2] + v[4 * c + 3] * v[4 * c + 3]);
+                    if constexpr (PAIR) // spelled out: a block's amplitude is the same to the bit whichever kernel forms it
+                        acc += fmaf(v[4 * c], v[4 * c], v[4 * c + 1] * v[4 * c + 1]) +
+                               fmaf(v[4 * c + 2], v[4 * c + 2], v[4 * c + 3] * v[4 * c + 3]);
+                    else
+                        acc += (v[4 * c] * v[4 * c] + v[4 * c + 1] * v[4 * c + 1]) +
+                               (v[4 * c + 2] * v[4 * c + 2] + v[4 * c + 3] * v[4 * c + 3]);
                     if (((c + 1) & (cps - 1u)) == 0u) {
                         const float s = wave_sum(acc, 6);
                         if (lane == 0) red[wave * segs_per_wave + ((uint32_t)c >> (G - 8u))] = s;
@@ -213,7 +232,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 }
             }
         }
-        if (a.scales_only) {
+        if (!LOOP && a.scales_only) {
             // amplitudes only (used to agree on a common amplitude before any worker quantises)
             __syncthreads();
             if constexpr (PAIR) {
@@ -484,6 +503,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
         // and one integer compare.  T is rounded to 256 (1 in r), i.e. the threshold moves by at most lambda' 2^-24, a
         // hundred times below the near-tie margin.  A NaN amplitude gives all bits 0, as NaN comparisons do.
         uint32_t my_lo = 0u, my_hi = 0u;
+        float nv[kV]; // LOOP: the next tile
         static_for<16>([&](auto gc) {
             constexpr int g = decltype(gc)::value;
             uint32_t w[4];
@@ -508,12 +528,20 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 my_lo = write_lane<r>(my_lo, (uint32_t)word[s]);
                 my_hi = write_lane<r>(my_hi, (uint32_t)(word[s] >> 32));
             });
+            if constexpr (LOOP) {
+                load_chunk(nv, next, lane, gc);
+                __builtin_amdgcn_sched_barrier(0); // the load stays here: the registers it takes are free now
+            }
         });
         // lane j holds the word of register j
         const uint64_t gw = (uint64_t)tile * 512u +
                             ((lane & 1u) | ((lane >> 5) << 1) | (((lane >> 1) & 1u) << 2) | (wave << 3) | (((lane >> 2) & 7u) << 6));
         if (gw < a.W)
             static_cast<uint64_t *>(a.dst)[slot * a.dst_stride + gw] = ((uint64_t)my_hi << 32) | my_lo;
+        if constexpr (LOOP) {
+#pragma unroll
+            for (int r = 0; r < kV; ++r) v[r] = nv[r];
+        }
     } else if constexpr (OUT == OUT_PACK) {
         uint32_t my_lo = 0u, my_hi = 0u;
         const float tscale = a.sqrtb * 5.9604644775390625e-08f; // 2^-24: u = m * 2^-24 with m odd
@@ -589,7 +617,9 @@ template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0,
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, a.tile0 + blockIdx.x, blockIdx.y, lds, threadIdx.x);
+    typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type v[kV];
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, a.tile0 + blockIdx.x, blockIdx.y, lds, threadIdx.x,
+                                                                            nullptr, v);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.
@@ -598,8 +628,46 @@ __global__ __launch_bounds__(2 * kThreads) void k_contig_pair(const ContigArgs a
 {
     __shared__ uint32_t lds[2 * kLdsWords];
     const uint32_t h = threadIdx.x >> 9;
-    contig_tile<IN_GRAD, OUT_PACK, DITHER, false, 15, MULTIK, false, true, GUARDED>(a, tab, a.tile0 + 2u * blockIdx.x + h, blockIdx.y, lds + h * kLdsWords,
-                                                                           threadIdx.x & 511u, lds + (h ^ 1u) * kLdsWords);
+    float v[kV];
+    contig_tile<IN_GRAD, OUT_PACK, DITHER, false, 15, MULTIK, false, true, GUARDED>(
+        a, tab, a.tile0 + 2u * blockIdx.x + h, blockIdx.y, lds + h * kLdsWords, threadIdx.x & 511u, lds + (h ^ 1u) * kLdsWords, v);
+}
+
+// The same for the `nblk` first blocks of every slot, all of which lie inside the input whole.  A workgroup fills a
+// compute unit (128 registers per thread, 148 KiB of LDS), so nothing else runs there while it waits for a block's 256
+// KiB; it walks over the blocks instead and loads the next one while it quantises the present one (the quantiser's
+// Philox rounds are a third of the arithmetic, and it gives up four registers at a time).  n = 2^27, eight workers: the step
+// takes 2.06 ms, with one workgroup per block 2.41.
+static __global__ __launch_bounds__(2 * kThreads) void k_contig_pair_walk(const ContigArgs a, const PtrTab tab, const uint32_t nblk,
+                                                                   const uint32_t nslots)
+{
+    __shared__ uint32_t lds[2 * kLdsWords];
+    const uint32_t h = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 9));
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)((threadIdx.x >> 6) & 7u));
+    uint32_t t = threadIdx.x & 511u;
+    const uint32_t units = nblk * nslots;
+    auto source = [&](uint32_t unit) -> const float * {
+        const uint32_t slot = unit / nblk, blk = unit - slot * nblk;
+        const float *p = a.use_tab ? tab.p[slot] : static_cast<const float *>(a.src) + slot * a.src_stride;
+        return p + ((uint64_t)(2u * blk + h) << kTileLog2) + wave * 4096u;
+    };
+    uint32_t unit = blockIdx.x;
+    if (unit >= units) return;
+    float v[kV];
+    {
+        const float *first = source(unit);
+        static_for<16>([&](auto cc) { load_chunk(v, first, t & 63u, cc); });
+    }
+    for (;;) {
+        // addresses are formed anew for every block: kept from one to the next they cost more registers than there are
+        asm volatile("" : "+v"(t));
+        const uint32_t slot = unit / nblk, blk = unit - slot * nblk, after = unit + gridDim.x;
+        contig_tile<IN_GRAD, OUT_PACK, true, false, 15, false, false, true, false, true>(
+            a, tab, 2u * blk + h, slot, lds + h * kLdsWords, t, lds + (h ^ 1u) * kLdsWords, v, source(after < units ? after : unit));
+        if (after >= units) break;
+        unit = after;
+        __syncthreads(); // the last reads of LDS are done before the next block writes there
+    }
 }
 
 } // namespace fo

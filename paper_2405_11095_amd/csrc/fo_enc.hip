@@ -21,7 +21,12 @@ int launch_pair(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c, con
         const uint64_t full64 = c.len_in >> 16;
         const uint32_t nfull = (uint32_t)(full64 < grid.x ? full64 : grid.x);
         ContigArgs cc = c;
-        if (nfull) FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, false>, dim3(nfull, grid.y), block, st, cc, tab));
+        const uint32_t units = nfull * grid.y;
+        if (units && c.scales_only) // a read and a sum: nothing to load behind
+            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, false>, dim3(nfull, grid.y), block, st, cc, tab));
+        else if (units)
+            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair_walk, dim3(units < pl->num_cus ? units : pl->num_cus), block, st, cc, tab,
+                          nfull, (uint32_t)grid.y));
         if (nfull < grid.x) {
             cc.tile0 = 2u * nfull;
             FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, true>, dim3(grid.x - nfull, grid.y), block, st, cc, tab));

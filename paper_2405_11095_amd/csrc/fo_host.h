@@ -127,6 +127,10 @@ inline bool args_ok(const ContigArgs &c, const PtrTab &tab, int kid)
     if (kid == KID_COUNT_LOW && (c.M < 1 || c.M > FO_MAX_WORKERS)) return false;
     return !needs_scales || c.scales != nullptr;
 }
+inline bool args_ok(const ContigArgs &c, const PtrTab &tab, uint32_t nblk, uint32_t nslots, int kid) // k_contig_pair_walk
+{
+    return nblk >= 1 && nblk <= c.nblocks && nslots >= 1 && nslots <= FO_MAX_WORKERS && args_ok(c, tab, kid);
+}
 inline bool args_ok(const ContigArgs &c, int kid) // k_declow, k_decode_tile
 {
     if (kid == KID_DEC_PAIR) return c.src && c.dst && c.scales && c.logb == 16;
