@@ -57,6 +57,7 @@ struct ContigArgs {
     uint32_t tile0;         // first tile of this launch (a launch may cover a range of tiles)
     uint32_t src_pad;       // IN_F32: tile t of the intermediate starts at t * (2^15 + src_pad) (see StridedArgs)
     uint32_t dst_pad;       // k_declow: the same for its int16 output
+    uint32_t group_log2;    // k_declow<true>: log2 of the rows of a block (see Grouped16)
     uint32_t party0;        // party id of slot 0 (slot y is party0 + y); FO_PARTY_SERVER stays as is
     uint32_t eps_party0;    // same for the eps stream
     uint32_t k0, k1, round_lo;

@@ -5,7 +5,8 @@ namespace fo_host {
 
 int launch_declow(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c)
 {
-    return launch(pl, KID_DEC_LOW, k_declow, grid, dim3(kThreads), st, c);
+    if (c.group_log2) return launch(pl, KID_DEC_LOW, k_declow<true>, grid, dim3(kThreads), st, c);
+    return launch(pl, KID_DEC_LOW, k_declow<false>, grid, dim3(kThreads), st, c);
 }
 
 // Decode one party into out[len_out] with the given store mode.
@@ -46,6 +47,7 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
     if (pl->npass == 1 && !multik) {
         // int16 intermediate between the two passes (padded rows when it is the plan's own buffer)
         c.dst_pad = s.src_pad = tmp == pl->buf_a ? pl->pad16 : 0u;
+        c.group_log2 = s.hb > 10 ? s.hb : 0u;
         FO_TRY(launch_declow(pl, grid, st, c));
         s.src = tmp;
         FO_TRY((launch_strided<SM_DEC_LAST, true>(pl, KID_DEC_HIGH, grid, st, s, none)));

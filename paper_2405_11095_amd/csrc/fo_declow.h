@@ -179,7 +179,8 @@ __device__ __forceinline__ constexpr uint32_t declow_reg_dword(int r)
 // (Kernels that are not templates are static: these headers are included by several translation units.)
 // Uses src, src_stride (64-bit words between slots), dst, dst_stride (int16 elements between slots) and W
 // of the argument block; the transform length is at least 2^15, so every tile is complete.
-static __global__ __launch_bounds__(kThreads, 4) void k_declow(const ContigArgs a)
+template <bool GROUPED>
+__global__ __launch_bounds__(kThreads, 4) void k_declow(const ContigArgs a)
 {
     __shared__ uint32_t xbuf[kXWords];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
@@ -188,6 +189,16 @@ static __global__ __launch_bounds__(kThreads, 4) void k_declow(const ContigArgs 
     s16x2 v[32];
     declow_tile<15>(src, a.W, tile, 15u, xbuf, xbuf, v);
 
+    if constexpr (GROUPED) {
+        // a register's 256 bytes of a wave go to two groups of columns, a line each
+        const uint32_t row = tile & ((1u << a.group_log2) - 1u), half = Grouped16::group(a.group_log2) / 2u; // dwords of a group
+        uint32_t *const to = reinterpret_cast<uint32_t *>(static_cast<int16_t *>(a.dst) + slot * a.dst_stride +
+                                                          (uint64_t)(tile >> a.group_log2) * Grouped16::block(a.group_log2)) + row * 32u;
+        const uint32_t dl = (lane & 31u) + ((lane >> 5) | (wave << 3)) * half;
+#pragma unroll
+        for (int r = 0; r < 32; ++r) to[dl + (declow_reg_dword(r) >> 5) * half] = __builtin_bit_cast(uint32_t, v[r]);
+        return;
+    }
     // store: a wave writes 256 contiguous bytes per register
     uint32_t *dst = reinterpret_cast<uint32_t *>(static_cast<int16_t *>(a.dst) + slot * a.dst_stride + ((uint64_t)tile << kTileLog2) + (uint64_t)tile * a.dst_pad);
     const uint32_t dt = lane | (wave << 8);

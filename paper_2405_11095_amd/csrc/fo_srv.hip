@@ -176,6 +176,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
         ContigArgs c = contig_base(pl, r);
         c.src = bits_up; c.src_stride = pl->W;
         c.dst = pl->buf_a; c.dst_stride = pl->ntot + pl->ntiles * pl->pad16; c.dst_pad = pl->pad16;
+        c.group_log2 = pl->hb[0] > 10 ? pl->hb[0] : 0u;
         FO_TRY(launch_declow(pl, dim3((unsigned)pl->ntiles, M), st, c));
     }
     {

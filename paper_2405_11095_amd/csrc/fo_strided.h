@@ -386,6 +386,18 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         g.origin = (outer << (g.ls + hb)) + (cg << cb);
     }
     const uint64_t gb = g.origin >> a.logb; // the tile lies inside one block
+    // where the tile lies in the int16 intermediate: rows of the caller's pitch, or groups of columns (Grouped16)
+    constexpr bool GROUPED = IN16 && HB > 10;
+    StridedGeom g16 = g;
+    uint32_t pad16 = 0u;
+    if constexpr (GROUPED) {
+        const uint32_t col = (uint32_t)g.origin & (kTile - 1u);
+        g16.ls = 6u;
+        g16.origin = (g.origin >> (kTileLog2 + HB)) * Grouped16::block(HB) + (uint64_t)(col >> 6) * Grouped16::group(HB) + (col & 63u);
+    } else if constexpr (IN16) {
+        pad16 = a.src_pad;
+        g16.origin = g.origin + (g.origin >> g.ls) * pad16;
+    }
 
     // thread parts of the tile coordinate and of the element offset in both layouts
     const uint32_t uta = L::ta(lane, wave), utb = L::tb(lane, wave);
@@ -397,11 +409,10 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
 
     // ---- input of one tile (layout LA) as 32 pairs
     auto load_int = [&](int32_t (&v)[kSV], const void *src_base) {
-        const uint32_t spad = IN16 ? a.src_pad : 0u;
-        const uint32_t otp = ota + (uta >> cb) * spad;
+        const uint32_t otp = g16.off(uta) + (uta >> cb) * pad16;
 #pragma unroll
         for (int p = 0; p < kSP; ++p) {
-            const uint32_t ro = g.off(L::pa(p)) + (L::pa(p) >> cb) * spad; // wave-uniform
+            const uint32_t ro = g16.off(L::pa(p)) + (L::pa(p) >> cb) * pad16; // wave-uniform
             if constexpr (IN16) {
                 const uint32_t d = ld_at<uint32_t>(static_cast<const int16_t *>(src_base) + ro, otp * 2u);
                 v[2 * p] = (int32_t)(int16_t)(d & 0xFFFFu);
@@ -463,7 +474,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
                 v[2 * p + 1] = d.y;
             }
         } else {
-            const char *src = static_cast<const char *>(a.src) + (slot * a.src_stride + g.origin + (IN16 ? (g.origin >> g.ls) * a.src_pad : 0u)) * (IN16 ? 2u : 4u);
+            const char *src = static_cast<const char *>(a.src) + (slot * a.src_stride + g16.origin) * (IN16 ? 2u : 4u);
             load_int(v, src);
         }
 
@@ -568,11 +579,11 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
             }
         } else {
         uint32_t raw[kSP]; // packed tile of the next worker, in flight while the current one is transformed
-        const uint32_t otp = ota + (uta >> cb) * a.src_pad;
+        const uint32_t otp = g16.off(uta) + (uta >> cb) * pad16;
         auto request = [&](uint32_t m) {
-            const int16_t *src = static_cast<const int16_t *>(a.src) + (uint64_t)m * a.src_stride + g.origin + (g.origin >> g.ls) * a.src_pad;
+            const int16_t *src = static_cast<const int16_t *>(a.src) + (uint64_t)m * a.src_stride + g16.origin;
 #pragma unroll
-            for (int p = 0; p < kSP; ++p) raw[p] = ld_uniform<uint32_t>(src + g.off(L::pa(p)) + (L::pa(p) >> cb) * a.src_pad, otp * 2u);
+            for (int p = 0; p < kSP; ++p) raw[p] = ld_uniform<uint32_t>(src + g16.off(L::pa(p)) + (L::pa(p) >> cb) * pad16, otp * 2u);
         };
         // finish worker m, whose packed tile is in `raw`; with PREFETCH the registers of `raw` are refilled
         // with worker m + 1 as soon as they have been unpacked
@@ -614,7 +625,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         for (uint32_t m = 0; m + 1 < a.M; ++m) {
             // generic geometry: keep the per-register row offsets (functions of ls) from being hoisted out of
             // this loop and held in scalar registers for its whole duration
-            if constexpr (HB == 0) asm volatile("" : "+s"(g.ls));
+            if constexpr (HB == 0) asm volatile("" : "+s"(g.ls), "+s"(g16.ls));
             process(m, std::true_type{});
         }
         process(a.M - 1, std::false_type{});
