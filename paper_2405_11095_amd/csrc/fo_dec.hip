@@ -48,6 +48,9 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
         // int16 intermediate between the two passes (padded rows when it is the plan's own buffer)
         c.dst_pad = s.src_pad = tmp == pl->buf_a ? pl->pad16 : 0u;
         c.group_log2 = s.hb > 10 ? s.hb : 0u;
+        if (c.group_log2) // the eps words go behind the intermediate, which takes half of tmp
+            FO_TRY(launch_eps_table(pl, st, s, s.eps_party0, 1, s.eps_party0,
+                                    reinterpret_cast<int16_t *>(tmp) + pl->ntot + pl->ntiles * pl->pad16));
         FO_TRY(launch_declow(pl, grid, st, c));
         s.src = tmp;
         FO_TRY((launch_strided<SM_DEC_LAST, true>(pl, KID_DEC_HIGH, grid, st, s, none)));

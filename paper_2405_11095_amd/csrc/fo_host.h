@@ -36,13 +36,14 @@ enum KernelId {
     KID_SHALL,          // k_shall
     KID_ENC_PAIR,       // k_contig_pair
     KID_DEC_PAIR,       // k_decode_pair
+    KID_EPS_TABLE,      // k_eps_table
     KID_SCALES,         // k_finalize_scales / k_fill_scales / k_server_scales
     KID_COUNT
 };
 inline const char *const kKernelNames[KID_COUNT] = {
     "k_contig<IN_GRAD,OUT_PACK>", "k_strided<ENC_FIRST>", "k_strided<MID_F32>", "k_contig<IN_F32,OUT_PACK>",
     "k_decode_tile",  "k_declow", "k_strided<MID_I32>", "k_strided<DEC_LAST>",
-    "k_strided<SERVER>", "k_server_mfma", "k_contig<IN_COUNT>", "k_mean_mfma", "k_shall", "k_contig_pair", "k_decode_pair", "scale kernels",
+    "k_strided<SERVER>", "k_server_mfma", "k_contig<IN_COUNT>", "k_mean_mfma", "k_shall", "k_contig_pair", "k_decode_pair", "k_eps_table", "scale kernels",
 };
 
 struct Profiler {
@@ -183,6 +184,18 @@ int launch(fo_plan *pl, int kid, Kern kernel, dim3 grid, dim3 block, hipStream_t
         if (rc_) return rc_;       \
     } while (0)
 
+// The eps words of `nparty` parties (party0 and on, the last one `last`) for the strided pass s, into device memory `table`.
+inline int launch_eps_table(fo_plan *pl, hipStream_t st, StridedArgs &s, uint32_t party0, uint32_t nparty, uint32_t last, void *table)
+{
+    s.eps_table = static_cast<const uint32_t *>(table);
+    s.eps_stride = pl->ntot / 32;
+    const dim3 grid((unsigned)(pl->ntot >> 15), nparty), block(256);
+    uint32_t *const to = static_cast<uint32_t *>(table);
+    if (s.hb == 11)
+        return launch(pl, KID_EPS_TABLE, k_eps_table<11>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
+    return launch(pl, KID_EPS_TABLE, k_eps_table<12>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
+}
+
 // Strided kernels come in a generic form and ones compiled for ten, eleven and twelve stages next to the contiguous tile
 // (the middle pass of three-pass transforms never has more than eight).
 template <int MODE, bool IN16 = false>
@@ -192,6 +205,10 @@ int launch_strided(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const Stride
     if (s.hb == 10 && s.ls == (uint32_t)kTileLog2)
         return launch(pl, kid, k_strided<MODE, 10, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
     if constexpr (MODE != SM_MID_F32 && MODE != SM_MID_I32 && (MODE != SM_SERVER || IN16)) {
+        if (IN16 && s.hb > 10 && !s.eps_table) {
+            std::snprintf(g_hip_err, sizeof(g_hip_err), "internal: no eps table for %s", kKernelNames[kid]);
+            return FO_EHIP;
+        }
         if (s.hb == 11) return launch(pl, kid, k_strided<MODE, 11, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
         if (s.hb == 12) return launch(pl, kid, k_strided<MODE, 12, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
     }

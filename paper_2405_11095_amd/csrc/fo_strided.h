@@ -38,6 +38,8 @@ struct StridedArgs {
     uint64_t dst_stride;
     const float *scales;   // [slot or worker][nblocks]
     uint64_t scales_stride;
+    const uint32_t *eps_table; // int16 source and eleven or twelve stages, else NULL: the parties' eps words (k_eps_table)
+    uint64_t eps_stride;       // its words between parties
     float *partials;       // ENC_FIRST: [slot][ntiles] tile sums of squares
     float *gbar;           // SERVER: optional fp32 [ntot] copy of the mean
     uint64_t len_in, len_out;
@@ -151,6 +153,39 @@ __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, c
                 e |= ((word_at((grp << 5) | k) >> shift) & ((1u << cols) - 1u)) << k;
             epsw[grp] = e;
         }
+    }
+}
+
+// The eps words of all tiles of strided passes of eleven or twelve stages, as fill_eps gives them, tile after tile (1024
+// words each).  A generator block covers 128 columns of a row and a tile uses 16 or 8 of them, so a tile that draws its own
+// words spends 2048 or 4096 draws on 2^15 bits, a fifth of the server's vector instructions; here every block is drawn once
+// and its bits are dealt out through LDS.  256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them) of
+// row part (2^HB / 128) of block; blockIdx.y = party party0 + y, the last one `last`.
+template <int HB>
+__global__ __launch_bounds__(256) void k_eps_table(uint32_t k0, uint32_t k1, uint32_t round_lo, const unsigned long long *round_dev,
+                                                   uint32_t party0, uint32_t last, uint32_t *table, uint64_t stride)
+{
+    constexpr uint32_t cb = (uint32_t)kTileLog2 - HB, tiles = 256u >> cb, per_tile = (128u << cb) / 32u; // words
+    using Piece = typename std::conditional<cb == 3, uint8_t, uint16_t>::type; // a row of a tile
+    static_assert(sizeof(Piece) * 8u == 1u << cb, "eleven or twelve stages");
+    __shared__ uint32_t lds[1024];
+    const uint32_t t = threadIdx.x, row = t & 127u, half = t >> 7;
+    const uint32_t cpart = blockIdx.x & 127u, rpart = (blockIdx.x >> 7) & ((1u << (HB - 7)) - 1u), blk = blockIdx.x >> HB;
+    uint32_t rk1, rlo;
+    resolve_round(k1, round_lo, round_dev, rk1, rlo);
+    const RngKey key = { k0, rk1, kDomainEps, rlo, blockIdx.y + 1u == gridDim.y ? last : party0 + blockIdx.y };
+    const uint64_t i = ((uint64_t)blk << (kTileLog2 + HB)) + ((uint64_t)(rpart * 128u + row) << kTileLog2) + cpart * 256u + half * 128u;
+    uint32_t w[4];
+    philox((uint32_t)(i >> 7), key, w);
+    Piece *const pieces = reinterpret_cast<Piece *>(lds);
+#pragma unroll
+    for (uint32_t k = 0; k < tiles / 2u; ++k) pieces[(half * (tiles / 2u) + k) * 128u + row] = (Piece)(w[(k << cb) >> 5] >> ((k << cb) & 31u));
+    __syncthreads();
+    uint32_t *const out = table + blockIdx.y * stride + ((((uint64_t)blk << HB) + cpart * tiles) << 10) + rpart * per_tile;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t d = t + 256u * k;
+        out[((uint64_t)(d / per_tile) << 10) + d % per_tile] = lds[d];
     }
 }
 
@@ -323,7 +358,8 @@ __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const Str
     // re-encode: eps^s flip, then the same stages in reverse layout order
     const RngKey key_s = { a.k0, rk1, kDomainEps, rlo, a.eps_party0 };
     __syncthreads();
-    fill_eps<L::T>(epsw, g, key_s, t);
+    if (a.eps_table) epsw[t & 1023u] = a.eps_table[a.M * a.eps_stride + ((uint64_t)tile << 10) + (t & 1023u)];
+    else fill_eps<L::T>(epsw, g, key_s, t);
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < kSP; ++p)
@@ -429,7 +465,12 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         TV v[kSV];
         const uint32_t eps_party = (a.eps_party0 >= 0xFFFFFFFEu) ? a.eps_party0 : a.eps_party0 + slot;
         const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, eps_party };
-        if constexpr (MODE == SM_ENC_FIRST || MODE == SM_DEC_LAST) fill_eps<L::T>(epsw, g, key_eps, t);
+        if constexpr (MODE == SM_DEC_LAST && GROUPED) {
+#pragma unroll
+            for (uint32_t h = 0; h < 1024u / L::T; ++h) epsw[t + h * L::T] = a.eps_table[((uint64_t)tile << 10) + t + h * L::T];
+        } else if constexpr (MODE == SM_ENC_FIRST || MODE == SM_DEC_LAST) {
+            fill_eps<L::T>(epsw, g, key_eps, t);
+        }
 
         // ---------------------------------------------------------------- load (LA)
         if constexpr (MODE == SM_ENC_FIRST) {
@@ -598,13 +639,16 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
                 buf[2 * p] = (TB)(int16_t)(raw[p] & 0xFFFFu);
                 buf[2 * p + 1] = (TB)((int32_t)raw[p] >> 16);
             }
+            uint32_t eps_word = 0u;
+            if constexpr (GROUPED) eps_word = a.eps_table[m * a.eps_stride + ((uint64_t)tile << 10) + t];
             if constexpr (PREFETCH) request(m + 1);
             const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, m };
             // Two eps tables in turn: worker m's table is written while slow waves may still read worker m-1's,
             // and it is read after this iteration's barrier, which every wave reaches only when done with m-1.
             uint32_t *const epsm = epsw + (m & 1u) * kEpsWords;
-            fill_eps<L::T>(epsm, g, key_eps, t);
+            if constexpr (!GROUPED) fill_eps<L::T>(epsm, g, key_eps, t);
             stages_a<TB, LV>(buf, cb);
+            if constexpr (GROUPED) epsm[t] = eps_word;
             if (need_x) {
                 __syncthreads(); // the previous worker's exchange buffer is no longer read
                 exchange_wide<TB, LV>(buf, xbuf, lane, wave);
