@@ -27,6 +27,7 @@ constexpr uint32_t kLdsWords = kXWords + kEpsWords + kLamWords + kRedWords;
 // or 8 columns wide there, pieces of 32 or 16 bytes of every row; row-major they would lie 64 KiB apart.  Columns go in
 // groups of 64, one 128-byte line a row, the rows of a group one after the other: tiles that share lines read one
 // contiguous region.  A group is followed by a line of padding, so that groups are not a power of two apart.
+// n = 2^27, four workers: server pass 1118 -> 1045 us, low pass 206 -> 216 us.
 struct Grouped16 {
     static __device__ __forceinline__ constexpr uint32_t group(uint32_t log_rows) { return (64u << log_rows) + 64u; } // elements
     static __device__ __forceinline__ constexpr uint64_t block(uint32_t log_rows) { return (uint64_t)group(log_rows) * (kTile / 64u); }

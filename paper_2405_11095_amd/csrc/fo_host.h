@@ -291,7 +291,7 @@ constexpr SmallRule kSmallRules[4] = {
 // Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
 // Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a
 // second strided pass moves every intermediate once more, and on the server's side in int32 instead of int16: a step of
-// n = 2^27 with four workers takes 3.60 ms with one pass of twelve stages and 5.43 ms with passes of six and six.
+// n = 2^27 with four workers takes 3.39 ms with one pass of twelve stages and 5.43 ms with passes of six and six.
 // Thirteen would leave rows of 4 columns, less than one line's worth per eight tiles.
 constexpr uint32_t kMaxHigh = 12;
 

@@ -12,9 +12,10 @@
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
 // v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
-// M = 4): encode 1.16 ms for 3.75 GB, server 1.11 ms for 1.6 GB, decode 0.49 ms for 1.1 GB; the encode is bound by its
-// 32-byte row segments, the server by its instruction count (38 vector instructions per value and worker) next to the
-// latency of 16-byte ones.
+// M = 4): encode 1.17 ms for 3.75 GB, server 0.90 ms for 1.6 GB, decode 0.48 ms for 1.1 GB.  Encode and decode are bound by
+// the 32-byte row segments of the caller's vectors (an encode on tiles of 2^16 coordinates, with segments of 64 bytes but
+// one workgroup per compute unit, took 1.32 ms; a decode of 32 values per thread, with half the loads in flight, 0.54), the
+// server by its vector instructions.
 // Modes
 //   SM_ENC_FIRST : fp32 gradient (zero padded), eps flip on load, tile sum of squares -> fp32 intermediate
 //   SM_DEC_LAST  : integer intermediate -> lambda/sqrt(b) scaling, eps flip, store / SGD update (Def. 3.8)
@@ -159,8 +160,9 @@ __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, c
 // The eps words of all tiles of strided passes of eleven or twelve stages, as fill_eps gives them, tile after tile (1024
 // words each).  A generator block covers 128 columns of a row and a tile uses 16 or 8 of them, so a tile that draws its own
 // words spends 2048 or 4096 draws on 2^15 bits, a fifth of the server's vector instructions; here every block is drawn once
-// and its bits are dealt out through LDS.  256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them) of
-// row part (2^HB / 128) of block; blockIdx.y = party party0 + y, the last one `last`.
+// and its bits are dealt out through LDS.  n = 2^27, four workers: 19 us for the five parties, server pass 1045 -> 903 us.
+// 256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them) of row part (2^HB / 128) of block;
+// blockIdx.y = party party0 + y, the last one `last`.
 template <int HB>
 __global__ __launch_bounds__(256) void k_eps_table(uint32_t k0, uint32_t k1, uint32_t round_lo, const unsigned long long *round_dev,
                                                    uint32_t party0, uint32_t last, uint32_t *table, uint64_t stride)

@@ -13,9 +13,10 @@ pytestmark = pytest.mark.gpu
     ((1 << 26) + 5, 2, 0, {}),                                     # twelve stages, most of the second half padding
     ((1 << 27) - 3, 2, 27, {"eps_mode": 1, "server_scale": 1}),    # one summed transform, measured-norm amplitude
     ((1 << 26) + 70_001, 1, 26, {"K": 3}),                         # two blocks of eleven stages, int32 intermediate
+    (50_000_001, 2, 0, {}),                                        # eleven stages, independent workers, plain signs
     (1, 1, 26, {}),                                                # one coordinate: every tile but the first reads padding
     ((3 << 15) + 31, 1, 27, {}),                                   # ends inside a register's rows, on an odd coordinate
-], ids=["2p27", "2p27_shared_l2", "two_blocks_2p26_K3", "one", "odd_end"])
+], ids=["2p27", "2p27_shared_l2", "two_blocks_2p26_K3", "2p26", "one", "odd_end"])
 def test_two_pass_transforms_of_narrow_rows(oracle, d, M, blk, kw):
     import torch
     from paper_2405_11095_amd import binding as B, inputs
