@@ -14,7 +14,10 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
                   float *out, uint64_t len_out, uint32_t store_mode, float out_coef, float delta, float *tmp,
                   hipStream_t st)
 {
-    if (pl->small_dec) // its coefficient and length are the plan's, as every caller's
+    // Plain signs of at most half a tile of 2^15, transforms longer than the short vectors' tile: one launch here, two there
+    // (n = 2^13: 8.4 and 10.4 us, n = 2^14: 8.3 and 10.0; n = 2^17 in such blocks: 10.7 and 10.0; K = 4, n = 2^13: 13.7 and 10.1).
+    const bool half_tile = pl->logb > 12 && pl->ntot <= kTile / 2 && (party != FO_PARTY_SERVER || pl->p.K == 1);
+    if (pl->small_dec && !half_tile) // its coefficient and length are the plan's, as every caller's
         return small_decode(pl, bits, scales, round, party, out, store_mode, delta, tmp, st);
     const Rng r = rng_of(pl, round);
     PtrTab none;
