@@ -131,8 +131,8 @@ __device__ __forceinline__ T &ref_at(void *uniform_base, uint32_t byte_off)
 }
 
 // eps words of the tile, one 32-bit word per 32 consecutive tile coordinates (u >> 5).  Rows of 32 columns or more fill
-// a word by themselves; a word of narrower rows (cb = 3, 4) is put together from the 2^(5-cb) rows it covers.
-template <int T>
+// a word by themselves; a word of narrower rows (NARROW: cb = 3, 4) is put together from the 2^(5-cb) rows it covers.
+template <int T, bool NARROW>
 __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, const RngKey &key, uint32_t t)
 {
 #pragma unroll
@@ -145,7 +145,7 @@ __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, c
             const uint32_t sel = (uint32_t)(i >> 5) & 3u;
             return sel == 0 ? w[0] : sel == 1 ? w[1] : sel == 2 ? w[2] : w[3];
         };
-        if (g.cb >= 5u) {
+        if constexpr (!NARROW) {
             epsw[grp] = word_at(grp << 5);
         } else {
             const uint32_t cols = 1u << g.cb, shift = (uint32_t)g.origin & 31u; // the tile's columns inside their word
@@ -236,13 +236,18 @@ __device__ __forceinline__ void bfly_lane4(T (&v)[V])
     }
 }
 
-// stages on lane bits 2 .. 5 (u3 .. u6) and on the register bits of LA (register bit k <-> u bit 6 + NW + k)
-template <typename T, int LV>
+// stages on lane bits 4, 5 (u5, u6; with NARROW on 2 .. 5, u3 .. u6) and on the register bits of LA (register bit k <-> u bit
+// 6 + NW + k).  NARROW is left to the kernels compiled for eleven and twelve stages: the generic kernels, which never have
+// more than ten, would carry two stages per value that no call reaches (a third more instructions; the summed-sign server
+// pass of n = 2^24 took 2 % longer for them).
+template <typename T, int LV, bool NARROW>
 __device__ __forceinline__ void stages_a(T (&v)[1 << LV], uint32_t cb)
 {
     constexpr int V = 1 << LV, B1 = 7 + SL<LV>::NW; // u bit of register bit 1
-    if (cb <= 3u) bfly_dpp<2, V>(v, threadIdx.x & 63u);
-    if (cb <= 4u) bfly_dpp<3, V>(v, threadIdx.x & 63u);
+    if constexpr (NARROW) {
+        if (cb <= 3u) bfly_dpp<2, V>(v, threadIdx.x & 63u);
+        if (cb <= 4u) bfly_dpp<3, V>(v, threadIdx.x & 63u);
+    }
     if (cb <= 5u) bfly_lane4<T, V>(v);
     if (cb <= 6u) bfly_lane5<T, V>(v);
     if (cb <= (uint32_t)B1) bfly<T, 1, V>(v);
@@ -322,7 +327,8 @@ __device__ __forceinline__ void flip_pair(float &x0, float &x1, uint32_t wshift)
 // optional copy of the mean, the tile's sum of squares for the measured-norm amplitude, eps^s flip, the forward
 // stages of the re-encode in reverse layout order, store of the fp32 intermediate (Sec. 4, server-to-workers encoding).
 // All threads of the workgroup call it; xbuf (kTile words if WIDE, else kXWords) and epsw (kEpsWords) are free on entry.
-template <int LV, bool WIDE>
+// TABLE: the eps^s words come from a.eps_table.
+template <int LV, bool WIDE, bool NARROW = false, bool TABLE = false>
 __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const StridedArgs &a, const StridedGeom &g, uint32_t tile,
                                                 uint32_t rk1, uint32_t rlo, uint32_t *xbuf, uint32_t *epsw, float *red, bool need_x)
 {
@@ -360,8 +366,8 @@ __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const Str
     // re-encode: eps^s flip, then the same stages in reverse layout order
     const RngKey key_s = { a.k0, rk1, kDomainEps, rlo, a.eps_party0 };
     __syncthreads();
-    if (a.eps_table) epsw[t & 1023u] = a.eps_table[a.M * a.eps_stride + ((uint64_t)tile << 10) + (t & 1023u)];
-    else fill_eps<L::T>(epsw, g, key_s, t);
+    if constexpr (TABLE) epsw[t & 1023u] = a.eps_table[a.M * a.eps_stride + ((uint64_t)tile << 10) + (t & 1023u)];
+    else fill_eps<L::T, NARROW>(epsw, g, key_s, t);
     __syncthreads();
 #pragma unroll
     for (int p = 0; p < kSP; ++p)
@@ -371,7 +377,7 @@ __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const Str
         if constexpr (WIDE) exchange_wide<float, LV>(acc, xbuf, lane, wave);
         else exchange<float, LV>(acc, xbuf, lane, wave);
     }
-    stages_a<float, LV>(acc, cb);
+    stages_a<float, LV, NARROW>(acc, cb);
     float *dst = static_cast<float *>(a.dst) + g.origin + (g.origin >> g.ls) * a.dst_pad;
     const uint32_t otd = ota + (uta >> cb) * a.dst_pad;
 #pragma unroll
@@ -391,6 +397,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
     using L = SL<LV>;
     constexpr int kSV = L::V, kSP = L::P;
     constexpr bool FIN = (MODE == SM_ENC_FIRST || MODE == SM_MID_F32); // fp32 input
+    constexpr bool NARROW = HB > 10; // rows of fewer than 32 columns
     using TV = typename std::conditional<FIN, float, int32_t>::type;
     // the server pass holds so many registers that one workgroup fills a CU: it takes the whole-tile exchange
     constexpr bool WIDE = (MODE == SM_SERVER);
@@ -471,7 +478,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
 #pragma unroll
             for (uint32_t h = 0; h < 1024u / L::T; ++h) epsw[t + h * L::T] = a.eps_table[((uint64_t)tile << 10) + t + h * L::T];
         } else if constexpr (MODE == SM_ENC_FIRST || MODE == SM_DEC_LAST) {
-            fill_eps<L::T>(epsw, g, key_eps, t);
+            fill_eps<L::T, NARROW>(epsw, g, key_eps, t);
         }
 
         // ---------------------------------------------------------------- load (LA)
@@ -522,7 +529,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         }
 
         // ---------------------------------------------------------------- stages
-        stages_a<TV, LV>(v, cb);
+        stages_a<TV, LV, NARROW>(v, cb);
         if (need_x) {
             exchange<TV, LV>(v, xbuf, lane, wave);
             stages_b<TV, LV>(v, cb);
@@ -576,9 +583,9 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
             static_assert(!IN16, "the summed sign vectors need an int32 intermediate");
             int32_t v[kSV];
             const RngKey key_w = { a.k0, rk1, kDomainEps, rlo, 0xFFFFFFFEu };
-            fill_eps<L::T>(epsw, g, key_w, t);
+            fill_eps<L::T, NARROW>(epsw, g, key_w, t);
             load_int(v, static_cast<const char *>(a.src) + g.origin * 4u);
-            stages_a<int32_t, LV>(v, cb);
+            stages_a<int32_t, LV, NARROW>(v, cb);
             if (need_x) {
                 exchange<int32_t, LV>(v, xbuf, lane, wave);
                 stages_b<int32_t, LV>(v, cb);
@@ -603,8 +610,8 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
                 load_int(v, static_cast<const char *>(a.src) + ((uint64_t)m * a.src_stride + g.origin) * 4u);
                 const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, m };
                 uint32_t *const epsm = epsw + (m & 1u) * kEpsWords; // two tables in turn, as below
-                fill_eps<L::T>(epsm, g, key_eps, t);
-                stages_a<int32_t, LV>(v, cb);
+                fill_eps<L::T, NARROW>(epsm, g, key_eps, t);
+                stages_a<int32_t, LV, NARROW>(v, cb);
                 if (need_x) {
                     __syncthreads(); // the previous worker's exchange buffer is no longer read
                     exchange_wide<int32_t, LV>(v, xbuf, lane, wave);
@@ -648,8 +655,8 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
             // Two eps tables in turn: worker m's table is written while slow waves may still read worker m-1's,
             // and it is read after this iteration's barrier, which every wave reaches only when done with m-1.
             uint32_t *const epsm = epsw + (m & 1u) * kEpsWords;
-            if constexpr (!GROUPED) fill_eps<L::T>(epsm, g, key_eps, t);
-            stages_a<TB, LV>(buf, cb);
+            if constexpr (!GROUPED) fill_eps<L::T, NARROW>(epsm, g, key_eps, t);
+            stages_a<TB, LV, NARROW>(buf, cb);
             if constexpr (GROUPED) epsm[t] = eps_word;
             if (need_x) {
                 __syncthreads(); // the previous worker's exchange buffer is no longer read
@@ -677,7 +684,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
         process(a.M - 1, std::false_type{});
         }
         }
-        server_reencode<LV, WIDE>(acc, a, g, tile, rk1, rlo, xbuf, epsw, red, need_x);
+        server_reencode<LV, WIDE, NARROW, GROUPED>(acc, a, g, tile, rk1, rlo, xbuf, epsw, red, need_x);
     }
 }
 
