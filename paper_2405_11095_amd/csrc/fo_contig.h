@@ -101,9 +101,8 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool GUARDED = true,
           bool LOOP = false>
 __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &tab, const uint32_t tile, const uint32_t slot,
-                                            uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner,
-                                            typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type (&v)[kV],
-                                            const float *const next = nullptr)
+                                            uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner = nullptr,
+                                            float *const held = nullptr, const float *const next = nullptr)
 {
     static_assert(!LOOP || (PAIR && !GUARDED && DITHER && !MULTIK && !STATS), "the walk over whole blocks of two tiles");
     static_assert(!PAIR || (IN == IN_GRAD && OUT == OUT_PACK && SC == 15 && !SMALLB), "pair mode: gradient in, bits out");
@@ -126,9 +125,12 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const RngKey key_eps = { a.k0, rk1, kDomainEps, rlo, eps_party };
     const RngKey key_dit = { a.k0, rk1, kDomainDither, rlo, party };
 
+    T v[kV];
+
     // ------------------------------------------------------------------ input, layout L0
     if constexpr (LOOP) {
-        // already in v
+#pragma unroll
+        for (int r = 0; r < kV; ++r) v[r] = held[r];
     } else if constexpr (IN == IN_GRAD || IN == IN_F32) {
         const float *src = (IN == IN_GRAD && a.use_tab) ? tab.p[slot]
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
@@ -541,7 +543,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             static_cast<uint64_t *>(a.dst)[slot * a.dst_stride + gw] = ((uint64_t)my_hi << 32) | my_lo;
         if constexpr (LOOP) {
 #pragma unroll
-            for (int r = 0; r < kV; ++r) v[r] = nv[r];
+            for (int r = 0; r < kV; ++r) held[r] = nv[r];
         }
     } else if constexpr (OUT == OUT_PACK) {
         uint32_t my_lo = 0u, my_hi = 0u;
@@ -618,9 +620,7 @@ template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0,
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
-    typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type v[kV];
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, a.tile0 + blockIdx.x, blockIdx.y, lds, threadIdx.x,
-                                                                            nullptr, v);
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, a.tile0 + blockIdx.x, blockIdx.y, lds, threadIdx.x);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.
@@ -629,9 +629,8 @@ __global__ __launch_bounds__(2 * kThreads) void k_contig_pair(const ContigArgs a
 {
     __shared__ uint32_t lds[2 * kLdsWords];
     const uint32_t h = threadIdx.x >> 9;
-    float v[kV];
     contig_tile<IN_GRAD, OUT_PACK, DITHER, false, 15, MULTIK, false, true, GUARDED>(
-        a, tab, a.tile0 + 2u * blockIdx.x + h, blockIdx.y, lds + h * kLdsWords, threadIdx.x & 511u, lds + (h ^ 1u) * kLdsWords, v);
+        a, tab, a.tile0 + 2u * blockIdx.x + h, blockIdx.y, lds + h * kLdsWords, threadIdx.x & 511u, lds + (h ^ 1u) * kLdsWords);
 }
 
 // The same for the `nblk` first blocks of every slot, all of which lie inside the input whole.  A workgroup fills a
