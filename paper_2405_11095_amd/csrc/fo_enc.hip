@@ -22,11 +22,12 @@ int launch_pair(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c, con
         const uint32_t nfull = (uint32_t)(full64 < grid.x ? full64 : grid.x);
         ContigArgs cc = c;
         const uint32_t units = nfull * grid.y;
-        if (units && c.scales_only) // a read and a sum: nothing to load behind
+        // a read and a sum, or a block for every compute unit at most: nothing to load behind (255 blocks: 52.7 us here,
+        // 54.7 with the walk, which reads every block once more)
+        if (units && (c.scales_only || units <= pl->num_cus))
             FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, false>, dim3(nfull, grid.y), block, st, cc, tab));
         else if (units)
-            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair_walk, dim3(units < pl->num_cus ? units : pl->num_cus), block, st, cc, tab,
-                          nfull, (uint32_t)grid.y));
+            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair_walk, dim3(pl->num_cus), block, st, cc, tab, nfull, (uint32_t)grid.y));
         if (nfull < grid.x) {
             cc.tile0 = 2u * nfull;
             FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, true>, dim3(grid.x - nfull, grid.y), block, st, cc, tab));
