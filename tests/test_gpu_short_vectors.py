@@ -43,3 +43,40 @@ def test_short_vectors(oracle, d, M, blk, kw):
                            device=torch.device("cuda:0"), threads=16, **kw)
     print(rep, flush=True)
     gates(rep)
+
+
+@pytest.mark.parametrize("d,blk", [(5_000, 0), (10_000, 9), (4096 + 63, 6), (70_001, 0), (12_288, 12)])
+def test_counters_of_short_vectors(oracle, d, blk):
+    """fo_stats with every wave of every workgroup adding to the counters (an amplitude a quarter of the rule's clips a
+    known share of the coordinates) and with none adding (the rule's own), against counts from the oracle's vector: equal
+    but for coordinates within rounding of a threshold, of which there are fewer than three in a million."""
+    import numpy as np
+    import torch
+    from paper_2405_11095_amd import binding as B, inputs
+    dev = torch.device("cuda:0")
+    plan = B.Plan(d=d, M=2, block_log2=blk, seed=71)
+    p = oracle.params(d=d, M=2, block_log2=blk, seed=71)
+    stats = torch.zeros(2 * (B.MAX_WORKERS + 1), dtype=torch.int64, device=dev)
+    plan.fo_set_stats(stats)
+    g = inputs.gaussian(d, 1)
+    gd = torch.from_numpy(g).to(dev)
+    bits = torch.zeros(plan.W, dtype=torch.int64, device=dev)
+    lam = torch.zeros(plan.nblocks, device=dev)
+    plan.fo_encode(gd, 2, 1, bits, lam)
+    torch.cuda.synchronize()
+    near = B.MAX_WORKERS + 1
+    free = stats.cpu().numpy()
+    lam *= 0.25
+    stats.zero_()
+    plan.fo_encode(gd, 2, 1, bits, lam, flags=B.FORCE_SCALE)
+    torch.cuda.synchronize()
+    forced = stats.cpu().numpy()
+    for h, f in ((free, 4.0), (forced, 1.0)):
+        lam64 = lam.cpu().numpy().astype(np.float64) * f
+        r = oracle.encode(p, g.astype(np.float64), 2, 1, lam=lam64, want_margin=True, want_z=True)
+        each = np.repeat(lam64, plan.b)[:plan.ntot]
+        assert abs(int(h[1]) - int(np.count_nonzero(np.abs(r["z"]) > each))) <= 2
+        assert abs(int(h[near + 1]) - int(np.count_nonzero(np.abs(r["margin"]) < 1e-6 * each))) <= 2
+        assert h[0] == 0 and h[near] == 0 and h[B.MAX_WORKERS] == 0
+    assert forced[1] > plan.ntot // 100
+    plan.close()
