@@ -148,15 +148,18 @@ def main():
     # intermediates are int16), i.e. what the kernels have to move through HBM; rocprofv3's counters agree with it.
     W8 = n // 8
     ind = args.eps_mode == "independent"
-    pair = "k_contig_pair" in per_kernel
+    walk = "k_contig_pair_walk" in per_kernel
+    pair = walk or "k_contig_pair" in per_kernel
     n_low = (M + 1) if not pair else 1                       # vectors through the encode's low pass
     n_dlow = (M + (0 if "k_decode_pair" in per_kernel else 1)) if ind else 1
     model = {
         "k_strided<ENC_FIRST>": M * (4 * d + 4 * n),
         # with blocks of 2^16 the workers' encode is one pass (k_contig_pair); only the server re-encodes in two
         "k_contig<IN_F32,OUT_PACK>": n_low * (4 * n + W8),
-        # blocks of 2^16: the server's re-encode of the mean is one more vector through the pair kernel
-        "k_contig_pair": M * (4 * d + W8) + ((4 * n + W8) if "k_mean_mfma" in per_kernel else 0),
+        # blocks of 2^16: the server's re-encode of the mean is one more vector through the pair kernel.  The walk takes
+        # the whole blocks (of the mean, all of them); what is left beside it are the workers' ragged last blocks.
+        "k_contig_pair_walk": M * ((d >> 16) << 16) * 33 // 8 + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
+        "k_contig_pair": M * (4 * (d & 0xFFFF) + 8192) if walk else M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
         "k_declow": n_dlow * (W8 + 4 * n),
         "k_strided<SERVER>": (M * 4 * n + 4 * n) if ind else 8 * n,
         "k_server_mfma": M * 4 * n + 4 * n,
@@ -167,6 +170,16 @@ def main():
         "k_contig<IN_GRAD,OUT_PACK>": M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
         "k_decode_tile": W8 + 8 * d,
         "k_decode_pair": W8 + 8 * d,
+        # short vectors: fp32 intermediates on the decode side too; with independent eps a message goes straight on into
+        # its decoder's low stages (one more intermediate written), and a mean in one tile never leaves the chip
+        "k_small_high<ENC>": M * (4 * d + 4 * n),
+        "k_small_encode<GRAD>": M * (4 * d + W8),
+        "k_small_encode<MID>": (M + 1) * (8 * n + W8) if ind else M * (4 * n + W8) + (8 * n + W8 if args.eps_mode == "shared" else 0),
+        "k_small_decode<LOW>": (M * W8 if args.eps_mode == "shared" else W8) + 4 * n,
+        "k_small_high<SERVER>": (M * 4 * n + 4 * n) if ind else 8 * n,
+        "k_small_server": M * W8 + W8 + 8 * d,
+        "k_small_decode<FINAL>": W8 + 8 * d,
+        "k_small_high<DEC>": 4 * n + 8 * d,
     }
     moved = dict(model)
     moved["k_declow"] = n_dlow * (W8 + 2 * n)

@@ -233,8 +233,7 @@ int fo_set_stats(fo_plan *plan, fo_stats *stats);
  * not).  fo_profile_end waits for the recorded work, writes one entry per kernel that ran into
  * the host array out[cap], sets *count and stops recording.  At most 8192 launches are recorded. */
 typedef struct {
-    char name[48];     /* kernel name as it appears in a rocprofv3 kernel trace (template form); the kernels for short
-                        * vectors go by the name of the kernel that runs their stage on long ones */
+    char name[48];     /* kernel name as it appears in a rocprofv3 kernel trace (template form) */
     uint32_t launches;
     float total_ms;    /* sum of the launches' durations                                         */
 } fo_kernel_time;

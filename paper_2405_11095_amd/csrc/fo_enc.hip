@@ -27,7 +27,7 @@ int launch_pair(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c, con
         if (units && (c.scales_only || units <= pl->num_cus))
             FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, false>, dim3(nfull, grid.y), block, st, cc, tab));
         else if (units)
-            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair_walk, dim3(pl->num_cus), block, st, cc, tab, nfull, (uint32_t)grid.y));
+            FO_TRY(launch(pl, KID_ENC_PAIR_WALK, k_contig_pair_walk, dim3(pl->num_cus), block, st, cc, tab, nfull, (uint32_t)grid.y));
         if (nfull < grid.x) {
             cc.tile0 = 2u * nfull;
             FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, true>, dim3(grid.x - nfull, grid.y), block, st, cc, tab));

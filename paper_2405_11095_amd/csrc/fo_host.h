@@ -18,8 +18,7 @@
 #include "fo_server_tile.h"
 #include "fo_shall.h"
 
-// Kernel identities for the optional per-kernel timing (fo_profile_begin / fo_profile_end).  The kernels for short
-// vectors (fo_small.h) are recorded as the one here that runs the same stage.
+// Kernel identities for the optional per-kernel timing (fo_profile_begin / fo_profile_end).
 enum KernelId {
     KID_ENC_SINGLE = 0, // k_contig<IN_GRAD,OUT_PACK>
     KID_ENC_HIGH,       // k_strided<ENC_FIRST>
@@ -35,15 +34,26 @@ enum KernelId {
     KID_SERVER_TILE,    // k_mean_mfma
     KID_SHALL,          // k_shall
     KID_ENC_PAIR,       // k_contig_pair
+    KID_ENC_PAIR_WALK,  // k_contig_pair_walk
     KID_DEC_PAIR,       // k_decode_pair
     KID_EPS_TABLE,      // k_eps_table
+    KID_SM_ENC_HIGH,    // k_small_high<SMH_ENC>
+    KID_SM_ENC_GRAD,    // k_small_encode<SMI_GRAD>
+    KID_SM_ENC_MID,     // k_small_encode<SMI_MID>
+    KID_SM_DEC_LOW,     // k_small_decode<false>
+    KID_SM_SERVER_HIGH, // k_small_high<SMH_SERVER>
+    KID_SM_SERVER,      // k_small_server
+    KID_SM_DEC,         // k_small_decode<true>
+    KID_SM_DEC_HIGH,    // k_small_high<SMH_DEC>
     KID_SCALES,         // k_finalize_scales / k_fill_scales / k_server_scales
     KID_COUNT
 };
 inline const char *const kKernelNames[KID_COUNT] = {
     "k_contig<IN_GRAD,OUT_PACK>", "k_strided<ENC_FIRST>", "k_strided<MID_F32>", "k_contig<IN_F32,OUT_PACK>",
     "k_decode_tile",  "k_declow", "k_strided<MID_I32>", "k_strided<DEC_LAST>",
-    "k_strided<SERVER>", "k_server_mfma", "k_contig<IN_COUNT>", "k_mean_mfma", "k_shall", "k_contig_pair", "k_decode_pair", "k_eps_table", "scale kernels",
+    "k_strided<SERVER>", "k_server_mfma", "k_contig<IN_COUNT>", "k_mean_mfma", "k_shall", "k_contig_pair", "k_contig_pair_walk", "k_decode_pair", "k_eps_table",
+    "k_small_high<ENC>", "k_small_encode<GRAD>", "k_small_encode<MID>", "k_small_decode<LOW>", "k_small_high<SERVER>",
+    "k_small_server", "k_small_decode<FINAL>", "k_small_high<DEC>", "scale kernels",
 };
 
 struct Profiler {
@@ -120,11 +130,12 @@ inline Rng rng_of(const fo_plan *pl, uint64_t round)
 // Host-side guard against launching a kernel with a pointer it will dereference left unset.
 inline bool args_ok(const ContigArgs &c, const PtrTab &tab, int kid)
 {
-    const bool grad_in = kid == KID_ENC_SINGLE || kid == KID_ENC_PAIR;
+    const bool pair = kid == KID_ENC_PAIR || kid == KID_ENC_PAIR_WALK;
+    const bool grad_in = kid == KID_ENC_SINGLE || pair;
     if (!c.dst) return false;
-    if (kid == KID_ENC_PAIR && (c.logb != 16 || c.S != 15)) return false;
+    if (pair && (c.logb != 16 || c.S != 15)) return false;
     if (grad_in ? (c.use_tab ? !tab.p[0] : !c.src) : !c.src) return false;
-    const bool needs_scales = kid == KID_ENC_SINGLE || kid == KID_ENC_PAIR || kid == KID_ENC_LOW || kid == KID_DEC_SINGLE;
+    const bool needs_scales = kid == KID_ENC_SINGLE || pair || kid == KID_ENC_LOW || kid == KID_DEC_SINGLE;
     if (kid == KID_COUNT_LOW && (c.M < 1 || c.M > FO_MAX_WORKERS)) return false;
     return !needs_scales || c.scales != nullptr;
 }

@@ -10,12 +10,12 @@ inline bool args_ok(const SmallArgs &a, int kid)
     if (a.logb < 6 || a.logb > 20 || a.S != S || a.M < 1 || a.M > FO_MAX_WORKERS) return false;
     if (a.K < 1 || a.planes < 1 || a.planes > kSmPlanes || a.Kin < 1 || a.planes_in < 1 || a.planes_in > kSmPlanes) return false;
     switch (kid) {
-    case KID_ENC_SINGLE: case KID_ENC_LOW: return (a.src || a.use_tab) && a.scales && (a.bits_out || a.scales_only);
-    case KID_DEC_SINGLE: return a.bits_in && a.out && a.scales;
-    case KID_DEC_LOW: case KID_COUNT_LOW: return a.bits_in && a.mid;
-    case KID_SERVER_TILE: return a.bits_in && a.scales_up && a.scales && a.bits_out;
+    case KID_SM_ENC_GRAD: case KID_SM_ENC_MID: return (a.src || a.use_tab) && a.scales && (a.bits_out || a.scales_only);
+    case KID_SM_DEC: return a.bits_in && a.out && a.scales;
+    case KID_SM_DEC_LOW: return a.bits_in && a.mid;
+    case KID_SM_SERVER: return a.bits_in && a.scales_up && a.scales && a.bits_out;
     }
-    return a.logb > (uint32_t)kSmLog2 && (a.src || a.use_tab) && (kid == KID_DEC_HIGH ? a.out && a.scales : a.mid != nullptr);
+    return a.logb > (uint32_t)kSmLog2 && (a.src || a.use_tab) && (kid == KID_SM_DEC_HIGH ? a.out && a.scales : a.mid != nullptr);
 }
 inline bool args_ok(const SmallArgs &a, const PtrTab &tab, int kid) { return args_ok(a, kid) && (!a.use_tab || tab.p[0]); }
 
@@ -45,8 +45,9 @@ SmallArgs small_base(const fo_plan *pl, const Rng &r)
 
 // Stages above the contiguous tile, b > 2^12.
 template <int MODE>
-int launch_high(fo_plan *pl, int kid, uint32_t nslots, hipStream_t st, const SmallArgs &a, const PtrTab &tab)
+int launch_high(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a, const PtrTab &tab)
 {
+    const int kid = MODE == SMH_ENC ? KID_SM_ENC_HIGH : MODE == SMH_SERVER ? KID_SM_SERVER_HIGH : KID_SM_DEC_HIGH;
     const dim3 grid((unsigned)pl->sm_tiles, nslots), block(kSmThreads);
     switch (pl->logb - kSmLog2) {
     case 1: return launch(pl, kid, k_small_high<MODE, 1>, grid, block, st, a, tab);
@@ -66,7 +67,7 @@ int launch_low(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a,
 {
     const dim3 grid((unsigned)pl->sm_tiles, nslots), block(kSmThreads);
     const bool dither = a.dither == FO_DITHER_UNIFORM;
-    const int kid = IN == SMI_GRAD ? KID_ENC_SINGLE : KID_ENC_LOW;
+    const int kid = IN == SMI_GRAD ? KID_SM_ENC_GRAD : KID_SM_ENC_MID;
     if (a.K > 1) {
         if (dither) return launch(pl, kid, k_small_encode<IN, true, true, DEC>, grid, block, st, a, tab);
         return launch(pl, kid, k_small_encode<IN, false, true, DEC>, grid, block, st, a, tab);
@@ -81,11 +82,11 @@ int launch_mean(fo_plan *pl, hipStream_t st, const SmallArgs &a)
     const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads);
     const bool dither = a.dither == FO_DITHER_UNIFORM;
     if (a.K > 1) {
-        if (dither) return launch(pl, KID_SERVER_TILE, k_small_server<true, true, UPDATE>, grid, block, st, a);
-        return launch(pl, KID_SERVER_TILE, k_small_server<false, true, UPDATE>, grid, block, st, a);
+        if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, true, UPDATE>, grid, block, st, a);
+        return launch(pl, KID_SM_SERVER, k_small_server<false, true, UPDATE>, grid, block, st, a);
     }
-    if (dither) return launch(pl, KID_SERVER_TILE, k_small_server<true, false, UPDATE>, grid, block, st, a);
-    return launch(pl, KID_SERVER_TILE, k_small_server<false, false, UPDATE>, grid, block, st, a);
+    if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, false, UPDATE>, grid, block, st, a);
+    return launch(pl, KID_SM_SERVER, k_small_server<false, false, UPDATE>, grid, block, st, a);
 }
 
 // What the decoder of one party's message (`party`) needs besides its input.
@@ -149,7 +150,7 @@ int encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride
     }
     a.mid = tmp; a.mid_stride = tmp_stride;
     a.partials = pl->partials;
-    FO_TRY(launch_high<SMH_ENC>(pl, KID_ENC_HIGH, nslots, st, a, tab ? *tab : none));
+    FO_TRY(launch_high<SMH_ENC>(pl, nslots, st, a, tab ? *tab : none));
     a.src = tmp; a.src_stride = tmp_stride; a.use_tab = 0u;
     a.common = common ? nslots : 0u;
     if (dec) return launch_low<SMI_MID, true>(pl, nslots, st, a, none); // in place
@@ -166,14 +167,14 @@ int decode(fo_plan *pl, const uint64_t *bits, const float *mid, const float *sca
     set_decode(a, pl, party, scales, out, store_mode, delta);
     const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads);
     a.bits_in = bits;
-    if (pl->logb <= (uint32_t)kSmLog2) return launch(pl, KID_DEC_SINGLE, k_small_decode<true>, grid, block, st, a);
+    if (pl->logb <= (uint32_t)kSmLog2) return launch(pl, KID_SM_DEC, k_small_decode<true>, grid, block, st, a);
     if (!mid) {
         a.mid = tmp;
-        FO_TRY(launch(pl, KID_DEC_LOW, k_small_decode<false>, grid, block, st, a));
+        FO_TRY(launch(pl, KID_SM_DEC_LOW, k_small_decode<false>, grid, block, st, a));
         mid = tmp;
     }
     a.src = mid;
-    return launch_high<SMH_DEC>(pl, KID_DEC_HIGH, 1, st, a, none);
+    return launch_high<SMH_DEC>(pl, 1, st, a, none);
 }
 
 // `mids`: the workers' messages are in buf_a with the decoder's low stages done.  x: also decode the server's message
@@ -193,20 +194,16 @@ int server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, bool mi
     a.in_coef = 2.f * (pl->rsqrtb / (float)pl->p.M); // half values
     a.gbar = gbar;
     if (pl->logb <= (uint32_t)kSmLog2) return x ? launch_mean<true>(pl, st, a) : launch_mean<false>(pl, st, a);
-    if (pl->prof.on && a.scale_mode == SMS_SERVER) { // its own entry in the timing
-        FO_TRY(launch_server_scales(pl, st, scales_up, scales_down));
-        a.scale_mode = SMS_GIVEN;
-    }
     const uint32_t nmsg = shared ? 1u : pl->p.M;
     if (!mids) {
         SmallArgs d = a;
         d.mid = pl->buf_a; d.mid_stride = pl->ntot;
-        FO_TRY(launch(pl, shared ? KID_COUNT_LOW : KID_DEC_LOW, k_small_decode<false>, dim3((unsigned)pl->sm_tiles, nmsg), dim3(kSmThreads), st, d));
+        FO_TRY(launch(pl, KID_SM_DEC_LOW, k_small_decode<false>, dim3((unsigned)pl->sm_tiles, nmsg), dim3(kSmThreads), st, d));
     }
     a.src = pl->buf_a; a.src_stride = pl->ntot;
     a.mid = pl->buf_b;
     a.partials = a.scale_mode == SMS_MEASURED ? pl->partials : nullptr;
-    FO_TRY(launch_high<SMH_SERVER>(pl, KID_SERVER_HIGH, 1, st, a, none));
+    FO_TRY(launch_high<SMH_SERVER>(pl, 1, st, a, none));
     a.src = pl->buf_b;
     if (!x) return launch_low<SMI_MID, false>(pl, 1, st, a, none);
     FO_TRY((launch_low<SMI_MID, true>(pl, 1, st, a, none))); // in place
@@ -238,13 +235,11 @@ int small_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, u
 int small_step(fo_plan *pl, const PtrTab &tab, float *x, float delta, uint64_t round, bool scales_given, hipStream_t st)
 {
     const uint32_t M = pl->p.M, mode = pl->p.eps_mode;
-    // with independent eps the server decodes every message, so the workers' kernel goes on with the decoder.  While the
-    // launches are being timed the joined stages run as kernels of their own (the same arithmetic, stage by stage).
-    const bool split = pl->prof.on;
-    const bool mids = mode == FO_EPS_INDEPENDENT && pl->logb > (uint32_t)kSmLog2 && !split;
+    // with independent eps the server decodes every message, so the workers' kernel goes on with the decoder
+    const bool mids = mode == FO_EPS_INDEPENDENT && pl->logb > (uint32_t)kSmLog2;
     FO_TRY(encode(pl, &tab, nullptr, 0, pl->p.d, M, 0, round, scales_given, pl->bits_up, pl->W, pl->scales_up, pl->nblocks,
                   pl->buf_a, pl->ntot, st, mode != FO_EPS_INDEPENDENT, mids));
-    if (mode == FO_EPS_SHARED_ALL || split) { // no transform on the server, or stage by stage
+    if (mode == FO_EPS_SHARED_ALL) { // no transform on the server
         FO_TRY(launch_server(pl, pl->bits_up, pl->scales_up, round, pl->bits_down, pl->scales_down, nullptr, st));
         return decode(pl, pl->bits_down, nullptr, pl->scales_down, round, FO_PARTY_SERVER, x, STORE_AXPY, delta, pl->buf_a, st);
     }

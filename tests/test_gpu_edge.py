@@ -483,7 +483,7 @@ def test_per_kernel_timing(env):
     import time
     import torch
     O, B, inputs, dev = env
-    d, M = 1 << 18, 4
+    d, M = (1 << 21) + 9, 4            # n = 2^22: longer than what the kernels for short vectors take
     gs = [torch.from_numpy(inputs.gaussian(d, m)).to(dev) for m in range(M)]
     x = torch.zeros(d, dtype=torch.float32, device=dev)
     plan = B.Plan(d=d, M=M, seed=8)
@@ -503,6 +503,39 @@ def test_per_kernel_timing(env):
     assert sum(ms for _, ms in prof.values()) <= wall_ms
     with pytest.raises(B.FoError):
         plan.fo_profile_end()          # not recording any more
+    plan.close()
+
+
+@pytest.mark.parametrize("d,blk,M,kw,kernels", [
+    (1 << 18, 0, 4, {}, {"k_small_high<ENC>": 1, "k_small_encode<MID>": 2, "k_small_high<SERVER>": 1, "k_small_high<DEC>": 1}),
+    (1 << 18, 0, 4, {"eps_mode": 1}, {"k_small_high<ENC>": 1, "k_small_encode<MID>": 2, "k_small_decode<LOW>": 1,
+                                      "k_small_high<SERVER>": 1, "k_small_high<DEC>": 1}),
+    (100_000, 9, 4, {"server_scale": 1}, {"k_small_encode<GRAD>": 1, "k_small_server": 1}),
+    (200 << 16, 16, 1, {}, {"k_contig_pair": 2, "k_mean_mfma": 1, "k_decode_pair": 1, "scale kernels": 1}),
+    (300 << 16, 16, 1, {}, {"k_contig_pair_walk": 2, "k_mean_mfma": 1, "k_decode_pair": 1, "scale kernels": 1}),
+], ids=["short", "short_shared", "short_blocks", "pair", "pair_walk"])
+def test_timing_reports_the_launches_of_an_ordinary_step(env, d, blk, M, kw, kernels):
+    """Per-kernel timing brackets what a step launches and changes nothing about it: short vectors run their joined
+    kernels (no separate decoder or amplitude launch), with every kernel bracketed or one, and x comes out the same."""
+    import torch
+    O, B, inputs, dev = env
+    gs = [torch.from_numpy(inputs.gaussian(d, m)).to(dev) for m in range(M)]
+    plan = B.Plan(d=d, M=M, block_log2=blk, seed=8, **kw)
+    xs = []
+    for timed in (None, "all", *kernels):
+        x = torch.zeros(d, dtype=torch.float32, device=dev)
+        if timed == "all":
+            plan.fo_profile_begin()
+        elif timed:
+            plan.fo_profile_begin_kernel(timed)
+        for r in range(3):
+            plan.fo_step(gs, x, 0.01, r)
+        torch.cuda.synchronize()
+        xs.append(x)
+        if timed:
+            got = {k: n for k, (n, ms) in plan.fo_profile_end().items()}
+            assert got == {k: 3 * n for k, n in kernels.items() if timed in ("all", k)}, timed
+    assert all(torch.equal(x, xs[0]) for x in xs)
     plan.close()
 
 
