@@ -176,14 +176,15 @@ int fo_server_aggregate(fo_plan *plan, const uint64_t *bits_up, const float *sca
 
 /* fo_encode for callers that cannot allocate device memory: code running under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  No plan: the geometry is derived from *params (host) at every call,
- * and the intermediates of transforms longer than 2^15 points (an fp32 vector of the padded length and one sum
- * of squares per tile) live in a static device array of 4 * FO_NOALLOC_MAX_N bytes + 512 bytes (16 MiB) that every
- * device the library runs on holds until the process ends.  The call allocates and frees nothing, on the host or
+ * and the intermediates of transforms longer than 2^16 points (an fp32 vector of the padded length and one sum
+ * of squares per tile) live in a static device array of 4 * FO_NOALLOC_MAX_N + 4096 bytes (16 MiB) that every
+ * device the library runs on holds until the process ends.  Shorter transforms (whole vectors or blocks) need none.  The call allocates and frees nothing, on the host or
  * on the device, and enqueues kernels only.  Arguments, messages and amplitudes are those of fo_encode with a plan
  * made from the same parameters (bit for bit); diagnostic counters and per-kernel timing are not available.
  *   FO_ESIZE   the padded length exceeds FO_NOALLOC_MAX_N (fo_last_hip_error gives the figures)
- * All calls on one device share that device's array, which keeps the last call's contents (every call overwrites
- * what it reads, so nothing needs clearing): calls that overlap on one device, on whatever streams, race. */
+ * All calls on transforms longer than 2^16 points on one device share that device's array, which keeps the last
+ * call's contents (every call overwrites what it reads, so nothing needs clearing): two such calls that overlap on
+ * one device, on whatever streams, race. */
 int fo_encode_noalloc(const fo_params *params, const float *g, uint64_t round, uint32_t party, uint32_t flags,
                       uint64_t *bits, float *scales, void *hip_stream);
 

@@ -494,16 +494,17 @@ extern "C" int fo_encode_noalloc(const fo_params *params, const float *g, uint64
     if (party != FO_PARTY_SERVER && party >= pl.p.M) return FO_EINVAL;
     if (flags & ~FO_FORCE_SCALE) return FO_EINVAL;
     if (!aligned(g, 16) || !aligned(bits, 8) || !aligned(scales, 4)) return FO_EALIGN;
-    float *ptr = nullptr;
-    {
-        const int rc = noalloc_scratch(&ptr);
-        if (rc) return rc;
-    }
     pl.scratch = nullptr;
     pl.scratch_bytes = 0;
-    pl.buf_a = ptr;                 // fp32 intermediate between the strided and the contiguous pass
-    pl.buf_b = pl.buf_c = nullptr;  // transforms of up to 2^22 points never take a third pass
-    pl.partials = ptr + kNoallocMaxN;
+    pl.buf_a = pl.partials = nullptr; // transforms of up to 2^16 points touch no scratch: their calls may overlap
+    if (pl.logb > 16) {
+        float *ptr = nullptr;
+        const int rc = noalloc_scratch(&ptr);
+        if (rc) return rc;
+        pl.buf_a = ptr;               // fp32 intermediate between the strided and the contiguous pass
+        pl.partials = ptr + kNoallocMaxN;
+    }
+    pl.buf_b = pl.buf_c = nullptr;    // transforms of up to 2^22 points never take a third pass
     pl.bits_up = pl.bits_down = nullptr;
     pl.scales_up = pl.scales_down = nullptr;
     pl.blk_sums = nullptr;

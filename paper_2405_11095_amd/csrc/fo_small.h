@@ -15,6 +15,9 @@
 // Since the low stages of the encoder and of the decoder act on the same tile, fo_step runs them in one kernel: the
 // tile's signs go out as the message and straight back in as the decoder's input.
 //
+// k_small_block does both passes of an encode of up to 2^16 points in one launch without the intermediate, for the entry
+// point that has no scratch of its own.
+//
 // Index-bit choreography of the contiguous tile (b0..b11 = bits of the tile-local coordinate):
 //   L0 (16-byte loads): regs = (b0,b1,b8,b9)    lanes = (b2..b7)            waves = (b10,b11)
 //   L1                : regs = (b2..b5)         lanes = (b0,b1,b8,b9,b6,b7) waves = (b10,b11)
@@ -578,6 +581,16 @@ __global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
     }
 }
 
+// A thread's sum of squares of a strided tile, spelled out: a block's amplitude is the same to the bit whichever kernel forms it
+__device__ __forceinline__ float small_sumsq(const float (&v)[16])
+{
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; r += 4)
+        s += fmaf(v[r], v[r], v[r + 1] * v[r + 1]) + fmaf(v[r + 2], v[r + 2], v[r + 3] * v[r + 3]);
+    return s;
+}
+
 // The HB = 1 .. 8 stages above the contiguous tile: 2^HB rows, 2^12 apart, by 2^(12-HB) columns.  Tile coordinate
 // u = row << cb | column:
 //   A (loads): regs = (u8..u11), threads = (u0..u7)        B: regs = (u4..u7), threads = (u0..u3, u8..u11)
@@ -644,10 +657,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
         for (int r = 0; r < 16; ++r) v[r] = pb[r * 16];
     };
     auto tile_sumsq = [&](const float (&v)[16]) { // -> partials[slot][tile]; two barriers
-        float s = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; r += 4) s += (v[r] * v[r] + v[r + 1] * v[r + 1]) + (v[r + 2] * v[r + 2] + v[r + 3] * v[r + 3]);
-        s = wave_sum(s, 6);
+        const float s = wave_sum(small_sumsq(v), 6);
         if (lane == 0) red[wave] = s;
         __syncthreads();
         if (t == 0) a.partials[(uint64_t)slot * a.ntiles + tile] = (red[0] + red[1]) + (red[2] + red[3]);
@@ -744,6 +754,111 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
 #pragma unroll
         for (int r = 0; r < 16; ++r) dst[off(ua(r))] = acc[r];
     }
+}
+
+// Encoder of a block of 2^(12+HB) coordinates, HB = 1 .. 4, in one launch and without scratch memory: the workgroup of a
+// contiguous tile, row R of the block's 2^HB rows, reads the whole block in the strided tiles of k_small_high, adds up
+// their squares as it does and keeps the one output of the high stages that falls into its row, then goes on like
+// k_small_encode<SMI_MID>.  Every sum has the operands and the order it has in those two kernels, so the message and the
+// amplitude are theirs to the bit.  It reads a block 2^HB times (from the caches but once) to save the trip through memory
+// and the second launch: n = 2^13 6.8 us, n = 2^16 9.9, the two kernels 9.6 and 9.7; 2^21 coordinates in blocks of 2^16, where
+// the repeated reads are 128 MiB of cache traffic, 20.5 and 13.3 (the kernels for long vectors 42).
+// The strided tiles are dealt to up to four groups of 256 threads, whose loads are in flight together; the first group does
+// the contiguous tile.  No diagnostic counters (their barrier would be the first group's alone).
+constexpr uint32_t small_block_groups(int hb) { return hb == 1 ? 2u : 4u; }
+template <int HB, bool DITHER, bool MULTIK>
+__global__ __launch_bounds__(kSmThreads * small_block_groups(HB)) void k_small_block(const SmallArgs a)
+{
+    constexpr uint32_t G = small_block_groups(HB);
+    static_assert(HB >= 1 && HB <= 4, "the strided tiles' rows have 256 columns at least, so a thread's columns are t mod 256");
+    constexpr uint32_t cb = kSmLog2 - HB, C = 4 - HB; // C: register bits of a strided tile that are column bits
+    __shared__ SmallLds l;
+    __shared__ __attribute__((aligned(16))) uint32_t eps[kSmEpsWords << HB]; // of the whole block
+    const uint32_t t = threadIdx.x & 255u, grp = threadIdx.x >> 8, lane = t & 63u, wave = t >> 6;
+    const uint64_t tile = blockIdx.x, gb = tile >> HB, origin = gb << (kSmLog2 + HB);
+    const uint32_t row = (uint32_t)tile & ((1u << HB) - 1u);
+    uint32_t rk1, rlo;
+    resolve_round(a.k1, a.round_lo, a.round_dev, rk1, rlo);
+    const char *const src = reinterpret_cast<const char *>(a.src + origin);
+    constexpr uint32_t b = kSmTile << HB;
+    const uint32_t room = a.len_in >= origin + b ? b : a.len_in > origin ? (uint32_t)(a.len_in - origin) : 0u;
+    // coordinate, inside the block, of register r of strided tile j
+    auto at = [&](uint32_t j, int r) -> uint32_t {
+        const uint32_t u = t | (uint32_t)r << 8;
+        return ((u >> cb) << kSmLog2) + (j << cb) + (u & ((1u << cb) - 1u));
+    };
+    float v[16], next[16];
+    auto load = [&](uint32_t j) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) next[r] = at(j, r) < room ? *reinterpret_cast<const float *>(src + at(j, r) * 4u) : 0.f;
+    };
+    load(grp);
+    {
+        const RngKey key = { a.k0, rk1, kDomainEps, rlo, a.eps_party0 };
+        for (uint32_t c = threadIdx.x; c < (kSmEpsWords << HB) / 4u; c += kSmThreads * G) {
+            uint32_t w[4];
+            philox((uint32_t)(origin >> 7) + c, key, w);
+            *reinterpret_cast<uint4 *>(eps + 4u * c) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t j = grp; j < (1u << HB); j += G) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = next[r];
+        if (j + G < (1u << HB)) load(j + G);
+        const float s = wave_sum(small_sumsq(v), 6);
+        if (lane == 0u) l.red[4u * j + wave] = s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint32_t u = at(j, r);
+            v[r] = flip_if(v[r], (eps[u >> 5] >> (u & 31u)) & 1u);
+        }
+        // of every butterfly the output that this row keeps: a + b or a - b (the product by one is exact)
+        static_for<HB>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const float sgn = (row >> k) & 1u ? -1.f : 1.f;
+#pragma unroll
+            for (int h = 0; h < (1 << (HB - 1 - k)); ++h)
+#pragma unroll
+                for (int c = 0; c < (1 << C); ++c) v[(h << C) | c] = fmaf(v[((2 * h + 1) << C) | c], sgn, v[((2 * h) << C) | c]);
+        });
+#pragma unroll
+        for (int c = 0; c < (1 << C); ++c) {
+            const uint32_t col = (j << cb) + t + 256u * (uint32_t)c;
+            l.x[col + 4u * (col >> 6)] = v[c];
+        }
+    }
+    __syncthreads();
+    if (grp != 0u) {
+        __syncthreads(); // the one in small_transform
+        return;
+    }
+    float lam;
+    if (a.scale_mode == SMS_MEASURED) {
+        double d = 0.0;
+        if (lane < (1u << HB)) d = (double)((l.red[4u * lane] + l.red[4u * lane + 1u]) + (l.red[4u * lane + 2u] + l.red[4u * lane + 3u]));
+#pragma unroll
+        for (int k = 0; k < 6; ++k) d += __shfl_xor(d, 1 << k, 64);
+        lam = a.coef * (float)sqrt(d);
+    } else {
+        lam = a.scales[gb];
+    }
+    if (t == 0) {
+        l.lam[0] = lam;
+        l.kq[0] = -128.f / (lam * (a.sqrtb * 5.9604644775390625e-08f));
+        if (a.scale_mode != SMS_GIVEN && row == 0u) a.scales[gb] = lam;
+    }
+    {
+        const float *const p = l.x + wave * 1088u + lane * 4u + 4u * (lane >> 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 x = *reinterpret_cast<const float4 *>(p + 272 * q);
+            v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+        }
+    }
+    small_transform(v, 12u, l.x, lane, wave); // its barrier publishes l.lam
+    small_pack<DITHER, MULTIK, false>(v, a, l, rk1, rlo, a.party0, 0u, tile, lane, wave);
 }
 
 } // namespace fo

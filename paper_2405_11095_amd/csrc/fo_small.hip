@@ -89,6 +89,21 @@ int launch_mean(fo_plan *pl, hipStream_t st, const SmallArgs &a)
     return launch(pl, KID_SM_SERVER, k_small_server<false, false, UPDATE>, grid, block, st, a);
 }
 
+// Both passes of the encoder in one launch, 2^12 < b <= 2^16.
+template <int HB>
+int launch_block(fo_plan *pl, hipStream_t st, const SmallArgs &a)
+{
+    const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads * small_block_groups(HB));
+    const bool dither = a.dither == FO_DITHER_UNIFORM;
+    if (a.stat_clipped) return FO_EINVAL;
+    if (a.K > 1) {
+        if (dither) return launch(pl, KID_SM_ENC_GRAD, k_small_block<HB, true, true>, grid, block, st, a);
+        return launch(pl, KID_SM_ENC_GRAD, k_small_block<HB, false, true>, grid, block, st, a);
+    }
+    if (dither) return launch(pl, KID_SM_ENC_GRAD, k_small_block<HB, true, false>, grid, block, st, a);
+    return launch(pl, KID_SM_ENC_GRAD, k_small_block<HB, false, false>, grid, block, st, a);
+}
+
 // What the decoder of one party's message (`party`) needs besides its input.
 void set_decode(SmallArgs &a, const fo_plan *pl, uint32_t party, const float *scales, float *out, uint32_t store_mode, float delta)
 {
@@ -122,7 +137,8 @@ void set_server(SmallArgs &a, const fo_plan *pl, const float *scales_up, uint64_
     set_stats(a, pl, FO_PARTY_SERVER);
 }
 
-// `dec`: leave the decoder's low stages of the messages in buf_a, one slot per party (b > 2^12)
+// `dec`: leave the decoder's low stages of the messages in buf_a, one slot per party (b > 2^12).  tmp == nullptr (no scratch
+// to be had, fo_encode_noalloc): one vector of blocks of at most 2^16 coordinates.
 int encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride, uint64_t len_in, uint32_t nslots, uint32_t party0,
            uint64_t round, bool scales_given, uint64_t *bits, uint64_t bits_stride, float *scales, uint64_t scales_stride, float *tmp,
            uint64_t tmp_stride, hipStream_t st, bool common, bool dec)
@@ -147,6 +163,16 @@ int encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride
             a.scale_mode = SMS_GIVEN;
         }
         return launch_low<SMI_GRAD, false>(pl, nslots, st, a, tab ? *tab : none);
+    }
+    if (!tmp) {
+        if (tab || nslots != 1 || dec) return FO_EINVAL;
+        switch (pl->logb - kSmLog2) {
+        case 1: return launch_block<1>(pl, st, a);
+        case 2: return launch_block<2>(pl, st, a);
+        case 3: return launch_block<3>(pl, st, a);
+        case 4: return launch_block<4>(pl, st, a);
+        }
+        return FO_EINVAL;
     }
     a.mid = tmp; a.mid_stride = tmp_stride;
     a.partials = pl->partials;

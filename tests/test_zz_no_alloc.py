@@ -8,6 +8,8 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+SERVER = 0xFFFFFFFF
+
 
 @pytest.fixture(scope="module")
 def env():
@@ -82,3 +84,75 @@ def test_noalloc_rejects_what_it_cannot_take(env):
     with pytest.raises(B.FoError) as e:
         B.fo_encode_noalloc(p, g[1:], 0, 0, bits, lam)              # gradient not 16-byte aligned
     assert e.value.code == B.EALIGN
+
+
+# every number of stages above a tile of 2^12, whole and ragged, one block and several; both quantisers, both dithers, both
+# sources of the amplitude
+ONE_LAUNCH = [
+    # d, block_log2, party, options
+    (8192, 0, 0, {}),
+    (4097, 0, 1, {}),                                     # all of the second row but one coordinate is padding
+    (10_001, 0, SERVER, {"K": 3}),
+    (16_385 + 4096, 0, 0, {"dither": 1}),
+    (32_767, 0, 1, {"scale_rule": 0, "B": 60.0}),
+    (65_536, 0, 0, {}),
+    (40_000, 0, SERVER, {"K": 255}),
+    (33_000, 0, SERVER, {"K": 2, "dither": 1}),
+    (100_001, 13, 1, {}),
+    ((1 << 20) - 1, 14, 0, {"eps_mode": 1}),
+    (70_000, 15, SERVER, {}),
+    ((1 << 21) - 70_001, 16, 1, {}),
+]
+
+
+@pytest.mark.parametrize("d,blk,party,kw", ONE_LAUNCH, ids=[f"{c[0]}-{c[1]}" for c in ONE_LAUNCH])
+def test_noalloc_encode_in_one_launch_equals_plan_encode(env, d, blk, party, kw):
+    """Transforms of 2^13 to 2^16 points: the plan's two kernels and the one without scratch, to the bit."""
+    import torch
+    B, inputs, dev = env
+    print(f"d={d} block_log2={blk} party={party:#x} {kw}", flush=True)
+    plan = B.Plan(d=d, M=2, block_log2=blk, seed=d, **kw)
+    n = plan.ntot if party == SERVER else d
+    g = torch.from_numpy(inputs.heavy_tailed(n, 1)).to(dev)
+    planes = plan.planes if party == SERVER else 1
+    for flags in (0, B.FORCE_SCALE):
+        out = []
+        for noalloc in (False, True):
+            bits = torch.full((planes, plan.W), 0x55 if noalloc else 0xAA, dtype=torch.int64, device=dev)
+            lam = torch.full((plan.nblocks,), 0.02 if flags else -1.0, device=dev)
+            if noalloc:
+                B.fo_encode_noalloc(plan.params, g, 3, party, bits, lam, flags=flags)
+            else:
+                plan.fo_encode(g, 3, party, bits, lam, flags=flags)
+            out.append((bits, lam))
+        assert torch.equal(out[0][1], out[1][1]) and bool((out[0][1] > 0).all())
+        assert torch.equal(out[0][0], out[1][0])
+    plan.close()
+
+
+def test_noalloc_encodes_of_short_transforms_may_overlap(env):
+    """No scratch is shared by transforms of up to 2^16 points: calls in flight on four streams at once give what each
+    gives alone."""
+    import torch
+    B, inputs, dev = env
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    shapes = [(65_536, 0), (30_000, 0), (150_000, 14), (9_000, 0)]
+    work = []
+    for k, (d, blk) in enumerate(shapes):
+        plan = B.Plan(d=d, M=1, block_log2=blk, seed=k)
+        g = torch.from_numpy(inputs.gaussian(d, k)).to(dev)
+        rounds = []
+        for r in range(12):
+            want, lam = torch.zeros(plan.W, dtype=torch.int64, device=dev), torch.zeros(plan.nblocks, device=dev)
+            plan.fo_encode(g, r, 0, want, lam)
+            rounds.append((want, lam, torch.zeros_like(want), torch.zeros_like(lam)))
+        work.append((plan, g, rounds))
+    torch.cuda.synchronize()
+    for r in range(12):
+        for s, (plan, g, rounds) in zip(streams, work):
+            B.fo_encode_noalloc(plan.params, g, r, 0, rounds[r][2], rounds[r][3], stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    for plan, g, rounds in work:
+        for want, lam, bits, lam2 in rounds:
+            assert torch.equal(bits, want) and torch.equal(lam2, lam)
+        plan.close()
