@@ -285,8 +285,7 @@ extern "C" int fo_decode(fo_plan *pl, const uint64_t *bits, const float *scales,
     if (!pl || !bits || !scales || !out) return FO_EINVAL;
     if (party != FO_PARTY_SERVER && party >= pl->p.M) return FO_EINVAL;
     if (!aligned(bits, 8) || !aligned(scales, 4) || !aligned(out, 16)) return FO_EALIGN;
-    return launch_decode(pl, bits, scales, round, party, out, pl->p.d, STORE_SET, pl->rsqrtb, 0.f, pl->buf_a,
-                         static_cast<hipStream_t>(hip_stream));
+    return launch_decode(pl, bits, scales, round, party, out, STORE_SET, 0.f, pl->buf_a, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int fo_server_aggregate(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, uint64_t round,
@@ -340,8 +339,7 @@ extern "C" int fo_step(fo_plan *pl, const float *const *g, float *x, float delta
     if (rc) return rc;
     rc = launch_server(pl, pl->bits_up, pl->scales_up, round, pl->bits_down, pl->scales_down, nullptr, st);
     if (rc) return rc;
-    return launch_decode(pl, pl->bits_down, pl->scales_down, round, FO_PARTY_SERVER, x, pl->p.d, STORE_AXPY, pl->rsqrtb,
-                         delta, pl->buf_a, st);
+    return launch_decode(pl, pl->bits_down, pl->scales_down, round, FO_PARTY_SERVER, x, STORE_AXPY, delta, pl->buf_a, st);
 }
 
 extern "C" int fo_step_dev_round(fo_plan *pl, const float *const *g, float *x, float delta, const uint64_t *round_dev,

@@ -9,15 +9,14 @@ int launch_declow(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c)
     return launch(pl, KID_DEC_LOW, k_declow<false>, grid, dim3(kThreads), st, c);
 }
 
-// Decode one party into out[len_out] with the given store mode.
+// Decode one party into out[d] with the given store mode.
 int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64_t round, uint32_t party,
-                  float *out, uint64_t len_out, uint32_t store_mode, float out_coef, float delta, float *tmp,
-                  hipStream_t st)
+                  float *out, uint32_t store_mode, float delta, float *tmp, hipStream_t st)
 {
     // Plain signs of at most half a tile of 2^15, transforms longer than the short vectors' tile: one launch here, two there
     // (n = 2^13: 8.4 and 10.4 us, n = 2^14: 8.3 and 10.0; n = 2^17 in such blocks: 10.7 and 10.0; K = 4, n = 2^13: 13.7 and 10.1).
     const bool half_tile = pl->logb > 12 && pl->ntot <= kTile / 2 && (party != FO_PARTY_SERVER || pl->p.K == 1);
-    if (pl->small_dec && !half_tile) // its coefficient and length are the plan's, as every caller's
+    if (pl->small_dec && !half_tile)
         return small_decode(pl, bits, scales, round, party, out, store_mode, delta, tmp, st);
     const Rng r = rng_of(pl, round);
     PtrTab none;
@@ -30,7 +29,8 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
     set_quantiser(c, pl, party);
     const bool multik = c.K > 1;
     // the decode-side transforms carry every value divided by two (see fo_contig.h); D = (lambda / K) D_eps H^T q
-    out_coef *= 2.f / (float)c.K;
+    const float out_coef = pl->rsqrtb * (2.f / (float)c.K);
+    const uint64_t len_out = pl->p.d;
     if (pl->npass == 0) {
         c.dst = out; c.len_out = len_out; c.store_mode = store_mode; c.out_coef = out_coef; c.delta = delta;
         if (multik) FO_TRY(launch(pl, KID_DEC_SINGLE, (k_contig<IN_BITS, OUT_F32, false, false, 0, true>), grid, block, st, c, none));

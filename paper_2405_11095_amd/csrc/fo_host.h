@@ -344,8 +344,7 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
 // fo_dec.hip
 int launch_declow(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c);
 int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64_t round, uint32_t party,
-                  float *out, uint64_t len_out, uint32_t store_mode, float out_coef, float delta, float *tmp,
-                  hipStream_t st);
+                  float *out, uint32_t store_mode, float delta, float *tmp, hipStream_t st);
 
 // fo_srv.hip
 int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, uint64_t round, uint64_t *bits_down,
