@@ -56,7 +56,8 @@ def test_bad_parameters_are_rejected_on_the_host(lib):
     # lambda^s = lambda is admissible only when the server shares the workers' eps
     assert create(server_scale=2, eps_mode=0) == B.EINVAL and create(server_scale=2, eps_mode=1) == B.EINVAL
     assert create(d=(1 << 30) + 1) == B.EINVAL
-    assert create(d=(1 << 26), M=32, eps_mode=1) == B.EINVAL    # the same limit for a three-pass transform (M b = 2^31)
+    assert create(d=(1 << 26), M=32, eps_mode=1) == B.EINVAL    # the same limit for eleven strided stages (M b = 2^31)
+    assert create(d=(1 << 28), M=8, eps_mode=2) == B.EINVAL     # and for three passes
     assert create(d=(1 << 25), M=64, eps_mode=1) == B.EINVAL    # M b = 2^31 would overflow the summed sign vectors
     assert lib.fo_plan_create(None, None) == B.EINVAL
     # NULL plan in the hot calls

@@ -27,8 +27,9 @@ def _encode(B, torch, dev, plan, g, rnd, party, flags=0, scales=None):
 @pytest.mark.parametrize("d,blk", [(1 << 15, 0), (1 << 16, 0), (3 << 16, 16), (1 << 18, 0), (1 << 14, 10), (1000, 6)])
 def test_decode_of_walsh_rows_is_a_spike(env, d, blk):
     """A message that is row j of the Walsh matrix decodes to lambda sqrt(b) eps_j e_j: the largest value an inverse
-    transform can produce (all b signs add up), elsewhere exact zeros.  j = 0 is the all-ones message.  Exercises
-    the integer decode paths at the end of their range (2^14, 2^15 and 2^16 in half values) and their offsets."""
+    transform can produce (all b signs add up), elsewhere exact zeros.  j = 0 is the all-ones message.  These sizes
+    take the decoder for short vectors; test_gpu_long_plans.py and test_gpu_three_pass.py send such rows through the
+    integer decode paths (2^14 to 2^27 in half values, with their offsets)."""
     import torch
     O, B, inputs, dev = env
     plan = B.Plan(d=d, M=2, block_log2=blk, seed=19)
@@ -63,8 +64,8 @@ def test_decode_of_walsh_rows_is_a_spike(env, d, blk):
 def test_extreme_messages_through_the_server(env, d, blk):
     """Both workers send the all-ones message: the inverse transform's value at the first coordinate of a block is
     b, the largest integer the decode side ever holds (for n = 2^25: 2^24 in half values in the fp32 stages of the
-    server pass, still exact).  Mean, downlink bits and one worker decode against the oracle, for the two-pass
-    server, the single-tile mean kernel and blocks of two tiles."""
+    server pass, still exact).  Mean, downlink bits and one worker decode against the oracle, for the two-pass server of
+    2^25 and the server for short vectors (the single-tile mean and blocks of two tiles: test_gpu_long_plans.py)."""
     import torch
     O, B, inputs, dev = env
     M, rnd = 2, 6
@@ -209,7 +210,7 @@ def test_parameter_variants(env, name, kw):
     ("two_pass", (1 << 18) + 11, 7, 0, 1),
     ("blocked_b65536", (1 << 18) + 11, 3, 16, 2),
     ("n2p25", 25_557_032, 3, 0, 1),
-    ("three_pass", (1 << 25) + 5, 2, 0, 1),
+    ("n2p26", (1 << 25) + 5, 2, 0, 1),
 ])
 def test_all_shared_eps_zero_transform_server(env, name, d, M, blk, K):
     """The server shares the workers' eps: its pre-quantisation vector is (lambda / M)(2 c - M) and the kernel
@@ -316,8 +317,8 @@ def test_single_worker_and_odd_worker_counts(env):
         gates(rep)
 
 
-def test_three_pass_transform(env):
-    """n = 2^26: two strided passes around the contiguous one."""
+def test_transform_of_2p26(env):
+    """n = 2^26: eleven strided stages, over rows of sixteen columns (three passes: test_gpu_three_pass.py)."""
     O, B, inputs, dev = env
     d, M = (1 << 26) - 12345, 1
     gs = [inputs.gaussian(d, 0)]
@@ -362,7 +363,7 @@ def test_c4_full_size_sampled_blocks(env, blk):
     ("two_pass", (1 << 18) + 11, 7, 0),
     ("blocked_b65536", (1 << 18) + 11, 5, 16),
     ("n2p25", 25_557_032, 3, 0),
-    ("three_pass", (1 << 25) + 5, 2, 0),
+    ("n2p26", (1 << 25) + 5, 2, 0),
 ])
 def test_shared_worker_eps_popcount_server(env, name, d, M, blk):
     """One eps and one amplitude for all workers: the server sums the packed sign vectors per
@@ -431,8 +432,8 @@ def test_diagnostic_counters(env):
             pl.close()
         assert torch.equal(got[0], got[1])
         assert int(stats[:B.MAX_WORKERS + 1].sum()) == 0
-    # blocks of 2^16: with counters the encode takes the two-pass kernels, without them the one-pass kernel.  The two
-    # add up the block norms in different orders, so the amplitudes may differ in the last place: same step up to that.
+    # blocks of 2^16, short vectors with counters and without (longer plans take the two-pass kernels with counters and the
+    # one-pass kernel without: test_gpu_long_plans.py holds each against the oracle)
     gs2 = [torch.from_numpy(inputs.gaussian(150_000, m)).to(dev) for m in range(M)]
     got = []
     for attach in (False, True):
@@ -572,8 +573,8 @@ def test_resume_needs_only_x_and_the_round(env):
                                      ((1 << 24) + 3, 0, 2), ((1 << 25) + 3, 0, 2)])
 def test_negative_amplitudes_flip_the_decoded_vector(env, d, blk, M):
     """The decoder is linear in the amplitude, D = lambda D_eps H^T q (Def. 3.8): a caller-supplied negative
-    amplitude gives minus the vector of the positive one on every kernel path (single tile, pair, two-pass, the
-    matrix-core server pass of n = 2^25, three-pass), and in
+    amplitude gives minus the vector of the positive one on every kernel path (short vectors, two-pass, the matrix-core
+    server pass of n = 2^25, eleven stages; three passes are in test_gpu_three_pass.py), and in
     the server's mean a worker with a negated amplitude enters with the opposite sign."""
     import torch
     O, B, inputs, dev = env

@@ -35,7 +35,7 @@ def _signs(bits, n):
 
 
 def test_sampled_check_on_a_small_ragged_vector(oracle):
-    """The same sampled check where the whole-vector tests also run (three passes need n >= 2^26; this is two)."""
+    """The same sampled check where the whole-vector tests also run (three passes need n >= 2^28; this is two)."""
     _sampled_check(oracle, (1 << 22) + 77)
 
 

@@ -25,7 +25,7 @@ def env(oracle):
     ("blocks_4096_K8", 300_000, 2, 12, 8, {}),
     ("eight_planes_K255", 70_000, 2, 0, 255, {}),
     ("no_dither_K3", 40_000, 2, 0, 3, dict(dither=1)),
-    ("three_pass_K3", (1 << 25) + 5, 1, 0, 3, {}),
+    ("n2p26_K3", (1 << 25) + 5, 1, 0, 3, {}),
     ("shared_eps_two_pass_K2", 90_000, 3, 0, 2, dict(eps_mode=1)),
     ("shared_eps_single_pass_K6", 9_000, 3, 0, 6, dict(eps_mode=1)),
     ("all_shared_two_pass_K4", 90_000, 3, 0, 4, dict(eps_mode=2)),
@@ -103,7 +103,7 @@ def test_second_moment_falls_as_one_over_K(env):
     ("blocked_65536", (1 << 18) + 9, 2, 16, {}),
     ("shared_eps_two_pass", 90_000, 3, 0, dict(eps_mode=1)),
     ("shared_eps_single_pass", 9_000, 3, 0, dict(eps_mode=1)),
-    ("three_pass", (1 << 25) + 5, 1, 0, {}),
+    ("n2p26", (1 << 25) + 5, 1, 0, {}),
     ("n2p25", 25_557_032, 2, 0, {}),
     ("all_shared_single_pass", 9_000, 3, 0, dict(eps_mode=2)),
     ("all_shared_blocked_small", 7_000, 5, 6, dict(eps_mode=2)),

@@ -1,6 +1,7 @@
 """GPU parity tests: every call goes through the C ABI (libfo.so) and is compared with the CPU
 oracle element by element.  Sizes span several 2^15 tiles, ragged tails, every kernel path
-(single-pass, two-pass, three-pass; blocked and full-length)."""
+(short vectors, single-pass, two-pass; blocked and full-length; three passes are in
+test_gpu_three_pass.py, plans just past the short ones in test_gpu_long_plans.py)."""
 import numpy as np
 import pytest
 
@@ -50,8 +51,8 @@ CASES = [
     # (server tiles of the second block start 2^25 coordinates up), the second partly filled
     ("n2p25_single_worker", (1 << 24) + 1, 1, 0, "gaussian"),
     ("blocked_b2p25_two_blocks", (1 << 25) + 300_001, 2, 25, "gaussian"),
-    # three passes (n = 2^26) with several workers: the fused server over the int32 intermediates
-    ("three_pass_three_workers", (1 << 25) + 77, 3, 0, "heavy"),
+    # eleven strided stages (n = 2^26) with several workers: the fused server over the grouped int16 intermediates
+    ("n2p26_with_three_workers", (1 << 25) + 77, 3, 0, "heavy"),
 ]
 
 
