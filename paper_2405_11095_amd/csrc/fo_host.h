@@ -87,10 +87,10 @@ struct fo_plan {
     // scratch (device)
     char *scratch;
     size_t scratch_bytes;
-    float *buf_a;        // [M][ntot] 4-byte intermediates (transform lengths above 2^15)
+    float *buf_a;        // [M][ntot] 4-byte intermediates (transform lengths above 2^15; short vectors: above 2^12)
     float *buf_b;        // [ntot] mean gradient / server intermediate
     float *buf_c;        // [ntot] second intermediate for three-pass transforms, else NULL
-    float *partials;     // [M][ntiles]
+    float *partials;     // [M][ntiles] sums of squares (short vectors: [M][sm_tiles])
     uint64_t *bits_up;   // [M][W]
     float *scales_up;    // [M][nblocks]
     uint64_t *bits_down; // [planes][W]

@@ -40,7 +40,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
         // the mean itself was asked for (checking): one inverse transform of the summed sign vectors, below
     }
     if (pl->p.eps_mode != FO_EPS_INDEPENDENT && pl->npass == 2) {
-        // the same for three-pass transforms (blocks above 2^25): counts -> low stages (int32) -> middle stages -> the
+        // the same for three-pass transforms (blocks above 2^27): counts -> low stages (int32) -> middle stages -> the
         // shared pass on the top stages (amplitude, eps, eps^s, forward top stages) -> middle stages forward -> low pass
         ContigArgs c = contig_base(pl, r);
         c.src = bits_up; c.src_stride = pl->W; c.M = M;
@@ -138,7 +138,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
                              pl->buf_a, 0, st);
     }
     if (pl->npass == 2) {
-        // three-pass transforms (blocks above 2^25): low stages of all workers (bits -> int32), the middle stages in
+        // three-pass transforms (blocks above 2^27): low stages of all workers (bits -> int32), the middle stages in
         // place, one fused pass on the top stages that forms the mean and starts the re-encode, the middle stages
         // forward, the low pass that dithers and packs
         const dim3 gridM((unsigned)pl->ntiles, M), grid1((unsigned)pl->ntiles, 1), block(kThreads);

@@ -603,7 +603,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
 #pragma unroll
         for (int r = 0; r < kSV; ++r) acc[r] = 0.f;
         if constexpr (!IN16) {
-            // int32 intermediate (three-pass transforms, blocks above 2^25): the values outgrow fp32's 24 bits, so the
+            // int32 intermediate (three-pass transforms, blocks above 2^27): the values outgrow fp32's 24 bits, so the
             // remaining stages stay in integers, as in the decoder, and only the result is converted; no prefetch.
             for (uint32_t m = 0; m < a.M; ++m) {
                 int32_t v[kSV];
