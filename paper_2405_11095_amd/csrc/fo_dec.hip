@@ -15,6 +15,7 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
 {
     // Plain signs of at most half a tile of 2^15, transforms longer than the short vectors' tile: one launch here, two there
     // (n = 2^13: 8.4 and 10.4 us, n = 2^14: 8.3 and 10.0; n = 2^17 in such blocks: 10.7 and 10.0; K = 4, n = 2^13: 13.7 and 10.1).
+    // From 2^15 on two launches are even or better among other calls (2^15 in blocks of 2^14: 9.7 and 9.9) and better alone (23.7, 21.5).
     const bool half_tile = pl->logb > 12 && pl->ntot <= kTile / 2 && (party != FO_PARTY_SERVER || pl->p.K == 1);
     if (pl->small_dec && !half_tile)
         return small_decode(pl, bits, scales, round, party, out, store_mode, delta, tmp, st);

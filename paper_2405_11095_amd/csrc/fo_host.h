@@ -288,7 +288,12 @@ constexpr uint32_t kRowPad32 = 32, kRowPad16 = 64;
 // number of workers at most `total`.  Steps on the general kernels -> on these, us: b = 2^12: 2^22 x 4 workers 72 -> 52,
 // 2^22 x 8 97 -> 92, 2^21 x 32 166 -> 192, 2^24 x 4 170 -> 220.  b = 2^14: 2^20 x 2 48 -> 38, x 8 68 -> 60, x 32 133 -> 166.
 // b = 2^16: 2^21 x 8 99 -> 87, x 32 230 -> 274, 2^22 x 4 92 -> 97.  b = 2^18: 2^21 x 32 374 -> 270, 2^23 x 4 (b = 2^19) even.
-// The decoder of one pass (b <= 2^12) is the better one at every length: 252 -> 146 us for d = 2^27.
+// A call of one vector (fo_encode of one worker) follows the plan's number of workers too, also where one vector alone would
+// be faster the other way (d = 2^20 in blocks of 2^14: 22 us on the general kernels, 10 on these): fo_step and the calls made
+// by hand give the same messages to the bit, and the two sets of kernels add in different orders.
+// The decoder of one pass (b <= 2^12; exact, so either will do) is the better one from 2^10 coordinates to the longest: n = 2^12
+// 7.4 -> 6.9 us, 2^20 10.4 -> 6.9, 2^26 130 -> 67; K = 4 12.5 -> 6.9, 20.8 -> 7.0, 146 -> 95.  Below 2^10 a call among others takes
+// 6.6 to 7.0 us either way, one after which the GPU is waited for 20.8 -> 17.8.
 struct SmallRule {
     uint64_t longest, total;
 };

@@ -6,9 +6,11 @@
 // vector occupies eight times as many workgroups, each with an eighth of the work.  Everything is fp32: on the decode
 // side the values are half integers below 2^23, so every sum is exact (the plan's rule sees to the bound).
 // Measured, general kernels before and these after: one encode of 1000 coordinates 12.0 -> 7.3 us (kernel 4.9 us), a step of
-// n = 2^16 with four workers 71.7 -> 25.8 us, n = 2^20 with eight 123 -> 64 us.  What bounds a kernel here is latency: one
-// trip to memory, two exchanges and the generator's chain of ten rounds, 4 to 6 us each with few waves per SIMD; at
-// n = 2^20 the encode is at 4 TB/s in the high pass and near its instruction count in the low one.
+// n = 2^16 with four workers 71.7 -> 25.9 us, n = 2^20 with eight 123 -> 64 us.  What bounds a kernel here is latency: one
+// trip to memory, two exchanges and the generator's chain of ten rounds, 4 to 7 us each with few waves per SIMD.  At n = 2^20
+// with eight workers the encode's high pass takes 17 us for 101 MB: its rows of 64 bytes are half a line each, and the other
+// half's tile runs on another XCD, so the 34 MB of gradients are read twice.  The joined low pass takes 21 us with the vector
+// units 47 % busy, at 59 instructions per value (the long kernels' encode and decode: 31 and 9).
 //
 // Transforms of up to 2^12 points (whole or blocked) take one pass, longer ones (up to 2^20 points) two: up to eight
 // stages over rows 2^12 apart (k_small_high), twelve inside the contiguous tile (k_small_encode, k_small_decode).
@@ -22,7 +24,8 @@
 //   L0 (16-byte loads): regs = (b0,b1,b8,b9)    lanes = (b2..b7)            waves = (b10,b11)
 //   L1                : regs = (b2..b5)         lanes = (b0,b1,b8,b9,b6,b7) waves = (b10,b11)
 //   L2 (outputs)      : regs = (b6,b7,b10,b11)  lanes = (b0..b5)            waves = (b8,b9)
-// Coordinate c sits at LDS word c + 4 (c / 64): conflict free in all three layouts, so L1 goes back to where it was
+// Coordinate c sits at LDS word c + 4 (c / 64): few bank conflicts in any of the three layouts (64 cycles per wave and
+// transform by the counter, 5 to 9 % of a busy kernel's time), so L1 goes back to where it was
 // read and the tile needs one workgroup barrier.
 #pragma once
 #include "fo_contig.h"

@@ -12,10 +12,11 @@
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
 // v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
-// M = 4): encode 1.17 ms for 3.75 GB, server 0.90 ms for 1.6 GB, decode 0.48 ms for 1.1 GB.  Encode and decode are bound by
-// the 32-byte row segments of the caller's vectors (an encode on tiles of 2^16 coordinates, with segments of 64 bytes but
-// one workgroup per compute unit, took 1.32 ms; a decode of 32 values per thread, with half the loads in flight, 0.54), the
-// server by its vector instructions.
+// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.17 ms, 3.94 GB, 40 %; server 0.88 ms,
+// 1.70 GB, 52 %; decode 0.48 ms, 1.13 GB, 22 %.  Encode and decode are bound by the 32-byte row segments of the caller's
+// vectors (an encode on tiles of 2^16 coordinates, with segments of 64 bytes but one workgroup per compute unit, took 1.32 ms;
+// a decode of 32 values per thread, with half the loads in flight, 0.54).  In the server, one workgroup to a compute unit,
+// the stages of a worker and the loads of the next cover each other only in part.
 // Modes
 //   SM_ENC_FIRST : fp32 gradient (zero padded), eps flip on load, tile sum of squares -> fp32 intermediate
 //   SM_DEC_LAST  : integer intermediate -> lambda/sqrt(b) scaling, eps flip, store / SGD update (Def. 3.8)
