@@ -28,7 +28,7 @@
 // transform by the counter, 5 to 9 % of a busy kernel's time), so L1 goes back to where it was
 // read and the tile needs one workgroup barrier.
 #pragma once
-#include "fo_contig.h"
+#include "fo_strided.h"
 
 namespace fo {
 
@@ -764,8 +764,8 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
 // their squares as it does and keeps the one output of the high stages that falls into its row, then goes on like
 // k_small_encode<SMI_MID>.  Every sum has the operands and the order it has in those two kernels, so the message and the
 // amplitude are theirs to the bit.  It reads a block 2^HB times (from the caches but once) to save the trip through memory
-// and the second launch: n = 2^13 6.8 us, n = 2^16 9.9, the two kernels 9.6 and 9.7; 2^21 coordinates in blocks of 2^16, where
-// the repeated reads are 128 MiB of cache traffic, 20.5 and 13.3 (the kernels for long vectors 42).
+// and the second launch: n = 2^13 7.1 us, n = 2^16 9.2, the two kernels 10.1 and 10.2; 2^21 coordinates in blocks of 2^16, where
+// the repeated reads are 128 MiB of cache traffic, 18.5 and 13.4 (the kernels for long vectors 42).
 // The strided tiles are dealt to up to four groups of 256 threads, whose loads are in flight together; the first group does
 // the contiguous tile.  No diagnostic counters (their barrier would be the first group's alone).
 constexpr uint32_t small_block_groups(int hb) { return hb == 1 ? 2u : 4u; }
@@ -785,15 +785,13 @@ __global__ __launch_bounds__(kSmThreads * small_block_groups(HB)) void k_small_b
     const char *const src = reinterpret_cast<const char *>(a.src + origin);
     constexpr uint32_t b = kSmTile << HB;
     const uint32_t room = a.len_in >= origin + b ? b : a.len_in > origin ? (uint32_t)(a.len_in - origin) : 0u;
-    // coordinate, inside the block, of register r of strided tile j
-    auto at = [&](uint32_t j, int r) -> uint32_t {
-        const uint32_t u = t | (uint32_t)r << 8;
-        return ((u >> cb) << kSmLog2) + (j << cb) + (u & ((1u << cb) - 1u));
-    };
+    // coordinate, inside the block, of register r of strided tile j: the register's part (the same in every lane) + the lane's
+    auto part = [](int r) -> uint32_t { return ((uint32_t)r >> C << kSmLog2) + (((uint32_t)r & ((1u << C) - 1u)) << 8); };
     float v[16], next[16];
     auto load = [&](uint32_t j) {
+        const uint32_t mine = (j << cb) + t;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) next[r] = at(j, r) < room ? *reinterpret_cast<const float *>(src + at(j, r) * 4u) : 0.f;
+        for (int r = 0; r < 16; ++r) next[r] = mine + part(r) < room ? ld_uniform<float>(src + part(r) * 4u, mine * 4u) : 0.f;
     };
     load(grp);
     {
@@ -813,10 +811,7 @@ __global__ __launch_bounds__(kSmThreads * small_block_groups(HB)) void k_small_b
         const float s = wave_sum(small_sumsq(v), 6);
         if (lane == 0u) l.red[4u * j + wave] = s;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const uint32_t u = at(j, r);
-            v[r] = flip_if(v[r], (eps[u >> 5] >> (u & 31u)) & 1u);
-        }
+        for (int r = 0; r < 16; ++r) v[r] = flip_if(v[r], (eps[(part(r) >> 5) + (((j << cb) + t) >> 5)] >> (t & 31u)) & 1u);
         // of every butterfly the output that this row keeps: a + b or a - b (the product by one is exact)
         static_for<HB>([&](auto kc) {
             constexpr int k = decltype(kc)::value;
