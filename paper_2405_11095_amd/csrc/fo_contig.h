@@ -11,8 +11,6 @@
 //   L0 (global loads, 16 B per lane): regs = (b0,b1,b8,b9,b10,b11) lanes = (b2..b7)   waves = (b12,b13,b14)
 //   L1 (after the intra-wave exchange): regs = (b2..b7)            lanes = (b0,b1,b8,b9,b10,b11)
 //   L2 (after the cross-wave exchange): regs = (b6,b8,b12,b13,b14,b7) lanes = (b0..b5) waves = (b9,b10,b11)
-// (OUT_I16 reads the second exchange as lanes = (b1..b6), regs = (b0,b8,b12,b13,b14,b7) instead, so that a
-// thread owns pairs of neighbouring coordinates and stores them as one dword.)
 // The decode side (IN_BITS) carries every value divided by two: the stage on b0 is fused into the
 // unpacking as (c0 + c1 - 1, c0 - c1) for sign bits c0, c1, which is half the butterfly of the +-1
 // values, so after all fifteen stages the values fit int16 exactly; consumers fold the factor two
@@ -26,7 +24,7 @@
 namespace fo {
 
 enum { IN_GRAD = 0, IN_F32 = 1, IN_BITS = 2, IN_COUNT = 3 };
-enum { OUT_PACK = 0, OUT_I32 = 1, OUT_F32 = 2, OUT_I16 = 3 };
+enum { OUT_PACK = 0, OUT_I32 = 1, OUT_F32 = 2 };
 enum { STORE_SET = 0, STORE_ACC = 1, STORE_AXPY = 2 };
 
 struct PtrTab {
@@ -36,7 +34,7 @@ struct PtrTab {
 struct ContigArgs {
     const void *src;        // IN_F32: fp32 [slot][ntot]; IN_BITS: uint64 [slot][W]; IN_GRAD: unused if use_tab
     uint64_t src_stride;    // elements between party slots
-    void *dst;              // OUT_PACK: uint64 [slot][W]; OUT_I32 / OUT_I16: int [slot][ntot]; OUT_F32: fp32 [len_out]
+    void *dst;              // OUT_PACK: uint64 [slot][W]; OUT_I32: int32 [slot][ntot]; OUT_F32: fp32 [len_out]
     uint64_t dst_stride;
     float *scales;          // [slot][nblocks]
     uint64_t scales_stride;
@@ -58,6 +56,7 @@ struct ContigArgs {
     uint32_t src_pad;       // IN_F32: tile t of the intermediate starts at t * (2^15 + src_pad) (see StridedArgs)
     uint32_t dst_pad;       // k_declow: the same for its int16 output
     uint32_t group_log2;    // k_declow<true>: log2 of the rows of a block (see Grouped16)
+    uint32_t seg;           // low passes of longer transforms: stages of a strided pass inside regions, else 0 (see TileMap)
     uint32_t party0;        // party id of slot 0 (slot y is party0 + y); FO_PARTY_SERVER stays as is
     uint32_t eps_party0;    // same for the eps stream
     uint32_t k0, k1, round_lo;
@@ -69,6 +68,27 @@ struct ContigArgs {
     unsigned long long *stat_clipped; // OUT_PACK, optional: per slot, += #{i : |z_i| > lambda} (flattening failed there)
     unsigned long long *stat_near;    // OUT_PACK, optional: per slot, += #{i : |z_i + tau_i| < 1e-6 lambda} (first dither)
 };
+
+// Where the 2^15 coordinates of a low pass's tile lie.  seg = 0: one after the other, tile after tile.  seg = s > 0: the strided
+// pass of s stages works inside regions (see StridedGeom), takes the s bits from 8 on, and the tile is one row of 256
+// coordinates of each of the 128 regions of 2^(8+s) that make up a block.  Bits 0..7 of the tile-local coordinate are the
+// coordinate's own, bits 8..14 say which region.  Reading segments of 1 KiB costs the low pass nothing for s = 10 (0.55 ms
+// for the 17 vectors of n = 2^25, M = 16 either way) and a tenth for s = 12 (0.59 -> 0.65 ms, n = 2^27, M = 4).
+struct TileMap {
+    uint32_t seg, unit0; // unit0: coordinate / 256 of the tile's first 256
+    __device__ __forceinline__ TileMap(uint32_t seg_, uint32_t tile) : seg(seg_)
+    {
+        unit0 = seg ? ((tile >> seg) << (7u + seg)) + (tile & ((1u << seg) - 1u)) : tile << 7;
+    }
+    // coordinate / 256 of the tile-local coordinates 256 q .. 256 q + 255
+    __device__ __forceinline__ uint32_t unit(uint32_t q) const { return unit0 + (q << seg); }
+};
+// Tiles that are neighbours inside a region have block indices on the same XCD (blocks are dealt round-robin over 8): four of
+// them share the 128-byte lines of packed signs that they read or write.
+__device__ __forceinline__ uint32_t seg_tile(uint32_t seg, uint32_t i)
+{
+    return seg ? (i & ~31u) | ((i & 7u) << 2) | ((i >> 3) & 3u) : i;
+}
 
 // Chunk C of 16 of the 4096 coordinates at wave_src (the same address in every lane), into the registers of layout L0.
 template <int C>
@@ -116,7 +136,10 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const float *const red_hi = PAIR ? reinterpret_cast<const float *>(((tile & 1u) ? lds : lds_partner) + kXWords + kEpsWords + kLamWords) : nullptr;
 
     const uint32_t lane = t & 63u, wave = LOOP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6)) : t >> 6;
-    const uint64_t base = (uint64_t)tile << kTileLog2;
+    // the low passes of longer transforms work on segments (TileMap); everything else on contiguous tiles
+    constexpr bool SEG = IN == IN_F32 || OUT == OUT_I32;
+    const TileMap map(SEG ? a.seg : 0u, tile);
+    const uint64_t base = (uint64_t)map.unit0 << 8;
     const uint32_t S = SC ? (uint32_t)SC : a.S;
     const uint32_t party = (a.party0 == 0xFFFFFFFFu) ? a.party0 : a.party0 + slot;
     const uint32_t eps_party = (a.eps_party0 >= 0xFFFFFFFEu) ? a.eps_party0 : a.eps_party0 + slot;
@@ -136,7 +159,15 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
         // GUARDED = false: the caller vouches that the whole tile lies inside the input (no per-chunk checks)
         const uint64_t limit = (IN == IN_GRAD && GUARDED) ? a.len_in : ~0ull;
-        if constexpr (IN == IN_F32) src += (uint64_t)tile * a.src_pad;
+        if constexpr (IN == IN_F32) {
+            const uint32_t ws = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
+            src += (uint64_t)tile * a.src_pad;
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+                const float4 x = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(src + ((uint64_t)map.unit(ws * 16u + c) << 8)) + lane * 16u);
+                v[4 * c + 0] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
+            }
+        } else
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
             const uint64_t i = base + wave * 4096u + c * 256u + lane * 4u;
@@ -162,7 +193,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             const uint32_t *sm = src + 2 * (uint64_t)m * a.src_stride;
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
-                const uint64_t gh = 2 * ((uint64_t)tile * 512u + wave * 64u + c * 4u) + (lane >> 3); // 32-bit half word
+                const uint64_t gh = 8 * (uint64_t)map.unit(wave * 16u + c) + (lane >> 3); // 32-bit half word
                 const uint32_t h = (gh < 2 * a.W) ? sm[gh] : 0u;
                 cnt[c] += (((h >> ((lane & 7u) * 4u)) & 15u) * 0x00204081u) & 0x01010101u;
             }
@@ -175,7 +206,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
         const uint64_t *src = static_cast<const uint64_t *>(a.src) + slot * a.src_stride;
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-            const uint64_t gw = (uint64_t)tile * 512u + wave * 64u + c * 4u + (lane >> 4);
+            const uint64_t gw = 4 * (uint64_t)map.unit(wave * 16u + c) + (lane >> 4);
             // half of the b0 butterfly of the values 2 c - K: sum / 2 = c0 + c1 - K, difference / 2 = c0 - c1
             int32_t c0, c1, c2, c3, K = 1;
             if constexpr (MULTIK) {
@@ -390,21 +421,10 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
 #pragma unroll
             for (int r = 0; r < 32; ++r) xbuf[wofs + r * 4] = __builtin_bit_cast(uint32_t, v[sub * 32 + r]);
             __syncthreads();
-            if constexpr (OUT == OUT_I16) {
-                // lanes = (b1..b6): a lane reads the pair b0 = 0, 1 (8 bytes); register sub*32 + q = (b0,b8,b12,b13,b14 | b7)
-                const uint2 *rp2 = reinterpret_cast<const uint2 *>(xbuf) + (lane + wave * 132u);
 #pragma unroll
-                for (int q = 0; q < 32; q += 2) {
-                    const uint2 d = rp2[(((q >> 1) & 1) + (q >> 2) * 16) * 66];
-                    v[sub * 32 + q] = __builtin_bit_cast(T, d.x);
-                    v[sub * 32 + q + 1] = __builtin_bit_cast(T, d.y);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 32; ++q) // register sub*32 + q = (b6,b8,b12,b13,b14 | b7 = sub)
-                    v[sub * 32 + q] =
-                        __builtin_bit_cast(T, xbuf[rofs + (q & 1) * 64 + (((q >> 1) & 1) + (q >> 2) * 16) * 132]);
-            }
+            for (int q = 0; q < 32; ++q) // register sub*32 + q = (b6,b8,b12,b13,b14 | b7 = sub)
+                v[sub * 32 + q] =
+                    __builtin_bit_cast(T, xbuf[rofs + (q & 1) * 64 + (((q >> 1) & 1) + (q >> 2) * 16) * 132]);
         }
     }
 
@@ -413,6 +433,12 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     if (S > 13u) bfly<T, 3>(v);
     if (S > 14u) bfly<T, 4>(v);
 
+    // number of the generator block of the dithers of registers 2 g, 2 g + 1, 2 g + 32, 2 g + 33, without the lane part
+    auto dither_of = [&](int g) -> uint32_t { return map.unit(((uint32_t)g & 1u) | (wave << 1) | (((uint32_t)g >> 1) << 4)) << 6; };
+    // the packed word of lane j's register j: word (b6, b7) of 256 coordinates
+    auto word_of_lane = [&]() -> uint64_t {
+        return 4 * (uint64_t)map.unit(((lane >> 1) & 1u) | (wave << 1) | (((lane >> 2) & 7u) << 4)) + ((lane & 1u) | ((lane >> 5) << 1));
+    };
     // tile-local coordinate of register r in L2
     auto local_of = [&](int r) -> uint32_t {
         return lane | ((uint32_t)(r & 1) << 6) | ((uint32_t)(r >> 5) << 7) | ((uint32_t)((r >> 1) & 1) << 8) | (wave << 9) |
@@ -429,7 +455,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
 #pragma unroll
             for (int g = 0; g < 16; ++g) {
                 uint32_t w[4] = { 0u, 0u, 0u, 0u };
-                if constexpr (DITHER) philox((uint32_t)(((base + local_of(2 * g)) >> 8) << 6) | lane, key_dit, w);
+                if constexpr (DITHER) philox(dither_of(g) | lane, key_dit, w);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     const int r = 2 * g + (s & 1) + 32 * (s >> 1);
@@ -461,7 +487,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 uint32_t w[4] = { 0u, 0u, 0u, 0u };
                 if constexpr (DITHER) {
                     const RngKey key_k = { key_dit.k0, key_dit.k1, kDomainDither | (k << 8), key_dit.c2, key_dit.c3 };
-                    philox((uint32_t)(((base + lg) >> 8) << 6) | lane, key_k, w);
+                    philox(dither_of(g) | lane, key_k, w);
                 }
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
@@ -491,8 +517,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 }
             });
         });
-        const uint64_t gw = (uint64_t)tile * 512u +
-                            ((lane & 1u) | ((lane >> 5) << 1) | (((lane >> 1) & 1u) << 2) | (wave << 3) | (((lane >> 2) & 7u) << 6));
+        const uint64_t gw = word_of_lane();
         if (gw < a.W) {
             uint64_t *dst = static_cast<uint64_t *>(a.dst) + slot * a.dst_stride + gw;
 #pragma unroll
@@ -511,7 +536,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             constexpr int g = decltype(gc)::value;
             uint32_t w[4];
             const uint32_t lg = local_of(2 * g); // b6 = b7 = 0
-            philox((uint32_t)(((base + lg) >> 8) << 6) | lane, key_dit, w);
+            philox(dither_of(g) | lane, key_dit, w);
             float kq_g = 0.f;
             if constexpr (!SMALLB) kq_g = lam[lg >> S];
             uint64_t word[4];
@@ -537,8 +562,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             }
         });
         // lane j holds the word of register j
-        const uint64_t gw = (uint64_t)tile * 512u +
-                            ((lane & 1u) | ((lane >> 5) << 1) | (((lane >> 1) & 1u) << 2) | (wave << 3) | (((lane >> 2) & 7u) << 6));
+        const uint64_t gw = word_of_lane();
         if (gw < a.W)
             static_cast<uint64_t *>(a.dst)[slot * a.dst_stride + gw] = ((uint64_t)my_hi << 32) | my_lo;
         if constexpr (LOOP) {
@@ -554,7 +578,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             const uint32_t lg = local_of(2 * g); // b6 = b7 = 0
             float thr_g = 0.f;
             if constexpr (DITHER) {
-                philox((uint32_t)(((base + lg) >> 8) << 6) | lane, key_dit, w);
+                philox(dither_of(g) | lane, key_dit, w);
                 if constexpr (!SMALLB) thr_g = lam[lg >> S] * tscale;
             }
             uint64_t word[4];
@@ -580,24 +604,16 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             });
         });
         // lane j holds the word of register j
-        const uint64_t gw = (uint64_t)tile * 512u +
-                            ((lane & 1u) | ((lane >> 5) << 1) | (((lane >> 1) & 1u) << 2) | (wave << 3) | (((lane >> 2) & 7u) << 6));
+        const uint64_t gw = word_of_lane();
         if (gw < a.W)
             static_cast<uint64_t *>(a.dst)[slot * a.dst_stride + gw] = ((uint64_t)my_hi << 32) | my_lo;
-    } else if constexpr (OUT == OUT_I16) {
-        // pairs (b0 = 0, 1) packed into one dword; a wave writes 256 contiguous bytes per register pair
-        uint32_t *dst = reinterpret_cast<uint32_t *>(static_cast<int16_t *>(a.dst) + slot * a.dst_stride + base);
-#pragma unroll
-        for (int r = 0; r < kV; r += 2) {
-            // dword index = coordinate / 2 = lane | b7 << 6 | b8 << 7 | wave << 8 | (b12..b14) << 11
-            const uint32_t di = lane | ((uint32_t)(r >> 5) << 6) | ((uint32_t)((r >> 1) & 1) << 7) | (wave << 8) |
-                                ((uint32_t)((r >> 2) & 7) << 11);
-            dst[di] = __builtin_amdgcn_perm((uint32_t)v[r + 1], (uint32_t)v[r], 0x05040100u);
-        }
     } else if constexpr (OUT == OUT_I32) {
         int32_t *dst = static_cast<int32_t *>(a.dst) + slot * a.dst_stride + base;
 #pragma unroll
-        for (int r = 0; r < kV; ++r) dst[local_of(r)] = v[r];
+        for (int r = 0; r < kV; ++r) {
+            const uint32_t l = local_of(r);
+            dst[((uint64_t)(map.unit(l >> 8) - map.unit0) << 8) + (l & 255u)] = v[r];
+        }
     } else {
         float *dst = static_cast<float *>(a.dst);
 #pragma unroll
@@ -620,7 +636,8 @@ template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0,
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, a.tile0 + blockIdx.x, blockIdx.y, lds, threadIdx.x);
+    const uint32_t tile = (IN == IN_F32 || OUT == OUT_I32) ? seg_tile(a.seg, blockIdx.x) : a.tile0 + blockIdx.x;
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.

@@ -5,8 +5,9 @@ namespace fo_host {
 
 int launch_declow(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c)
 {
-    if (c.group_log2) return launch(pl, KID_DEC_LOW, k_declow<true>, grid, dim3(kThreads), st, c);
-    return launch(pl, KID_DEC_LOW, k_declow<false>, grid, dim3(kThreads), st, c);
+    if (c.seg) return launch(pl, KID_DEC_LOW, k_declow<true, true>, grid, dim3(kThreads), st, c);
+    if (c.group_log2) return launch(pl, KID_DEC_LOW, k_declow<true, false>, grid, dim3(kThreads), st, c);
+    return launch(pl, KID_DEC_LOW, k_declow<false, false>, grid, dim3(kThreads), st, c);
 }
 
 // Decode one party into out[d] with the given store mode.
@@ -45,6 +46,7 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
         return launch(pl, KID_DEC_PAIR, k_decode_pair, dim3((unsigned)(pl->ntiles / 2), 1), dim3(2 * kThreads), st, c);
     }
     c.dst = tmp; c.dst_stride = 0;
+    c.seg = decode_regions(pl);
     StridedArgs s = strided_base(pl, r, pl->npass - 1);
     s.dst = out; s.len_out = len_out; s.store_mode = store_mode; s.out_coef = out_coef; s.delta = delta;
     s.scales = scales; s.scales_stride = 0; s.eps_party0 = eps_party_of(pl, party);
@@ -53,7 +55,7 @@ int launch_decode(fo_plan *pl, const uint64_t *bits, const float *scales, uint64
         c.dst_pad = s.src_pad = tmp == pl->buf_a ? pl->pad16 : 0u;
         c.group_log2 = s.hb > 10 ? s.hb : 0u;
         if (c.group_log2) // the eps words go behind the intermediate, which takes half of tmp
-            FO_TRY(launch_eps_table(pl, st, s, s.eps_party0, 1, s.eps_party0,
+            FO_TRY(launch_eps_table<true>(pl, st, s, s.eps_party0, 1, s.eps_party0,
                                     reinterpret_cast<int16_t *>(tmp) + pl->ntot + pl->ntiles * pl->pad16));
         FO_TRY(launch_declow(pl, grid, st, c));
         s.src = tmp;

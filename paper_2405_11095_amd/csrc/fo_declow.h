@@ -45,9 +45,10 @@ constexpr uint32_t walsh_mask32(int j)
 // second call does by itself when xa and xb differ.
 // declow_front: up to the point where the tile sits in xb in layout LB and the barrier after it has been passed;
 // declow_back: the read into layout LC and the last three stages.  declow_tile is the two in a row.
-template <int SC>
+// SEG: the tile is made of segments (TileMap), `seg` says how.
+template <int SC, bool SEG = false>
 __device__ __forceinline__ void declow_front(const uint32_t *words, uint64_t W, uint32_t tile, uint32_t S_arg, uint32_t *xa,
-                                             uint32_t *xb, s16x2 (&v)[32], const uint32_t t)
+                                             uint32_t *xb, s16x2 (&v)[32], const uint32_t t, const uint32_t seg = 0u)
 {
     const uint32_t lane = t & 63u, wave = t >> 6;
     const uint32_t S = SC ? (uint32_t)SC : S_arg;
@@ -55,7 +56,9 @@ __device__ __forceinline__ void declow_front(const uint32_t *words, uint64_t W, 
     // ------------------------------------------------------------------ stages b0..b4 (layout LA)
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-        const uint64_t gh = (uint64_t)tile * 1024u + wave * 128u + x * 64u + lane; // 32-bit half word
+        // 32-bit half word: lane = (b5..b10), x = b11, wave = (b12..b14)
+        uint64_t gh = (uint64_t)tile * 1024u + wave * 128u + x * 64u + lane;
+        if constexpr (SEG) gh = 8 * (uint64_t)TileMap(seg, tile).unit((lane >> 3) | (uint32_t)x << 3 | wave << 4) + (lane & 7u);
         const uint32_t w = (gh < 2 * W) ? words[gh] : 0u;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -179,31 +182,34 @@ __device__ __forceinline__ constexpr uint32_t declow_reg_dword(int r)
 // (Kernels that are not templates are static: these headers are included by several translation units.)
 // Uses src, src_stride (64-bit words between slots), dst, dst_stride (int16 elements between slots) and W
 // of the argument block; the transform length is at least 2^15, so every tile is complete.
-template <bool GROUPED>
+// GROUPED: the output is laid out as Grouped16 says; SEG: see declow_front.
+template <bool GROUPED, bool SEG>
 __global__ __launch_bounds__(kThreads, 4) void k_declow(const ContigArgs a)
 {
     __shared__ uint32_t xbuf[kXWords];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    const uint32_t tile = blockIdx.x, slot = blockIdx.y;
+    const uint32_t tile = SEG ? seg_tile(a.seg, blockIdx.x) : blockIdx.x, slot = blockIdx.y;
     const uint32_t *src = reinterpret_cast<const uint32_t *>(static_cast<const uint64_t *>(a.src) + slot * a.src_stride);
     s16x2 v[32];
-    declow_tile<15>(src, a.W, tile, 15u, xbuf, xbuf, v);
+    declow_front<15, SEG>(src, a.W, tile, 15u, xbuf, xbuf, v, t, a.seg);
+    declow_back<15>(xbuf, 15u, v, t);
 
+    int16_t *const dst = static_cast<int16_t *>(a.dst) + slot * a.dst_stride;
     if constexpr (GROUPED) {
-        // a register's 256 bytes of a wave go to two groups of columns, a line each
-        const uint32_t row = tile & ((1u << a.group_log2) - 1u), half = Grouped16::group(a.group_log2) / 2u; // dwords of a group
-        uint32_t *const to = reinterpret_cast<uint32_t *>(static_cast<int16_t *>(a.dst) + slot * a.dst_stride +
-                                                          (uint64_t)(tile >> a.group_log2) * Grouped16::block(a.group_log2)) + row * 32u;
-        const uint32_t dl = (lane & 31u) + ((lane >> 5) | (wave << 3)) * half;
+        // a register's 256 bytes of a wave go to two groups of columns, a line each.  The tile is a row, of a block's 512 groups
+        // or of the four groups of each of its 128 regions: 256 coordinates are four groups one after the other either way.
+        const uint32_t row = tile & ((1u << a.group_log2) - 1u), group = Grouped16::group(a.group_log2) / 2u; // dwords
+        uint32_t *const to = reinterpret_cast<uint32_t *>(dst) + (uint64_t)(tile >> a.group_log2) * 512u * group + row * 32u;
+        const uint32_t dl = (lane & 31u) + ((lane >> 5) | (wave << 3)) * group; // wave = (b9,b10,b11), lane bit 5 = b6
 #pragma unroll
-        for (int r = 0; r < 32; ++r) to[dl + (declow_reg_dword(r) >> 5) * half] = __builtin_bit_cast(uint32_t, v[r]);
+        for (int r = 0; r < 32; ++r) to[dl + (declow_reg_dword(r) >> 5) * group] = __builtin_bit_cast(uint32_t, v[r]);
         return;
     }
     // store: a wave writes 256 contiguous bytes per register
-    uint32_t *dst = reinterpret_cast<uint32_t *>(static_cast<int16_t *>(a.dst) + slot * a.dst_stride + ((uint64_t)tile << kTileLog2) + (uint64_t)tile * a.dst_pad);
+    uint32_t *const to = reinterpret_cast<uint32_t *>(dst + (uint64_t)tile * (kTile + a.dst_pad));
     const uint32_t dt = lane | (wave << 8);
 #pragma unroll
-    for (int r = 0; r < 32; ++r) dst[dt + declow_reg_dword(r)] = __builtin_bit_cast(uint32_t, v[r]);
+    for (int r = 0; r < 32; ++r) to[dt + declow_reg_dword(r)] = __builtin_bit_cast(uint32_t, v[r]);
 }
 
 } // namespace fo

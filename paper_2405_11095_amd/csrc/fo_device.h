@@ -24,13 +24,12 @@ constexpr uint32_t kRedWords = 520;
 constexpr uint32_t kLdsWords = kXWords + kEpsWords + kLamWords + kRedWords;
 
 // Layout of the int16 intermediate of blocks of 2^26 and 2^27 between the low and the strided stages.  A strided tile is 16
-// or 8 columns wide there, pieces of 32 or 16 bytes of every row; row-major they would lie 64 KiB apart.  Columns go in
+// or 8 columns wide there, pieces of 32 or 16 bytes of every row; row-major they would lie far apart.  Columns go in
 // groups of 64, one 128-byte line a row, the rows of a group one after the other: tiles that share lines read one
 // contiguous region.  A group is followed by a line of padding, so that groups are not a power of two apart.
 // n = 2^27, four workers: server pass 1118 -> 1045 us, low pass 206 -> 216 us.
 struct Grouped16 {
     static __device__ __forceinline__ constexpr uint32_t group(uint32_t log_rows) { return (64u << log_rows) + 64u; } // elements
-    static __device__ __forceinline__ constexpr uint64_t block(uint32_t log_rows) { return (uint64_t)group(log_rows) * (kTile / 64u); }
 };
 
 constexpr uint32_t kDomainEps = 1u;
@@ -103,6 +102,27 @@ __device__ __forceinline__ float flip_if(float x, uint32_t bit) // bit in {0,1}
 __device__ __forceinline__ float flip_by_bit31(float x, uint32_t w)
 {
     return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(x), w, 0x80000000u, 0x78));
+}
+
+// Load through a base pointer that is the same in every lane (held in scalar registers: the load takes the
+// "scalar base + 32-bit lane offset" addressing form instead of 64-bit vector adds) plus a per-lane byte offset.
+template <typename T>
+__device__ __forceinline__ T ld_uniform(const void *uniform_base, uint32_t byte_off)
+{
+    typedef const __attribute__((address_space(1))) char *gptr;
+    const uint64_t v = reinterpret_cast<uint64_t>(uniform_base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    const gptr g = (gptr)(((uint64_t)hi << 32) | lo);
+    return *(const __attribute__((address_space(1))) T *)(g + byte_off);
+}
+template <typename T>
+__device__ __forceinline__ void st_uniform(void *uniform_base, uint32_t byte_off, T value)
+{
+    typedef __attribute__((address_space(1))) char *gptr;
+    const uint64_t v = reinterpret_cast<uint64_t>(uniform_base);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    const gptr g = (gptr)(((uint64_t)hi << 32) | lo);
+    *(__attribute__((address_space(1))) T *)(g + byte_off) = value;
 }
 
 template <typename T, int BIT, int V = kV>

@@ -165,7 +165,7 @@ inline bool args_ok(const StridedArgs &s, const PtrTab &tab, int kid)
     if (kid == KID_ENC_HIGH ? (s.use_tab ? !tab.p[0] : !s.src) : !s.src) return false;
     if (kid == KID_ENC_HIGH && !s.partials) return false;
     if ((kid == KID_DEC_HIGH || kid == KID_SERVER_HIGH || kid == KID_SERVER_MFMA) && !s.scales) return false;
-    return s.hb >= 1 && (s.hb <= 10 || (s.hb <= 12 && s.ls == (uint32_t)kTileLog2)) && s.ls >= (uint32_t)kTileLog2;
+    return s.hb >= 1 && (s.hb < kSegHigh || (s.hb <= 12 && s.ls == (uint32_t)kTileLog2)) && s.ls >= (uint32_t)kTileLog2;
 }
 template <typename... Args>
 inline bool args_ok(const Args &...) { return true; }
@@ -196,26 +196,26 @@ int launch(fo_plan *pl, int kid, Kern kernel, dim3 grid, dim3 block, hipStream_t
     } while (0)
 
 // The eps words of `nparty` parties (party0 and on, the last one `last`) for the strided pass s, into device memory `table`.
-inline int launch_eps_table(fo_plan *pl, hipStream_t st, StridedArgs &s, uint32_t party0, uint32_t nparty, uint32_t last, void *table)
+template <bool REGIONS>
+int launch_eps_table(fo_plan *pl, hipStream_t st, StridedArgs &s, uint32_t party0, uint32_t nparty, uint32_t last, void *table)
 {
     s.eps_table = static_cast<const uint32_t *>(table);
     s.eps_stride = pl->ntot / 32;
     const dim3 grid((unsigned)(pl->ntot >> 15), nparty), block(256);
     uint32_t *const to = static_cast<uint32_t *>(table);
     if (s.hb == 11)
-        return launch(pl, KID_EPS_TABLE, k_eps_table<11>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
-    return launch(pl, KID_EPS_TABLE, k_eps_table<12>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
+        return launch(pl, KID_EPS_TABLE, k_eps_table<11, REGIONS>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
+    return launch(pl, KID_EPS_TABLE, k_eps_table<12, REGIONS>, grid, block, st, s.k0, s.k1, s.round_lo, s.round_dev, party0, last, to, s.eps_stride);
 }
 
-// Strided kernels come in a generic form and ones compiled for ten, eleven and twelve stages next to the contiguous tile
-// (the middle pass of three-pass transforms never has more than eight).
+// Strided kernels come in a generic form and ones compiled for the ten, eleven and twelve stages of two-pass transforms
+// (the passes of three-pass transforms never have more than eight).
 template <int MODE, bool IN16 = false>
 int launch_strided(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const StridedArgs &s, const PtrTab &tab)
 {
     constexpr int LV = (MODE == SM_SERVER || MODE == SM_SHARED || MODE == SM_ENC_FIRST) ? 5 : 6;
-    if (s.hb == 10 && s.ls == (uint32_t)kTileLog2)
-        return launch(pl, kid, k_strided<MODE, 10, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
     if constexpr (MODE != SM_MID_F32 && MODE != SM_MID_I32 && (MODE != SM_SERVER || IN16)) {
+        if (s.hb == 10) return launch(pl, kid, k_strided<MODE, 10, IN16, LV>, grid, dim3(SL<LV>::T), st, s, tab);
         if (IN16 && s.hb > 10 && !s.eps_table) {
             std::snprintf(g_hip_err, sizeof(g_hip_err), "internal: no eps table for %s", kKernelNames[kid]);
             return FO_EHIP;
@@ -231,7 +231,7 @@ inline StridedArgs strided_base(const fo_plan *pl, const Rng &r, uint32_t pass)
     StridedArgs s;
     std::memset(&s, 0, sizeof(s));
     s.hb = pl->hb[pass];
-    s.ls = pass == 0 ? (uint32_t)kTileLog2 : (uint32_t)kTileLog2 + pl->hb[0];
+    s.ls = pass == 0 ? (uint32_t)kTileLog2 : (uint32_t)kTileLog2 + pl->hb[0]; // (passes inside regions have their own)
     s.logb = pl->logb;
     s.k0 = r.k0; s.k1 = r.k1; s.round_lo = r.round_lo; s.round_dev = r.round_dev;
     s.len_in = s.len_out = pl->ntot;
@@ -303,6 +303,10 @@ constexpr SmallRule kSmallRules[4] = {
     { (uint64_t)1 << 21, (uint64_t)1 << 24 }, // b = 2^16: a pair of tiles on one workgroup there
     { (uint64_t)1 << 21, (uint64_t)1 << 26 }, // b <= 2^20
 };
+
+// Stages of a strided pass inside regions (see kRegions): what the low pass of the encoder and of the decoder has to know.
+inline uint32_t encode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] >= kSegHigh ? pl->hb[0] : 0u; }
+inline uint32_t decode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] > kSegHigh ? pl->hb[0] : 0u; }
 
 // Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
 // Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a

@@ -188,7 +188,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
         s.M = M; s.out_coef = 2.f * mean_coef; s.eps_party0 = FO_PARTY_SERVER; // int16 input holds half values
         s.partials = l2s ? pl->partials : nullptr;
         if (s.hb > 10) // the eps words go behind the int16 intermediates, which take half of buf_a
-            FO_TRY(launch_eps_table(pl, st, s, 0, M + 1, FO_PARTY_SERVER,
+            FO_TRY(launch_eps_table<false>(pl, st, s, 0, M + 1, FO_PARTY_SERVER,
                                     reinterpret_cast<int16_t *>(pl->buf_a) + M * s.src_stride));
         if (s.hb == 10 && pl->server_mfma) // blocks of 2^25: the inverse stages on the matrix cores
             FO_TRY(launch(pl, KID_SERVER_MFMA, k_server_mfma, dim3((unsigned)pl->ntiles), dim3(1024), st, s));

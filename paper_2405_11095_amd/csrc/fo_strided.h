@@ -12,10 +12,11 @@
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
 // v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
-// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.17 ms, 3.94 GB, 40 %; server 0.88 ms,
-// 1.70 GB, 52 %; decode 0.48 ms, 1.13 GB, 22 %.  Encode and decode are bound by the 32-byte row segments of the caller's
-// vectors (an encode on tiles of 2^16 coordinates, with segments of 64 bytes but one workgroup per compute unit, took 1.32 ms;
-// a decode of 32 values per thread, with half the loads in flight, 0.54).  In the server, one workgroup to a compute unit,
+// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.07 ms, 3.94 GB, 40 %; server 0.88 ms,
+// 1.70 GB, 52 %; decode 0.37 ms, 1.13 GB, 22 %.  Encode and decode are bound by the 32-byte row segments of the caller's
+// vectors: reading and writing them without arithmetic takes the encode's time (an encode on tiles of 2^16 coordinates, with
+// segments of 64 bytes but one workgroup per compute unit, took a seventh longer; a decode of 32 values per thread, with
+// half the loads in flight, an eighth).  In the server, one workgroup to a compute unit,
 // the stages of a worker and the loads of the next cover each other only in part.
 // Modes
 //   SM_ENC_FIRST : fp32 gradient (zero padded), eps flip on load, tile sum of squares -> fp32 intermediate
@@ -57,6 +58,7 @@ struct StridedArgs {
     float delta;
     // Padding of an intermediate that the neighbouring contiguous pass reads or writes tile by tile: row R (2^ls elements)
     // starts at R * (2^ls + pad) elements, which keeps rows that are a power of two apart off the same memory channels.
+    // Regions have no padding.
     uint32_t dst_pad;      // ENC_FIRST, SERVER, SHARED: fp32 destination
     uint32_t src_pad;      // DEC_LAST, SERVER with the int16 source
 };
@@ -64,6 +66,18 @@ struct StridedArgs {
 // Element offset of tile coordinate u from the tile origin.  Each bit of u has a fixed weight
 // (column bits keep theirs, row bits move up to the row stride), so off(u1 | u2) = off(u1) + off(u2)
 // for disjoint bit sets: a thread adds its own part once and a wave-uniform part per register pair.
+// Regions: the encoder's pass of ten to twelve stages and the decoder's of eleven and twelve, which read or write the caller's
+// fp32 vectors, take the bits from kSegLog2 = 8 on (a region of 2^(8+hb) consecutive coordinates is 2^hb rows of 256) and leave
+// bits 0..7 and the seven above the region to the low pass (TileMap).  Tiles have 32, 16 or 8 columns, so the 8, 16 or 32 tiles
+// of a region read every 1 KiB row between them; with block indices that put them on one XCD the pieces of a row are asked for
+// together.  With rows 2^15 coordinates (128 KiB) apart every row is another page and all rows of a tile start on the same
+// memory channel.  Reading and writing 2^29 fp32 in the two patterns without arithmetic: ten stages 0.99 -> 0.78 ms, eleven
+// 1.33 -> 0.90, twelve 1.52 -> 1.08; nine 0.86 -> 0.84 and eight 0.78 both ways, hence the line at ten.  The kernels: encode of
+// n = 2^25, M = 16 0.80 -> 0.76 ms, n = 2^27, M = 4 1.17 -> 1.06; decode of 2^27 0.48 -> 0.37 ms.  Not where the caller's vector is
+// not touched (the server: int16 in padded rows, 0.33 -> 0.35 ms at n = 2^25, even at 2^27) and not in the decoder of ten stages (75 -> 82 us).
+constexpr uint32_t kSegLog2 = 8, kSegHigh = 10;
+template <int MODE, int HB>
+constexpr bool kRegions = (MODE == 0 && HB >= (int)kSegHigh) || (MODE == 1 && HB > (int)kSegHigh); // SM_ENC_FIRST, SM_DEC_LAST
 struct StridedGeom {
     uint64_t origin; // coordinate of u = 0
     uint32_t cb, ls;
@@ -95,30 +109,8 @@ struct SL {
     }
 };
 
-// Load through a base pointer that is the same in every lane (held in scalar registers: the load takes the
-// "scalar base + 32-bit lane offset" addressing form instead of 64-bit vector adds) plus a per-lane byte offset.
-template <typename T>
-__device__ __forceinline__ T ld_uniform(const void *uniform_base, uint32_t byte_off)
-{
-    typedef const __attribute__((address_space(1))) char *gptr;
-    const uint64_t v = reinterpret_cast<uint64_t>(uniform_base);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    const gptr g = (gptr)(((uint64_t)hi << 32) | lo);
-    return *(const __attribute__((address_space(1))) T *)(g + byte_off);
-}
-
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ void st_uniform(void *uniform_base, uint32_t byte_off, T value)
-{
-    typedef __attribute__((address_space(1))) char *gptr;
-    const uint64_t v = reinterpret_cast<uint64_t>(uniform_base);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    const gptr g = (gptr)(((uint64_t)hi << 32) | lo);
-    *(__attribute__((address_space(1))) T *)(g + byte_off) = value;
-}
-
 // Access through a wave-uniform base pointer plus a 32-bit per-lane byte offset.
 template <typename T>
 __device__ __forceinline__ T ld_at(const void *uniform_base, uint32_t byte_off)
@@ -162,9 +154,10 @@ __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, c
 // words each).  A generator block covers 128 columns of a row and a tile uses 16 or 8 of them, so a tile that draws its own
 // words spends 2048 or 4096 draws on 2^15 bits, a fifth of the server's vector instructions; here every block is drawn once
 // and its bits are dealt out through LDS.  n = 2^27, four workers: 19 us for the five parties, server pass 1045 -> 903 us.
-// 256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them) of row part (2^HB / 128) of block;
+// 256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them; one with REGIONS) of row part (2^HB / 128) of
+// block (region);
 // blockIdx.y = party party0 + y, the last one `last`.
-template <int HB>
+template <int HB, bool REGIONS>
 __global__ __launch_bounds__(256) void k_eps_table(uint32_t k0, uint32_t k1, uint32_t round_lo, const unsigned long long *round_dev,
                                                    uint32_t party0, uint32_t last, uint32_t *table, uint64_t stride)
 {
@@ -173,18 +166,19 @@ __global__ __launch_bounds__(256) void k_eps_table(uint32_t k0, uint32_t k1, uin
     static_assert(sizeof(Piece) * 8u == 1u << cb, "eleven or twelve stages");
     __shared__ uint32_t lds[1024];
     const uint32_t t = threadIdx.x, row = t & 127u, half = t >> 7;
-    const uint32_t cpart = blockIdx.x & 127u, rpart = (blockIdx.x >> 7) & ((1u << (HB - 7)) - 1u), blk = blockIdx.x >> HB;
+    constexpr uint32_t CP = REGIONS ? 0u : 7u; // log2 of the column parts
+    const uint32_t cpart = blockIdx.x & ((1u << CP) - 1u), rpart = (blockIdx.x >> CP) & ((1u << (HB - 7)) - 1u), blk = blockIdx.x >> (HB - 7 + CP);
     uint32_t rk1, rlo;
     resolve_round(k1, round_lo, round_dev, rk1, rlo);
     const RngKey key = { k0, rk1, kDomainEps, rlo, blockIdx.y + 1u == gridDim.y ? last : party0 + blockIdx.y };
-    const uint64_t i = ((uint64_t)blk << (kTileLog2 + HB)) + ((uint64_t)(rpart * 128u + row) << kTileLog2) + cpart * 256u + half * 128u;
+    const uint64_t i = ((uint64_t)blk << (8u + CP + HB)) + ((uint64_t)(rpart * 128u + row) << (8u + CP)) + cpart * 256u + half * 128u;
     uint32_t w[4];
     philox((uint32_t)(i >> 7), key, w);
     Piece *const pieces = reinterpret_cast<Piece *>(lds);
 #pragma unroll
     for (uint32_t k = 0; k < tiles / 2u; ++k) pieces[(half * (tiles / 2u) + k) * 128u + row] = (Piece)(w[(k << cb) >> 5] >> ((k << cb) & 31u));
     __syncthreads();
-    uint32_t *const out = table + blockIdx.y * stride + ((((uint64_t)blk << HB) + cpart * tiles) << 10) + rpart * per_tile;
+    uint32_t *const out = table + blockIdx.y * stride + ((((uint64_t)blk << CP) + cpart) * tiles << 10) + rpart * per_tile;
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
         const uint32_t d = t + 256u * k;
@@ -387,7 +381,7 @@ __device__ __forceinline__ void server_reencode(float (&acc)[1 << LV], const Str
 }
 
 // HB = 0: the number of stages (at most ten) and the row stride are read from the arguments.  HB = 10, 11, 12: compiled
-// for exactly HB stages with rows 2^15 apart (the pass next to the contiguous tile), which turns
+// for exactly HB stages of a two-pass transform with rows 2^15 or, inside regions, 2^8 apart (kRegions), which turns
 // every per-register offset into a constant and removes the stage-selection branches.
 // IN16: the integer input is the contiguous kernel's int16 intermediate.
 // LV: log2 of the values per thread (6: 512 threads; 5: 1024 threads, used where two tiles' worth of
@@ -414,18 +408,19 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
     resolve_round(a.k1, a.round_lo, a.round_dev, rk1, rlo);
     const uint32_t hb = HB ? (uint32_t)HB : a.hb;
     const uint32_t cb = (uint32_t)kTileLog2 - hb;
+    constexpr bool REGIONS = kRegions<MODE, HB>;
     // Row segments shorter than a 128-byte line (fp32 below 32 columns, int16 below 64): the 2^gl column groups that share
-    // lines are given block indices that land on the same XCD (blocks are dealt round-robin over 8 XCDs)
+    // lines, and all of a region, are given block indices that land on the same XCD (blocks are dealt round-robin over 8 XCDs)
     uint32_t tile = blockIdx.x;
     {
         const uint32_t line = IN16 ? 6u : 5u; // log2 of the columns in a line
-        const uint32_t gl = ((IN16 || HB > 10) && cb < line && cb <= 5u) ? line - cb : 0u;
+        const uint32_t gl = REGIONS ? kSegLog2 - cb : ((IN16 || HB > 10) && cb < line && cb <= 5u) ? line - cb : 0u;
         tile = (tile & ~((8u << gl) - 1u)) | ((tile & 7u) << gl) | ((tile >> 3) & ((1u << gl) - 1u));
     }
     const bool need_x = cb <= 6u + (uint32_t)L::NW; // some row bit lives in the wave index
     StridedGeom g;
     g.cb = cb;
-    g.ls = HB ? (uint32_t)kTileLog2 : a.ls;
+    g.ls = REGIONS ? kSegLog2 : HB ? (uint32_t)kTileLog2 : a.ls;
     {
         const uint32_t sh = g.ls - cb; // column groups per outer block = 2^sh
         const uint64_t outer = (uint64_t)tile >> sh, cg = tile & ((1u << sh) - 1u);
@@ -437,9 +432,9 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
     StridedGeom g16 = g;
     uint32_t pad16 = 0u;
     if constexpr (GROUPED) {
-        const uint32_t col = (uint32_t)g.origin & (kTile - 1u);
+        const uint32_t col = (uint32_t)g.origin & ((1u << g.ls) - 1u);
         g16.ls = 6u;
-        g16.origin = (g.origin >> (kTileLog2 + HB)) * Grouped16::block(HB) + (uint64_t)(col >> 6) * Grouped16::group(HB) + (col & 63u);
+        g16.origin = (((g.origin >> (g.ls + HB)) << (g.ls - 6u)) + (col >> 6)) * Grouped16::group(HB) + (col & 63u);
     } else if constexpr (IN16) {
         pad16 = a.src_pad;
         g16.origin = g.origin + (g.origin >> g.ls) * pad16;
@@ -563,7 +558,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
                 }
             }
         } else {
-            const uint32_t pad = (MODE == SM_ENC_FIRST) ? a.dst_pad : 0u;
+            const uint32_t pad = (MODE == SM_ENC_FIRST && !REGIONS) ? a.dst_pad : 0u;
             TV *dst = static_cast<TV *>(a.dst) + slot * a.dst_stride + g.origin + (g.origin >> g.ls) * pad;
             const uint32_t ot_pad = ot_out + (ut_out >> cb) * pad;
 #pragma unroll

@@ -16,7 +16,11 @@ pytestmark = pytest.mark.gpu
     (50_000_001, 2, 0, {}),                                        # eleven stages, independent workers, plain signs
     (1, 1, 26, {}),                                                # one coordinate: every tile but the first reads padding
     ((3 << 15) + 31, 1, 27, {}),                                   # ends inside a register's rows, on an odd coordinate
-], ids=["2p27", "2p27_shared_l2", "two_blocks_2p26_K3", "2p26", "one", "odd_end"])
+    ((1 << 26) + 300_001, 2, 26, {}),                              # two blocks, so regions of more than one, plain signs both ways
+    ((1 << 25) + 40_003, 1, 25, {"dither": 1}),                    # ten stages in two blocks, quantiser without dither
+    ((1 << 25) + 9, 1, 25, {"K": 5}),                              # and the K-fold one
+], ids=["2p27", "2p27_shared_l2", "two_blocks_2p26_K3", "2p26", "one", "odd_end", "two_blocks_2p26", "two_blocks_2p25_no_dither",
+        "two_blocks_2p25_K5"])
 def test_two_pass_transforms_of_narrow_rows(oracle, d, M, blk, kw):
     import torch
     from paper_2405_11095_amd import binding as B, inputs
