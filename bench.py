@@ -173,6 +173,7 @@ def main():
         # short vectors: fp32 intermediates on the decode side too; with independent eps a message goes straight on into
         # its decoder's low stages (one more intermediate written), and a mean in one tile never leaves the chip
         "k_small_high<ENC>": M * (4 * d + 4 * n),
+        "k_enc_wave": M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
         "k_small_encode<GRAD>": M * (4 * d + W8),
         "k_small_encode<MID>": (M + 1) * (8 * n + W8) if ind else M * (4 * n + W8) + (8 * n + W8 if args.eps_mode == "shared" else 0),
         "k_small_decode<LOW>": (M * W8 if args.eps_mode == "shared" else W8) + 4 * n,

@@ -2,6 +2,7 @@
 // instantiates the variants without the diagnostic counters, and by fo_enc_stats.hip, which instantiates those with).
 #pragma once
 #include "fo_host.h"
+#include "fo_enc_wave.h"
 
 namespace fo_host {
 
@@ -18,28 +19,47 @@ int launch_pack_s(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigA
     }
     if (dither && c.S == 15) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS>, grid, block, st, c, tab);
     if constexpr (IN == IN_GRAD && !STATS) {
-        // block lengths of the blocked workload, compiled for their stage count; tiles that lie inside the input
-        // whole go to a variant without the per-chunk end-of-input checks
-        if (dither && (c.S == 10 || c.S == 12 || c.S == 14)) {
+        // Blocks inside a wave's 4096 coordinates, each length compiled for itself; what lies inside the input whole goes to a
+        // variant without the per-chunk end-of-input checks.
+        if (dither && c.S <= 12) {
+            const uint64_t wgs = (pl->ntot + 4095u) >> 12, full = c.len_in >> 12;
+            const uint32_t nfull = (uint32_t)(full < wgs ? full : wgs), rest = (uint32_t)wgs - nfull;
+            ContigArgs cc = c;
+            auto both = [&](auto sc) -> int {
+                constexpr int SC = decltype(sc)::value;
+                if (nfull) FO_TRY(launch(pl, KID_ENC_WAVE, k_enc_wave<SC, false>, dim3(nfull, grid.y), dim3(kWvThreads), st, cc, tab));
+                cc.tile0 = nfull;
+                if (rest) FO_TRY(launch(pl, KID_ENC_WAVE, k_enc_wave<SC, true>, dim3(rest, grid.y), dim3(kWvThreads), st, cc, tab));
+                return FO_OK;
+            };
+            switch (c.S) {
+            case 6: return both(std::integral_constant<int, 6>{});
+            case 7: return both(std::integral_constant<int, 7>{});
+            case 8: return both(std::integral_constant<int, 8>{});
+            case 9: return both(std::integral_constant<int, 9>{});
+            case 10: return both(std::integral_constant<int, 10>{});
+            case 11: return both(std::integral_constant<int, 11>{});
+            default: return both(std::integral_constant<int, 12>{});
+            }
+        }
+        // blocks of 2^14, likewise compiled for their stage count and without checks where they can be
+        if (dither && c.S == 14) {
             const uint64_t full64 = c.len_in >> kTileLog2;
             const uint32_t nfull = (uint32_t)(full64 < grid.x ? full64 : grid.x);
             ContigArgs cc = c;
-            auto go = [&](auto sc, auto guarded, uint32_t tile0, uint32_t ntile) -> int {
+            auto go = [&](auto guarded, uint32_t tile0, uint32_t ntile) -> int {
                 cc.tile0 = tile0;
-                return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, decltype(sc)::value, false, false, decltype(guarded)::value>,
-                              dim3(ntile, grid.y), block, st, cc, tab);
+                return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 14, false, false, decltype(guarded)::value>, dim3(ntile, grid.y), block,
+                              st, cc, tab);
             };
-            auto both = [&](auto sc) -> int {
-                if (nfull) FO_TRY(go(sc, std::false_type{}, 0u, nfull));
-                if (nfull < grid.x) FO_TRY(go(sc, std::true_type{}, nfull, grid.x - nfull));
-                return FO_OK;
-            };
-            if (c.S == 10) return both(std::integral_constant<int, 10>{});
-            if (c.S == 12) return both(std::integral_constant<int, 12>{});
-            return both(std::integral_constant<int, 14>{});
+            if (nfull) FO_TRY(go(std::false_type{}, 0u, nfull));
+            if (nfull < grid.x) FO_TRY(go(std::true_type{}, nfull, grid.x - nfull));
+            return FO_OK;
         }
     }
-    if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, false, STATS>, grid, block, st, c, tab);
+    if constexpr (STATS) {
+        if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, false, STATS>, grid, block, st, c, tab);
+    }
     if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, false, STATS>, grid, block, st, c, tab);
     return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, false, STATS>, grid, block, st, c, tab);
 }

@@ -1,7 +1,7 @@
 // Host-side internals shared by the library's translation units (fo_api.hip, fo_enc.hip, fo_enc_stats.hip,
 // fo_dec.hip, fo_srv.hip): the plan, the kernel launcher with its optional event bracketing, argument-block
 // builders and the launch sequences' declarations.  The library is split into several translation units only
-// so that they compile side by side; every step of the codec runs in the kernels of fo_contig.h, fo_strided.h,
+// so that they compile side by side; every step of the codec runs in the kernels of fo_contig.h, fo_enc_wave.h, fo_strided.h,
 // fo_declow.h, fo_server_tile.h, fo_server_high.h and fo_shall.h.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -21,6 +21,7 @@
 // Kernel identities for the optional per-kernel timing (fo_profile_begin / fo_profile_end).
 enum KernelId {
     KID_ENC_SINGLE = 0, // k_contig<IN_GRAD,OUT_PACK>
+    KID_ENC_WAVE,       // k_enc_wave
     KID_ENC_HIGH,       // k_strided<ENC_FIRST>
     KID_ENC_MID,        // k_strided<MID_F32>
     KID_ENC_LOW,        // k_contig<IN_F32,OUT_PACK>
@@ -49,7 +50,7 @@ enum KernelId {
     KID_COUNT
 };
 inline const char *const kKernelNames[KID_COUNT] = {
-    "k_contig<IN_GRAD,OUT_PACK>", "k_strided<ENC_FIRST>", "k_strided<MID_F32>", "k_contig<IN_F32,OUT_PACK>",
+    "k_contig<IN_GRAD,OUT_PACK>", "k_enc_wave", "k_strided<ENC_FIRST>", "k_strided<MID_F32>", "k_contig<IN_F32,OUT_PACK>",
     "k_decode_tile",  "k_declow", "k_strided<MID_I32>", "k_strided<DEC_LAST>",
     "k_strided<SERVER>", "k_server_mfma", "k_contig<IN_COUNT>", "k_mean_mfma", "k_shall", "k_contig_pair", "k_contig_pair_walk", "k_decode_pair", "k_eps_table",
     "k_small_high<ENC>", "k_small_encode<GRAD>", "k_small_encode<MID>", "k_small_decode<LOW>", "k_small_high<SERVER>",
@@ -131,11 +132,12 @@ inline Rng rng_of(const fo_plan *pl, uint64_t round)
 inline bool args_ok(const ContigArgs &c, const PtrTab &tab, int kid)
 {
     const bool pair = kid == KID_ENC_PAIR || kid == KID_ENC_PAIR_WALK;
-    const bool grad_in = kid == KID_ENC_SINGLE || pair;
+    const bool grad_in = kid == KID_ENC_SINGLE || kid == KID_ENC_WAVE || pair;
     if (!c.dst) return false;
     if (pair && (c.logb != 16 || c.S != 15)) return false;
     if (grad_in ? (c.use_tab ? !tab.p[0] : !c.src) : !c.src) return false;
-    const bool needs_scales = kid == KID_ENC_SINGLE || pair || kid == KID_ENC_LOW || kid == KID_DEC_SINGLE;
+    if (kid == KID_ENC_WAVE && (c.S < 6 || c.S > 12 || c.S != c.logb)) return false;
+    const bool needs_scales = kid == KID_ENC_SINGLE || kid == KID_ENC_WAVE || pair || kid == KID_ENC_LOW || kid == KID_DEC_SINGLE;
     if (kid == KID_COUNT_LOW && (c.M < 1 || c.M > FO_MAX_WORKERS)) return false;
     return !needs_scales || c.scales != nullptr;
 }
