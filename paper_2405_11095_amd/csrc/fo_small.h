@@ -6,10 +6,9 @@
 // vector occupies eight times as many workgroups, each with an eighth of the work.  Everything is fp32: on the decode
 // side the values are half integers below 2^23, so every sum is exact (the plan's rule sees to the bound).
 // Measured, general kernels before and these after: one encode of 1000 coordinates 12.0 -> 7.3 us (kernel 4.9 us), a step of
-// n = 2^16 with four workers 71.7 -> 25.9 us, n = 2^20 with eight 123 -> 64 us.  What bounds a kernel here is latency: one
+// n = 2^16 with four workers 71.7 -> 24.9 us, n = 2^20 with eight 123 -> 55 us.  What bounds a kernel here is latency: one
 // trip to memory, two exchanges and the generator's chain of ten rounds, 4 to 7 us each with few waves per SIMD.  At n = 2^20
-// with eight workers the encode's high pass takes 17 us for 101 MB: its rows of 64 bytes are half a line each, and the other
-// half's tile runs on another XCD, so the 34 MB of gradients are read twice.  The joined low pass takes 21 us with the vector
+// with eight workers the joined low pass takes 21 us with the vector
 // units 47 % busy, at 59 instructions per value (the long kernels' encode and decode: 31 and 9).
 //
 // Transforms of up to 2^12 points (whole or blocked) take one pass, longer ones (up to 2^20 points) two: up to eight
@@ -598,16 +597,28 @@ __device__ __forceinline__ float small_sumsq(const float (&v)[16])
 // u = row << cb | column:
 //   A (loads): regs = (u8..u11), threads = (u0..u7)        B: regs = (u4..u7), threads = (u0..u3, u8..u11)
 // B is reached through LDS (word u + 16 (u / 256)) where some row bit lies below u8 (HB > 4).
-template <int MODE, int HB>
-__global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, const PtrTab tab)
+// G > 1 (SMH_SERVER): G groups of 256 threads share the workers, group g takes g, g + G, ..., and the first adds up the groups'
+// parts of the mean, in order, and goes on alone.  A vector of 2^20 has one tile for every compute unit, and one wave on a SIMD
+// waits out every exchange and every generator chain of the M workers one after the other.  The kernel, us, one group and four:
+// n = 2^16, M = 4 8.5 and 7.1; 2^17, M = 8 12.1 and 9.2; 2^18, M = 32 33 and 20; 2^20, M = 32 40 and 32.
+constexpr uint32_t small_server_groups(uint32_t nmsg) { return nmsg >= 4u ? 4u : nmsg >= 2u ? 2u : 1u; }
+template <int MODE, int HB, int G = 1>
+__global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a, const PtrTab tab)
 {
+    static_assert(G == 1 || MODE == SMH_SERVER, "groups share the workers");
     constexpr uint32_t cb = kSmLog2 - HB;
     constexpr bool X = HB > 4;
-    __shared__ float xb[kSmXWords];
-    __shared__ __attribute__((aligned(16))) uint32_t eps[2][kSmEpsWords];
+    __shared__ float xbs[G][kSmXWords];
+    __shared__ __attribute__((aligned(16))) uint32_t epss[G][2][kSmEpsWords];
     __shared__ float red[4];
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, slot = blockIdx.y;
-    const uint64_t tile = blockIdx.x;
+    const uint32_t t = G > 1 ? threadIdx.x & (kSmThreads - 1u) : threadIdx.x, lane = t & 63u, wave = t >> 6, slot = blockIdx.y;
+    const uint32_t grp = G > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kSmThreads)) : 0u;
+    float *const xb = xbs[grp];
+    uint32_t (&eps)[2][kSmEpsWords] = epss[grp];
+    // Rows of 64 bytes (HB = 8), half a line: the two tiles that share lines are given block indices that land on the same XCD
+    // (blocks are dealt round-robin over 8 XCDs).  n = 2^20, M = 8, us: encoder 18.8 -> 14.7, server 15.6 -> 13.0, decoder 10.0 -> 7.3.
+    const uint32_t i0 = blockIdx.x;
+    const uint64_t tile = HB == 8 ? (i0 & ~15u) | ((i0 & 7u) << 1) | ((i0 >> 3) & 1u) : i0;
     const uint64_t origin = ((tile >> HB) << (kSmLog2 + HB)) + ((tile & ((1u << HB) - 1u)) << cb);
     const uint64_t gb = origin >> a.logb;
     uint32_t rk1, rlo;
@@ -710,21 +721,26 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
         float acc[16], next[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        const uint32_t nmsg = a.count ? 1u : a.M;
+        const uint32_t nmsg = a.count ? 1u : a.M, rounds = (nmsg + G - 1u) / G;
         const float *src = a.src + origin;
+        auto request = [&](uint32_t m) {
+            if (G > 1 && m >= nmsg) return;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) next[r] = src[off(ua(r))];
-        for (uint32_t m = 0; m < nmsg; ++m) {
+            for (int r = 0; r < 16; ++r) next[r] = src[m * a.src_stride + off(ua(r))];
+        };
+        request(grp);
+        for (uint32_t k = 0; k < rounds; ++k) {
+            const uint32_t m = k * G + grp;
+            const bool mine = G == 1 || m < nmsg;
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[r] = next[r];
-            if (m + 1 < nmsg) {
-                src += a.src_stride;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) next[r] = src[off(ua(r))];
+            if (k + 1u < rounds) request(m + G);
+            uint32_t *const e = eps[k & 1u]; // last read one round ago, before that round's closing barrier
+            float c = 0.f;
+            if (mine) {
+                fill(e, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + m);
+                c = a.scales_up[(uint64_t)m * a.nblocks + gb] * a.in_coef;
             }
-            uint32_t *const e = eps[m & 1u]; // last read one worker ago, before that worker's closing barrier
-            fill(e, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + m);
-            const float c = a.scales_up[(uint64_t)m * a.nblocks + gb] * a.in_coef;
             stages_hi(v);
             if constexpr (X) {
                 a_to_b(v); // its barrier publishes the eps table
@@ -732,9 +748,26 @@ __global__ __launch_bounds__(kSmThreads) void k_small_high(const SmallArgs a, co
             } else {
                 __syncthreads();
             }
+            if (mine)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], flip(c, e, uo(r)), acc[r]);
+                for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], flip(c, e, uo(r)), acc[r]);
             __syncthreads(); // xb is free
+        }
+        if constexpr (G > 1) {
+            if (grp)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) xb[r * 256 + t] = acc[r];
+            __syncthreads();
+            if (grp) { // the barriers of the first group
+                if (a.partials) __syncthreads();
+                __syncthreads();
+                if constexpr (X) __syncthreads();
+                return;
+            }
+#pragma unroll
+            for (int k = 1; k < G; ++k)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] += xbs[k][r * 256 + t];
         }
         if (a.gbar)
 #pragma unroll

@@ -44,20 +44,26 @@ SmallArgs small_base(const fo_plan *pl, const Rng &r)
 }
 
 // Stages above the contiguous tile, b > 2^12.
-template <int MODE>
+template <int MODE, int G = 1>
 int launch_high(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a, const PtrTab &tab)
 {
+    if constexpr (MODE == SMH_SERVER && G == 1) {
+        // a tile for every compute unit at most (512 tiles, M = 8: 79 us a step with one group, 81 with four)
+        const uint32_t groups = pl->sm_tiles <= pl->num_cus ? small_server_groups(a.count ? 1u : a.M) : 1u;
+        if (groups == 4u) return launch_high<MODE, 4>(pl, nslots, st, a, tab);
+        if (groups == 2u) return launch_high<MODE, 2>(pl, nslots, st, a, tab);
+    }
     const int kid = MODE == SMH_ENC ? KID_SM_ENC_HIGH : MODE == SMH_SERVER ? KID_SM_SERVER_HIGH : KID_SM_DEC_HIGH;
-    const dim3 grid((unsigned)pl->sm_tiles, nslots), block(kSmThreads);
+    const dim3 grid((unsigned)pl->sm_tiles, nslots), block(kSmThreads * G);
     switch (pl->logb - kSmLog2) {
-    case 1: return launch(pl, kid, k_small_high<MODE, 1>, grid, block, st, a, tab);
-    case 2: return launch(pl, kid, k_small_high<MODE, 2>, grid, block, st, a, tab);
-    case 3: return launch(pl, kid, k_small_high<MODE, 3>, grid, block, st, a, tab);
-    case 4: return launch(pl, kid, k_small_high<MODE, 4>, grid, block, st, a, tab);
-    case 5: return launch(pl, kid, k_small_high<MODE, 5>, grid, block, st, a, tab);
-    case 6: return launch(pl, kid, k_small_high<MODE, 6>, grid, block, st, a, tab);
-    case 7: return launch(pl, kid, k_small_high<MODE, 7>, grid, block, st, a, tab);
-    case 8: return launch(pl, kid, k_small_high<MODE, 8>, grid, block, st, a, tab);
+    case 1: return launch(pl, kid, k_small_high<MODE, 1, G>, grid, block, st, a, tab);
+    case 2: return launch(pl, kid, k_small_high<MODE, 2, G>, grid, block, st, a, tab);
+    case 3: return launch(pl, kid, k_small_high<MODE, 3, G>, grid, block, st, a, tab);
+    case 4: return launch(pl, kid, k_small_high<MODE, 4, G>, grid, block, st, a, tab);
+    case 5: return launch(pl, kid, k_small_high<MODE, 5, G>, grid, block, st, a, tab);
+    case 6: return launch(pl, kid, k_small_high<MODE, 6, G>, grid, block, st, a, tab);
+    case 7: return launch(pl, kid, k_small_high<MODE, 7, G>, grid, block, st, a, tab);
+    case 8: return launch(pl, kid, k_small_high<MODE, 8, G>, grid, block, st, a, tab);
     }
     return FO_EINVAL;
 }
