@@ -52,7 +52,7 @@ struct ContigArgs {
     uint32_t K;             // MULTIK: averaging count of the quantiser (Def. 3.2) being applied / decoded
     uint32_t planes;        // MULTIK: bit planes of the message, ceil(log2(K + 1)); plane p starts at word p * W
     uint32_t scales_only;   // IN_GRAD: write the blocks' amplitudes and stop (no transform)
-    uint32_t tile0;         // first tile of this launch (a launch may cover a range of tiles)
+    uint32_t tile0;         // k_contig_pair: first tile of this launch (a launch may cover a range of tiles)
     uint32_t src_pad;       // IN_F32: tile t of the intermediate starts at t * (2^15 + src_pad) (see StridedArgs)
     uint32_t dst_pad;       // k_declow: the same for its int16 output
     uint32_t group_log2;    // k_declow<true>: log2 of the rows of a block (see Grouped16)
@@ -115,16 +115,15 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 // swap their values through LDS, the lower forms x_lo + x_hi and the upper x_lo - x_hi, and each runs the fifteen
 // remaining stages on its own tile as usual.  The 2^16-point transform then costs one pass over memory instead
 // of two.  The block's norm is the sum of the two groups' partial sums.
-// LOOP (PAIR, GUARDED = false): the caller walks over tiles.  v holds the tile's input on entry; `next` is where this wave's
+// LOOP (PAIR): the caller walks over tiles.  v holds the tile's input on entry; `next` is where this wave's
 // part of the next tile begins (any readable tile if there is none), and its loads go out while this tile is quantised, each
 // chunk into the four registers that the group of coordinates before it has left.
-template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool GUARDED = true,
-          bool LOOP = false>
+template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool LOOP = false>
 __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &tab, const uint32_t tile, const uint32_t slot,
                                             uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner = nullptr,
                                             float *const held = nullptr, const float *const next = nullptr)
 {
-    static_assert(!LOOP || (PAIR && !GUARDED && DITHER && !MULTIK && !STATS), "the walk over whole blocks of two tiles");
+    static_assert(!LOOP || (PAIR && DITHER && !MULTIK && !STATS), "the walk over whole blocks of two tiles");
     static_assert(!PAIR || (IN == IN_GRAD && OUT == OUT_PACK && SC == 15 && !SMALLB), "pair mode: gradient in, bits out");
     using T = typename std::conditional<(IN == IN_BITS || IN == IN_COUNT), int32_t, float>::type;
     uint32_t *const xbuf = lds;
@@ -157,8 +156,6 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     } else if constexpr (IN == IN_GRAD || IN == IN_F32) {
         const float *src = (IN == IN_GRAD && a.use_tab) ? tab.p[slot]
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
-        // GUARDED = false: the caller vouches that the whole tile lies inside the input (no per-chunk checks)
-        const uint64_t limit = (IN == IN_GRAD && GUARDED) ? a.len_in : ~0ull;
         if constexpr (IN == IN_F32) {
             const uint32_t ws = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
             src += (uint64_t)tile * a.src_pad;
@@ -167,19 +164,24 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 const float4 x = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(src + ((uint64_t)map.unit(ws * 16u + c) << 8)) + lane * 16u);
                 v[4 * c + 0] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
             }
-        } else
+        } else if (base + kTile <= a.len_in) {
+            // the tile lies inside the input whole: no per-chunk checks
+            src += base + wave * 4096u;
+            static_for<16>([&](auto cc) { load_chunk(v, src, lane, cc); });
+        } else {
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const uint64_t i = base + wave * 4096u + c * 256u + lane * 4u;
-            float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (i + 3 < limit) {
-                x = *reinterpret_cast<const float4 *>(src + i);
-            } else {
-                if (i < limit) x.x = src[i];
-                if (i + 1 < limit) x.y = src[i + 1];
-                if (i + 2 < limit) x.z = src[i + 2];
+            for (int c = 0; c < 16; ++c) {
+                const uint64_t i = base + wave * 4096u + c * 256u + lane * 4u;
+                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (i + 3 < a.len_in) {
+                    x = *reinterpret_cast<const float4 *>(src + i);
+                } else {
+                    if (i < a.len_in) x.x = src[i];
+                    if (i + 1 < a.len_in) x.y = src[i + 1];
+                    if (i + 2 < a.len_in) x.z = src[i + 2];
+                }
+                v[4 * c + 0] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
             }
-            v[4 * c + 0] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
         }
     } else if constexpr (IN == IN_COUNT) {
         // q_sum_i = sum_n q_{n,i} = 2 * popcount_i - M.  The four coordinates of a lane are a nibble of one
@@ -631,22 +633,21 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     }
 }
 
-template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false,
-          bool GUARDED = true>
+template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false>
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
-    const uint32_t tile = (IN == IN_F32 || OUT == OUT_I32) ? seg_tile(a.seg, blockIdx.x) : a.tile0 + blockIdx.x;
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, GUARDED>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
+    const uint32_t tile = (IN == IN_F32 || OUT == OUT_I32) ? seg_tile(a.seg, blockIdx.x) : blockIdx.x;
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.
-template <bool DITHER, bool MULTIK, bool GUARDED = true>
+template <bool DITHER, bool MULTIK>
 __global__ __launch_bounds__(2 * kThreads) void k_contig_pair(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[2 * kLdsWords];
     const uint32_t h = threadIdx.x >> 9;
-    contig_tile<IN_GRAD, OUT_PACK, DITHER, false, 15, MULTIK, false, true, GUARDED>(
+    contig_tile<IN_GRAD, OUT_PACK, DITHER, false, 15, MULTIK, false, true>(
         a, tab, a.tile0 + 2u * blockIdx.x + h, blockIdx.y, lds + h * kLdsWords, threadIdx.x & 511u, lds + (h ^ 1u) * kLdsWords);
 }
 
@@ -679,7 +680,7 @@ static __global__ __launch_bounds__(2 * kThreads) void k_contig_pair_walk(const 
         // addresses are formed anew for every block: kept from one to the next they cost more registers than there are
         asm volatile("" : "+v"(t));
         const uint32_t slot = unit / nblk, blk = unit - slot * nblk, after = unit + gridDim.x;
-        contig_tile<IN_GRAD, OUT_PACK, true, false, 15, false, false, true, false, true>(
+        contig_tile<IN_GRAD, OUT_PACK, true, false, 15, false, false, true, true>(
             a, tab, 2u * blk + h, slot, lds + h * kLdsWords, t, lds + (h ^ 1u) * kLdsWords, v, source(after < units ? after : unit));
         if (after >= units) break;
         unit = after;

@@ -17,22 +17,19 @@ int launch_pair(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c, con
         return launch(pl, KID_ENC_PAIR, k_contig_pair<false, true>, grid, block, st, c, tab);
     }
     if (dither) {
-        // blocks that lie inside the input whole: no per-chunk end-of-input checks
+        // A read and a sum, or a block for every compute unit at most: nothing to load behind (255 blocks: 52.7 us here,
+        // 54.7 with the walk, which reads every block once more).  The walk takes the blocks that lie inside the input whole;
+        // a block that does not is a launch of its own behind it, 25 us for its one workgroup, which pays from about five blocks
+        // for every compute unit on (a block takes 28 us here and 20 in the walk).
         const uint64_t full64 = c.len_in >> 16;
         const uint32_t nfull = (uint32_t)(full64 < grid.x ? full64 : grid.x);
+        if (c.scales_only || (uint64_t)nfull * grid.y <= (nfull == grid.x ? 1u : 5u) * (uint64_t)pl->num_cus)
+            return launch(pl, KID_ENC_PAIR, k_contig_pair<true, false>, grid, block, st, c, tab);
+        FO_TRY(launch(pl, KID_ENC_PAIR_WALK, k_contig_pair_walk, dim3(pl->num_cus), block, st, c, tab, nfull, (uint32_t)grid.y));
+        if (nfull == grid.x) return FO_OK;
         ContigArgs cc = c;
-        const uint32_t units = nfull * grid.y;
-        // a read and a sum, or a block for every compute unit at most: nothing to load behind (255 blocks: 52.7 us here,
-        // 54.7 with the walk, which reads every block once more)
-        if (units && (c.scales_only || units <= pl->num_cus))
-            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, false>, dim3(nfull, grid.y), block, st, cc, tab));
-        else if (units)
-            FO_TRY(launch(pl, KID_ENC_PAIR_WALK, k_contig_pair_walk, dim3(pl->num_cus), block, st, cc, tab, nfull, (uint32_t)grid.y));
-        if (nfull < grid.x) {
-            cc.tile0 = 2u * nfull;
-            FO_TRY(launch(pl, KID_ENC_PAIR, k_contig_pair<true, false, true>, dim3(grid.x - nfull, grid.y), block, st, cc, tab));
-        }
-        return FO_OK;
+        cc.tile0 = 2u * nfull;
+        return launch(pl, KID_ENC_PAIR, k_contig_pair<true, false>, dim3(grid.x - nfull, grid.y), block, st, cc, tab);
     }
     return launch(pl, KID_ENC_PAIR, k_contig_pair<false, false>, grid, block, st, c, tab);
 }

@@ -19,43 +19,23 @@ int launch_pack_s(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigA
     }
     if (dither && c.S == 15) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS>, grid, block, st, c, tab);
     if constexpr (IN == IN_GRAD && !STATS) {
-        // Blocks inside a wave's 4096 coordinates, each length compiled for itself; what lies inside the input whole goes to a
-        // variant without the per-chunk end-of-input checks.
+        // blocks inside a wave's 4096 coordinates, each length compiled for itself
         if (dither && c.S <= 12) {
-            const uint64_t wgs = (pl->ntot + 4095u) >> 12, full = c.len_in >> 12;
-            const uint32_t nfull = (uint32_t)(full < wgs ? full : wgs), rest = (uint32_t)wgs - nfull;
-            ContigArgs cc = c;
-            auto both = [&](auto sc) -> int {
-                constexpr int SC = decltype(sc)::value;
-                if (nfull) FO_TRY(launch(pl, KID_ENC_WAVE, k_enc_wave<SC, false>, dim3(nfull, grid.y), dim3(kWvThreads), st, cc, tab));
-                cc.tile0 = nfull;
-                if (rest) FO_TRY(launch(pl, KID_ENC_WAVE, k_enc_wave<SC, true>, dim3(rest, grid.y), dim3(kWvThreads), st, cc, tab));
-                return FO_OK;
+            auto go = [&](auto sc) -> int {
+                return launch(pl, KID_ENC_WAVE, k_enc_wave<decltype(sc)::value>, dim3((unsigned)((pl->ntot + 4095u) >> 12), grid.y), dim3(kWvThreads),
+                              st, c, tab);
             };
             switch (c.S) {
-            case 6: return both(std::integral_constant<int, 6>{});
-            case 7: return both(std::integral_constant<int, 7>{});
-            case 8: return both(std::integral_constant<int, 8>{});
-            case 9: return both(std::integral_constant<int, 9>{});
-            case 10: return both(std::integral_constant<int, 10>{});
-            case 11: return both(std::integral_constant<int, 11>{});
-            default: return both(std::integral_constant<int, 12>{});
+            case 6: return go(std::integral_constant<int, 6>{});
+            case 7: return go(std::integral_constant<int, 7>{});
+            case 8: return go(std::integral_constant<int, 8>{});
+            case 9: return go(std::integral_constant<int, 9>{});
+            case 10: return go(std::integral_constant<int, 10>{});
+            case 11: return go(std::integral_constant<int, 11>{});
+            default: return go(std::integral_constant<int, 12>{});
             }
         }
-        // blocks of 2^14, likewise compiled for their stage count and without checks where they can be
-        if (dither && c.S == 14) {
-            const uint64_t full64 = c.len_in >> kTileLog2;
-            const uint32_t nfull = (uint32_t)(full64 < grid.x ? full64 : grid.x);
-            ContigArgs cc = c;
-            auto go = [&](auto guarded, uint32_t tile0, uint32_t ntile) -> int {
-                cc.tile0 = tile0;
-                return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 14, false, false, decltype(guarded)::value>, dim3(ntile, grid.y), block,
-                              st, cc, tab);
-            };
-            if (nfull) FO_TRY(go(std::false_type{}, 0u, nfull));
-            if (nfull < grid.x) FO_TRY(go(std::true_type{}, nfull, grid.x - nfull));
-            return FO_OK;
-        }
+        if (dither && c.S == 14) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 14>, grid, block, st, c, tab);
     }
     if constexpr (STATS) {
         if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, false, STATS>, grid, block, st, c, tab);

@@ -46,13 +46,13 @@ __device__ __forceinline__ void wv_collect(uint32_t &acc, const uint32_t (&w)[4]
 // x with its sign flipped when bit 0 of n is set: 2^31 n added to the bits, one instruction
 __device__ __forceinline__ float flip_by_bit0(float x, uint32_t n) { return __uint_as_float(__float_as_uint(x) + (n << 31)); }
 
-// SC = log2 of the block.  GUARDED: the wave's coordinates may reach past the end of the input.
-template <int SC, bool GUARDED>
+// SC = log2 of the block.
+template <int SC>
 __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, const PtrTab tab)
 {
     static_assert(SC >= 6 && SC <= 12, "blocks inside a wave's 4096 coordinates");
     __shared__ __attribute__((aligned(16))) uint32_t lds[kWvLds];
-    const uint32_t lane = threadIdx.x, slot = blockIdx.y, part = a.tile0 + blockIdx.x; // which 4096 coordinates
+    const uint32_t lane = threadIdx.x, slot = blockIdx.y, part = blockIdx.x; // which 4096 coordinates
     const uint64_t base = (uint64_t)part << 12;
     uint32_t *const epsw = lds;
     float *const blk = reinterpret_cast<float *>(lds + 128);
@@ -65,9 +65,11 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
 
     float v[kV];
     const float *const src = (a.use_tab ? tab.p[slot] : static_cast<const float *>(a.src) + slot * a.src_stride);
-    static_for<16>([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        if constexpr (GUARDED) {
+    if (base + 4096u <= a.len_in) {
+        static_for<16>([&](auto cc) { load_chunk(v, src + base, lane, cc); });
+    } else {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
             const uint64_t i = base + c * 256u + lane * 4u;
             float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
             if (i + 3 < a.len_in) {
@@ -78,10 +80,8 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
                 if (i + 2 < a.len_in) x.z = src[i + 2];
             }
             v[4 * c + 0] = x.x; v[4 * c + 1] = x.y; v[4 * c + 2] = x.z; v[4 * c + 3] = x.w;
-        } else {
-            load_chunk(v, src + base, lane, cc);
         }
-    });
+    }
     // eps words, while the loads are on their way: lane q < 32 draws the generator block of coordinates 128 q ..
     if (lane < 32u) {
         uint32_t w[4];
