@@ -108,6 +108,7 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 // c_i = #{k < K : z_i + tau_{k,i} >= 0} in {0..K}, i.e. q_i = 2 c_i - K = (K / lambda) Q_{lambda,K}(z)_i, stored as
 // `planes` bit planes of W words each (plane p holds bit p of every c_i).  OUT_PACK draws K dithers per
 // coordinate and writes the planes; IN_BITS reads them.  K = 1 is the plain sign message and uses MULTIK = false.
+// SEG: the tile is made of segments, a.seg says how (TileMap).
 // The work of 512 threads (t = 0..511) on tile `tile` of party slot `slot`; lds has kLdsWords words.
 // PAIR (gradient in, transform length exactly 2^16): two such groups of 512 threads in one workgroup take the two
 // tiles of a block; lds_partner is the other group's LDS.  The stage on bit 15 pairs coordinate i of the lower
@@ -118,7 +119,8 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 // LOOP (PAIR): the caller walks over tiles.  v holds the tile's input on entry; `next` is where this wave's
 // part of the next tile begins (any readable tile if there is none), and its loads go out while this tile is quantised, each
 // chunk into the four registers that the group of coordinates before it has left.
-template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool LOOP = false>
+template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool LOOP = false,
+          bool SEG = false>
 __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &tab, const uint32_t tile, const uint32_t slot,
                                             uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner = nullptr,
                                             float *const held = nullptr, const float *const next = nullptr)
@@ -135,8 +137,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const float *const red_hi = PAIR ? reinterpret_cast<const float *>(((tile & 1u) ? lds : lds_partner) + kXWords + kEpsWords + kLamWords) : nullptr;
 
     const uint32_t lane = t & 63u, wave = LOOP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6)) : t >> 6;
-    // the low passes of longer transforms work on segments (TileMap); everything else on contiguous tiles
-    constexpr bool SEG = IN == IN_F32 || OUT == OUT_I32;
+    static_assert(!SEG || IN == IN_F32 || OUT == OUT_I32, "the low passes of longer transforms");
     const TileMap map(SEG ? a.seg : 0u, tile);
     const uint64_t base = (uint64_t)map.unit0 << 8;
     const uint32_t S = SC ? (uint32_t)SC : a.S;
@@ -633,12 +634,12 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     }
 }
 
-template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false>
+template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false, bool SEG = false>
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
-    const uint32_t tile = (IN == IN_F32 || OUT == OUT_I32) ? seg_tile(a.seg, blockIdx.x) : blockIdx.x;
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
+    const uint32_t tile = SEG ? seg_tile(a.seg, blockIdx.x) : blockIdx.x;
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, false, SEG>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.
