@@ -307,14 +307,15 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
         wave_sync();
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
-            const uint32_t nib = epsw[wave * 128u + c * 8u + (lane >> 3)] >> ((lane & 7u) * 4u);
+            uint32_t nib = epsw[wave * 128u + c * 8u + (lane >> 3)] >> ((lane & 7u) * 4u);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[4 * c + k] = flip_by_bit31(v[4 * c + k], nib << (31 - k));
+            for (int k = 0; k < 4; ++k, nib = flip_next(nib)) v[4 * c + k] = flip_by_bit0(v[4 * c + k], nib);
         }
         if constexpr (PAIR) {
             // stage b15 across the two groups, sixteen values per thread and round.  Two buffers in turn: the
             // barrier of round g+1 comes after every thread's reads of round g, so round g+2 may overwrite them.
-            const uint32_t upper = tile & 1u;
+            // upper: x becomes o - x = fma(x, -1, o), lower: x + o (the product by one is exact)
+            const float sgn = (tile & 1u) ? -1.f : 1.f;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 float4 *const mine = reinterpret_cast<float4 *>(xbuf + (g & 1) * 8192u) + t;
@@ -330,7 +331,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         float &x = v[16 * g + 4 * c + k];
-                        x = upper ? ov[k] - x : x + ov[k];
+                        x = fmaf(x, sgn, ov[k]);
                     }
                 }
             }

@@ -43,9 +43,6 @@ __device__ __forceinline__ void wv_collect(uint32_t &acc, const uint32_t (&w)[4]
         : "vcc");
 }
 
-// x with its sign flipped when bit 0 of n is set: 2^31 n added to the bits, one instruction
-__device__ __forceinline__ float flip_by_bit0(float x, uint32_t n) { return __uint_as_float(__float_as_uint(x) + (n << 31)); }
-
 // SC = log2 of the block.
 template <int SC>
 __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, const PtrTab tab)
@@ -137,8 +134,7 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             v[4 * c + k] = flip_by_bit0(v[4 * c + k], n);
-            n >>= 1;
-            asm("" : "+v"(n)); // the two shifts stay apart: the second is part of the addition
+            n = flip_next(n);
         }
     }
 

@@ -78,7 +78,7 @@ static __global__ __launch_bounds__(1024) void k_server_mfma(const StridedArgs a
             bh[mm][e] = (_Float16)(parity32(k & col) ? -0.25f : 0.25f);
         }
     // Constants the compiler must not fold: the -1 of stage B's remainder (so that value - piece stays a multiply-add
-    // and becomes v_fma_mixlo/hi_f16) and the two constants of stage A's second piece (one v_and_or_b32 from registers).
+    // and becomes v_fma_mix_f32) and the two constants of stage A's second piece (one v_and_or_b32 from registers).
     float minus_one = -1.f;
     asm volatile("" : "+s"(minus_one));
     uint32_t lo_mask = 0x007F007Fu, lo_magic = 0x48004800u;
@@ -179,12 +179,13 @@ static __global__ __launch_bounds__(1024) void k_server_mfma(const StridedArgs a
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 hp[i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(d[2 * i], d[2 * i + 1]));
-                // remainder = value - first piece, formed and converted in one mixed-precision fma per half
-                // (exact: at most ten significant bits)
+                // remainder = value - first piece (exact: at most ten significant bits)
                 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
                 const h2 top = __builtin_bit_cast(h2, hp[i]);
-                const h2 rest = { (_Float16)fmaf((float)top[0], minus_one, d[2 * i]), (_Float16)fmaf((float)top[1], minus_one, d[2 * i + 1]) };
-                lp[i] = __builtin_bit_cast(uint32_t, rest);
+                typedef float f2 __attribute__((ext_vector_type(2)));
+                f2 rest = { fmaf((float)top[0], minus_one, d[2 * i]), fmaf((float)top[1], minus_one, d[2 * i + 1]) };
+                asm("" : "+v"(rest)); // v_fma_mix_f32 and one conversion: the mixlo / mixhi forms issue at half the rate
+                lp[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, h2));
             }
         };
         auto bias_vec = [&]() -> mf_v16f {

@@ -314,8 +314,8 @@ __device__ __forceinline__ void exchange_wide(T (&v)[1 << LV], uint32_t *xbuf, u
 // flip a pair by bits 2k, 2k+1 of an eps word already shifted right by 2k
 __device__ __forceinline__ void flip_pair(float &x0, float &x1, uint32_t wshift)
 {
-    x0 = __uint_as_float(__float_as_uint(x0) ^ (wshift << 31));
-    x1 = __uint_as_float(__float_as_uint(x1) ^ ((wshift << 30) & 0x80000000u));
+    x0 = flip_by_bit0(x0, wshift);
+    x1 = flip_by_bit0(x1, flip_next(wshift));
 }
 
 // Tail of the server passes, on the mean of one tile held in layout LB (LA if no row bit lives in the wave index):
