@@ -46,9 +46,12 @@ struct ContigArgs {
     uint32_t logb;          // log2 of the transform length
     uint32_t use_tab;       // IN_GRAD: take the source pointer of slot y from the pointer table
     uint32_t compute_scale; // IN_GRAD: derive lambda from the measured block norm (else read scales[])
+    const float *partials;  // IN_F32, optional: [slot][tiles] sums of squares of the strided pass's tiles; lambda comes from their sum
+    uint64_t partials_stride;
+    const float *scales_up; // IN_GRAD, optional: [M][nblocks] the workers' amplitudes; lambda is coef_lambda times the largest
     uint32_t dither;        // 0 uniform, 1 none
     uint32_t store_mode;    // OUT_F32: STORE_*
-    uint32_t M;             // IN_COUNT: number of packed vectors to add up
+    uint32_t M;             // workers; IN_COUNT: number of packed vectors to add up
     uint32_t K;             // MULTIK: averaging count of the quantiser (Def. 3.2) being applied / decoded
     uint32_t planes;        // MULTIK: bit planes of the message, ceil(log2(K + 1)); plane p starts at word p * W
     uint32_t scales_only;   // IN_GRAD: write the blocks' amplitudes and stop (no transform)
@@ -61,7 +64,7 @@ struct ContigArgs {
     uint32_t eps_party0;    // same for the eps stream
     uint32_t k0, k1, round_lo;
     const unsigned long long *round_dev; // optional: round counter read at run time (see resolve_round)
-    float coef_lambda;      // alpha * sqrt(ln b / b)
+    float coef_lambda;      // alpha * sqrt(ln b / b); with scales_up: alpha_s sqrt(ln b)
     float sqrtb;            // threshold in the unnormalised domain = lambda * sqrt(b)
     float out_coef;         // OUT_F32: value = lambda * out_coef * (H^T q)_i  (1/sqrt(b), times 1/M on the server)
     float delta;            // STORE_AXPY: x -= delta * value
@@ -88,6 +91,20 @@ struct TileMap {
 __device__ __forceinline__ uint32_t seg_tile(uint32_t seg, uint32_t i)
 {
     return seg ? (i & ~31u) | ((i & 7u) << 2) | ((i >> 3) & 3u) : i;
+}
+
+// The server's amplitude of block gb by the theorem's rule: coef_lambda times the largest of the workers', NaN if any is NaN.
+__device__ __forceinline__ float server_scale_of(const ContigArgs &a, uint64_t gb)
+{
+    float m = 0.f;
+    bool nan = false;
+#pragma unroll 8
+    for (uint32_t n = 0; n < a.M; ++n) {
+        const float l = a.scales_up[(uint64_t)n * a.nblocks + gb];
+        nan |= (l != l);
+        m = fmaxf(m, l);
+    }
+    return nan ? __builtin_nanf("") : a.coef_lambda * m;
 }
 
 // Chunk C of 16 of the 4096 coordinates at wave_src (the same address in every lane), into the registers of layout L0.
@@ -158,6 +175,17 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
         const float *src = (IN == IN_GRAD && a.use_tab) ? tab.p[slot]
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
         if constexpr (IN == IN_F32) {
+            // The block's sum of squares, by every workgroup in the same order (at most 2^10 tiles of the strided pass): a
+            // launch of its own for it took 4 to 5 us.  Published by the barrier before the amplitude.
+            if (a.partials) {
+                const uint32_t hb = a.logb - (uint32_t)kTileLog2;
+                const float *const part = a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb);
+                double d = 0.0;
+                for (uint32_t k = t; k < (1u << hb); k += kThreads) d += (double)part[k];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) d += __shfl_xor(d, 1 << k, 64);
+                if (lane == 0u) reinterpret_cast<double *>(red)[wave] = d;
+            }
             const uint32_t ws = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
             src += (uint64_t)tile * a.src_pad;
 #pragma unroll
@@ -395,6 +423,13 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 }
                 l = a.coef_lambda * sqrtf(s);
                 if (gb < a.nblocks && !(PAIR && (tile & 1u))) a.scales[slot * a.scales_stride + gb] = l;
+            } else if (IN == IN_F32 && a.partials) {
+                double s = 0.0;
+                for (uint32_t k = 0; k < 8u; ++k) s += reinterpret_cast<const double *>(red)[k];
+                l = a.coef_lambda * (float)sqrt(s);
+                if ((tile & ((1u << (a.logb - (uint32_t)kTileLog2)) - 1u)) == 0u) a.scales[slot * a.scales_stride + gb] = l;
+            } else if (IN == IN_GRAD && !PAIR && a.scales_up) {
+                if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l = server_scale_of(a, gb);
             } else if (gb < a.nblocks) {
                 l = a.scales[slot * a.scales_stride + gb];
             }

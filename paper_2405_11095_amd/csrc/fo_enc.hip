@@ -39,11 +39,12 @@ int launch_pair(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c, con
 // Encode `nslots` vectors.  Sources: tab (pointer table, nslots entries) or src + slot * src_stride.
 // scales_given: scales[] already holds the amplitudes (forced / bound rule); else they come from the
 // measured norms.  common: the nslots parties are all the workers of a shared-eps round and must agree
-// on one amplitude per block (the largest) before any of them quantises; scales is then [M][nblocks].
+// on one amplitude per block (the largest) before any of them quantises; scales is then [M][nblocks].  scales_up (the
+// server's vector, single-pass geometry): the amplitude by the theorem's rule from the workers', into scales.
 int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride, uint64_t len_in,
                   uint32_t nslots, uint32_t party0, uint64_t round, bool scales_given, uint64_t *bits,
                   uint64_t bits_stride, float *scales, uint64_t scales_stride, float *tmp, uint64_t tmp_stride,
-                  hipStream_t st, bool common)
+                  hipStream_t st, bool common, const float *scales_up)
 {
     if (pl->small)
         return small_encode(pl, tab, src, src_stride, len_in, nslots, party0, round, scales_given, bits, bits_stride, scales,
@@ -65,6 +66,11 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
         c.src = src; c.src_stride = src_stride; c.use_tab = tab ? 1u : 0u;
         c.len_in = len_in;
         c.compute_scale = scales_given ? 0u : 1u;
+        if (scales_up) {
+            c.scales_up = scales_up;
+            c.M = pl->p.M;
+            c.coef_lambda = pl->coef_s;
+        }
         if (common && !scales_given) {
             // one extra read of the gradients: norms first, then the common amplitude, then the encode proper
             c.scales_only = 1u;
@@ -109,7 +115,12 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
         s2.src = pl->buf_c; s2.dst = tmp; s2.src_stride = 0; s2.dst_stride = tmp_stride;
         FO_TRY(launch_strided<SM_MID_F32>(pl, KID_ENC_MID, grid, st, s2, none));
     }
-    if (!scales_given) {
+    // Up to 2^10 tiles a block, every workgroup of the low pass adds up the partial sums itself (n = 2^25: 87.5 -> 83 us); beyond,
+    // and where the workers have to agree, a kernel does it.
+    if (!scales_given && !common && pl->npass == 1 && pl->hb[0] <= 10) {
+        c.partials = pl->partials;
+        c.partials_stride = pl->ntiles;
+    } else if (!scales_given) {
         FO_TRY(launch_finalize_scales(pl, st, nslots, coef, scales, scales_stride));
         if (common) FO_TRY(launch_common_scales(pl, st, scales, nslots));
     }

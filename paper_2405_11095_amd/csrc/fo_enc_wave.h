@@ -116,7 +116,9 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
             l = a.coef_lambda * sqrtf(blk[lane]);
             if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l;
         } else if (gb < a.nblocks) {
-            l = a.scales[slot * a.scales_stride + gb];
+            float *const at = a.scales + slot * a.scales_stride + gb;
+            if (a.scales_up) *at = l = server_scale_of(a, gb);
+            else l = *at;
         }
         blk[lane] = -128.f / (l * (a.sqrtb * 5.9604644775390625e-08f));
     }

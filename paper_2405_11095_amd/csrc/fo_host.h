@@ -350,7 +350,7 @@ inline int launch_pack(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const Co
 int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src_stride, uint64_t len_in,
                   uint32_t nslots, uint32_t party0, uint64_t round, bool scales_given, uint64_t *bits,
                   uint64_t bits_stride, float *scales, uint64_t scales_stride, float *tmp, uint64_t tmp_stride,
-                  hipStream_t st, bool common = false);
+                  hipStream_t st, bool common = false, const float *scales_up = nullptr);
 
 // fo_dec.hip
 int launch_declow(fo_plan *pl, dim3 grid, hipStream_t st, const ContigArgs &c);

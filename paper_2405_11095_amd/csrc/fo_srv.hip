@@ -15,7 +15,8 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
     std::memset(&none, 0, sizeof(none));
     // server amplitude: the theorem's rule from the workers' amplitudes now, or from the norm of the mean later
     const bool l2s = pl->p.server_scale == FO_SERVER_SCALE_L2;
-    if (!l2s)
+    const bool fold = pl->npass == 0 && pl->p.eps_mode != FO_EPS_SHARED_ALL; // the encoder of the mean does it
+    if (!l2s && !fold)
         FO_TRY(launch_server_scales(pl, st, scales_up, scales_down));
     auto finalize_server_scales = [&]() -> int { // after a fused strided pass that left the tile sums of squares of gbar
         return launch_finalize_scales(pl, st, 1, pl->coef_lambda_s, scales_down, 0);
@@ -86,7 +87,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
             FO_TRY(launch(pl, KID_COUNT_LOW, (k_contig<IN_COUNT, OUT_F32>), grid1, block, st, c, none));
             if (zero_transform) return FO_OK;
             return launch_encode(pl, nullptr, gbar, 0, pl->ntot, 1, FO_PARTY_SERVER, round, !l2s, bits_down, 0, scales_down,
-                                 0, nullptr, 0, st);
+                                 0, nullptr, 0, st, false, l2s ? nullptr : scales_up);
         }
         c.dst = pl->buf_a; c.dst_stride = 0;
         FO_TRY(launch(pl, KID_COUNT_LOW, (k_contig<IN_COUNT, OUT_I32, false, false, 15>), grid1, block, st, c, none));
@@ -120,7 +121,7 @@ int launch_server(fo_plan *pl, const uint64_t *bits_up, const float *scales_up, 
         const unsigned nwg = (unsigned)(pl->ntiles < pl->num_cus ? pl->ntiles : pl->num_cus);
         FO_TRY(launch(pl, KID_SERVER_TILE, k_mean_mfma, dim3(nwg), dim3(kMfThreads), st, sa, (uint32_t)pl->ntiles));
         return launch_encode(pl, nullptr, gbar, 0, pl->ntot, 1, FO_PARTY_SERVER, round, !l2s, bits_down, 0, scales_down, 0,
-                             nullptr, 0, st);
+                             nullptr, 0, st, false, l2s ? nullptr : scales_up);
     }
     if (pl->logb == 16) {
         // blocks of exactly two tiles: the mean in one pass over the packed signs, two workgroups per block, then the
