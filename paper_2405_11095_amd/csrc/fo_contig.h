@@ -176,7 +176,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                                                         : static_cast<const float *>(a.src) + slot * a.src_stride;
         if constexpr (IN == IN_F32) {
             // The block's sum of squares, by every workgroup in the same order (at most 2^10 tiles of the strided pass): a
-            // launch of its own for it took 4 to 5 us.  Published by the barrier before the amplitude.
+            // launch of its own for it took 1 to 2 us.  Published by the barrier before the amplitude.
             if (a.partials) {
                 const uint32_t hb = a.logb - (uint32_t)kTileLog2;
                 const float *const part = a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb);

@@ -115,7 +115,7 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
         s2.src = pl->buf_c; s2.dst = tmp; s2.src_stride = 0; s2.dst_stride = tmp_stride;
         FO_TRY(launch_strided<SM_MID_F32>(pl, KID_ENC_MID, grid, st, s2, none));
     }
-    // Up to 2^10 tiles a block, every workgroup of the low pass adds up the partial sums itself (n = 2^25: 87.5 -> 83 us); beyond,
+    // Up to 2^10 tiles a block, every workgroup of the low pass adds up the partial sums itself (n = 2^24: 51.4 -> 50.0 us; 2^22: 27.2 -> 25.4); beyond,
     // and where the workers have to agree, a kernel does it.
     if (!scales_given && !common && pl->npass == 1 && pl->hb[0] <= 10) {
         c.partials = pl->partials;
