@@ -504,15 +504,20 @@ __global__ __launch_bounds__(kSmThreads) void k_small_decode(const SmallArgs a)
 }
 
 // Server for b <= 2^12: the mean of the M messages in registers, its encode, and with UPDATE (fo_step) the decoder of
-// the server's own message with the update of x.
+// the server's own message with the update of x.  G > 1: G groups of 256 threads share the workers, as in k_small_high.
+// One wave on a SIMD waits out every exchange and generator chain of the workers one after the other; the step, us, one group
+// and four: d = 10^6 in blocks of 2^12, M = 8 36.4 and 30.6; 2 * 10^5, M = 32 76.7 and 48.4; 5 * 10^4, M = 4 20.4 and 18.2.
 // The eps words come eight workers at a time, so that every thread has a generator block to draw (d = 3 * 10^6 in blocks of
 // 2^9, M = 5, K = 4: 53.5 us a step with one worker's at a time, 52.9 like this).
-template <bool DITHER, bool MULTIK, bool UPDATE>
-__global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
+template <bool DITHER, bool MULTIK, bool UPDATE, int G>
+__global__ __launch_bounds__(kSmThreads * G) void k_small_server(const SmallArgs a)
 {
-    __shared__ SmallLds l;
-    __shared__ __attribute__((aligned(16))) uint32_t eps8[8 * kSmEpsWords];
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, S = a.S;
+    __shared__ SmallLds ls[G];
+    __shared__ __attribute__((aligned(16))) uint32_t eps8s[G][8 * kSmEpsWords];
+    const uint32_t t = G > 1 ? threadIdx.x & (kSmThreads - 1u) : threadIdx.x, lane = t & 63u, wave = t >> 6, S = a.S;
+    const uint32_t grp = G > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kSmThreads)) : 0u;
+    SmallLds &l = ls[grp];
+    uint32_t *const eps8 = eps8s[grp];
     const uint64_t tile = blockIdx.x, base = tile << kSmLog2;
     const uint32_t nblk = kSmTile >> S;
     uint32_t rk1, rlo;
@@ -533,14 +538,16 @@ __global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
             for (int q = 0; q < 4; ++q) wnext[q] = word(m, wave * 16u + (lane >> 4) + 4u * q);
         lnext = lam_mine ? a.scales_up[(uint64_t)m * a.nblocks + gb_mine] : 0.f;
     };
-    request(0u);
-    for (uint32_t m = 0; m < nmsg; ++m) {
+    if (grp < nmsg) request(grp);
+    const uint32_t rounds = (nmsg + G - 1u) / G;
+    for (uint32_t k = 0; k < rounds; ++k) {
+        const uint32_t m = k * G + grp;
         if (a.count) small_from_bits(v, a.M, true, 0.5f * (float)a.M, lane, wave, word);
         else small_from_signs(v, wnext, lane);
         const float lam = lnext * a.in_coef;
-        if (m + 1u < nmsg) request(m + 1u);
-        if ((m & 7u) == 0u) { // the eps words of eight workers, a generator block for every thread; the last use was before the barrier
-            const uint32_t w8 = m + (t >> 5);
+        if (m + G < nmsg) request(m + G);
+        if ((k & 7u) == 0u) { // the eps words of eight workers, a generator block for every thread; the last use was before the barrier
+            const uint32_t w8 = m + (t >> 5) * G;
             if (w8 < nmsg) {
                 const RngKey key = { a.k0, rk1, kDomainEps, rlo, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + w8 };
                 uint32_t w[4];
@@ -551,8 +558,24 @@ __global__ __launch_bounds__(kSmThreads) void k_small_server(const SmallArgs a)
         if (t < nblk) l.lam[t] = lam;
         small_transform(v, S, l.x, lane, wave);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], small_signed_lam(l, eps8 + (m & 7u) * kSmEpsWords, r, S, lane, wave), acc[r]);
+        for (int r = 0; r < 16; ++r)
+            if (G == 1 || m < nmsg) acc[r] = fmaf(v[r], small_signed_lam(l, eps8 + (k & 7u) * kSmEpsWords, r, S, lane, wave), acc[r]);
         __syncthreads(); // the tables and l.x are free
+    }
+    if constexpr (G > 1) {
+        if (grp)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) l.x[r * 256 + t] = acc[r];
+        __syncthreads();
+        if (grp) { // the barriers of the first group: here, in small_encode_tile and small_transform, in small_pack, with the update
+            const uint32_t left = 3u + (a.stat_clipped ? 1u : 0u) + (UPDATE ? 2u : 0u);
+            for (uint32_t k = 0; k < left; ++k) __syncthreads();
+            return;
+        }
+#pragma unroll
+        for (int g = 1; g < G; ++g)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] += ls[g].x[r * 256 + t];
     }
     {
         float *const p = l.x + lane + wave * 272u;

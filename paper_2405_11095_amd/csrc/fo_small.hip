@@ -43,13 +43,19 @@ SmallArgs small_base(const fo_plan *pl, const Rng &r)
     return a;
 }
 
+// Groups of threads that share the workers in the server's kernels: a tile for every compute unit at most (512 tiles, M = 8,
+// b = 2^16: 79 us a step with one group, 81 with four; blocks of 2^9, d = 2 * 10^6, M = 4 34.3 and 41.4, in two groups 34.5).
+uint32_t server_groups(const fo_plan *pl, const SmallArgs &a)
+{
+    return pl->sm_tiles <= pl->num_cus ? small_server_groups(a.count ? 1u : a.M) : 1u;
+}
+
 // Stages above the contiguous tile, b > 2^12.
 template <int MODE, int G = 1>
 int launch_high(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a, const PtrTab &tab)
 {
     if constexpr (MODE == SMH_SERVER && G == 1) {
-        // a tile for every compute unit at most (512 tiles, M = 8: 79 us a step with one group, 81 with four)
-        const uint32_t groups = pl->sm_tiles <= pl->num_cus ? small_server_groups(a.count ? 1u : a.M) : 1u;
+        const uint32_t groups = server_groups(pl, a);
         if (groups == 4u) return launch_high<MODE, 4>(pl, nslots, st, a, tab);
         if (groups == 2u) return launch_high<MODE, 2>(pl, nslots, st, a, tab);
     }
@@ -82,17 +88,21 @@ int launch_low(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a,
     return launch(pl, kid, k_small_encode<IN, false, false, DEC>, grid, block, st, a, tab);
 }
 
-template <bool UPDATE>
+template <bool UPDATE, int G = 1>
 int launch_mean(fo_plan *pl, hipStream_t st, const SmallArgs &a)
 {
-    const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads);
+    if constexpr (G == 1) {
+        // from four workers (three in two groups: 21.0 -> 21.4 us a step of d = 10^6; two: the same time)
+        if (server_groups(pl, a) == 4u) return launch_mean<UPDATE, 4>(pl, st, a);
+    }
+    const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads * G);
     const bool dither = a.dither == FO_DITHER_UNIFORM;
     if (a.K > 1) {
-        if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, true, UPDATE>, grid, block, st, a);
-        return launch(pl, KID_SM_SERVER, k_small_server<false, true, UPDATE>, grid, block, st, a);
+        if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, true, UPDATE, G>, grid, block, st, a);
+        return launch(pl, KID_SM_SERVER, k_small_server<false, true, UPDATE, G>, grid, block, st, a);
     }
-    if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, false, UPDATE>, grid, block, st, a);
-    return launch(pl, KID_SM_SERVER, k_small_server<false, false, UPDATE>, grid, block, st, a);
+    if (dither) return launch(pl, KID_SM_SERVER, k_small_server<true, false, UPDATE, G>, grid, block, st, a);
+    return launch(pl, KID_SM_SERVER, k_small_server<false, false, UPDATE, G>, grid, block, st, a);
 }
 
 // Both passes of the encoder in one launch, 2^12 < b <= 2^16.

@@ -35,6 +35,11 @@ CASES = [
     (150_001, 7, 0, {"K": 3}),
     (1 << 20, 4, 0, {"server_scale": 1}),                        # a tile for every compute unit; one tile more
     ((1 << 20) + 5, 3, 13, {}),
+    (20_011, 4, 12, {}),                                         # blocks of a tile and less: workers dealt to four groups
+    (30_007, 7, 10, {"K": 3, "server_scale": 1}),
+    (9_001, 35, 8, {"dither": 1}),                               # a second draw of eps words, for three workers
+    (1 << 20, 5, 12, {}),                                        # a tile for every compute unit; one tile more
+    ((1 << 20) + 5, 5, 9, {}),
 ]
 
 
