@@ -182,8 +182,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 const float *const part = a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb);
                 double d = 0.0;
                 for (uint32_t k = t; k < (1u << hb); k += kThreads) d += (double)part[k];
-#pragma unroll
-                for (int k = 0; k < 6; ++k) d += __shfl_xor(d, 1 << k, 64);
+                d = wave_sum(d, 6);
                 if (lane == 0u) reinterpret_cast<double *>(red)[wave] = d;
             }
             const uint32_t ws = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);

@@ -149,14 +149,6 @@ __device__ __forceinline__ void bfly(T (&v)[V])
         }
 }
 
-__device__ __forceinline__ float wave_sum(float s, int steps) // butterfly sum over 2^steps lanes
-{
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-        if (k < steps) s += __shfl_xor(s, 1 << k, 64);
-    return s;
-}
-
 // Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{})
 template <int N, int I = 0, typename F>
 __device__ __forceinline__ void static_for(F &&f)
@@ -165,6 +157,52 @@ __device__ __forceinline__ void static_for(F &&f)
         f(std::integral_constant<int, I>{});
         static_for<N, I + 1>(f);
     }
+}
+
+// Step K of a butterfly sum: s plus the s of the lane whose number differs in bit K.  Lanes that differ below bit K only hold the
+// same sum, so mirroring 8 or 16 lanes reaches the partner as well; bits 4 and 5 are the row swaps.  In registers: a shuffle goes
+// through LDS, 100 cycles and more of a chain of six (step of 3 M coordinates in blocks of 2^9, M = 5, K = 4: 53.2 -> 48.9 us; of
+// 10^6 in blocks of 2^8, M = 8: 32.3 -> 29.7; d = 1000, M = 2: 14.5 -> 14.2).
+template <int K, typename T>
+__device__ __forceinline__ T wave_sum_step(T s)
+{
+    constexpr int words = sizeof(T) / 4;
+    struct Words { uint32_t w[words]; };
+    const Words x = __builtin_bit_cast(Words, s);
+    Words a = x, b;
+#pragma unroll
+    for (int i = 0; i < words; ++i) {
+        if constexpr (K < 4) {
+            constexpr int ctrl = K == 0 ? 0xB1 : K == 1 ? 0x4E : K == 2 ? 0x141 : 0x140; // quad_perm 1,0,3,2 | 2,3,0,1, row_half_mirror, row_mirror
+            b.w[i] = (uint32_t)__builtin_amdgcn_mov_dpp((int)x.w[i], ctrl, 0xf, 0xf, true);
+        } else if constexpr (K == 4) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x.w[i], x.w[i], false, false);
+            a.w[i] = r[0]; b.w[i] = r[1];
+        } else {
+            const auto r = __builtin_amdgcn_permlane32_swap(x.w[i], x.w[i], false, false);
+            a.w[i] = r[0]; b.w[i] = r[1];
+        }
+    }
+    return __builtin_bit_cast(T, a) + __builtin_bit_cast(T, b);
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_sum(T s, int steps) // butterfly sum over 2^steps lanes, steps >= 4; every lane takes part
+{
+    static_for<4>([&](auto k) { s = wave_sum_step<decltype(k)::value>(s); });
+    if (steps > 4) s = wave_sum_step<4>(s);
+    if (steps > 5) s = wave_sum_step<5>(s);
+    return s;
+}
+
+// The same by shuffles, for many independent sums in a kernel whose vector units are busier than its LDS (k_enc_wave; the step of
+// 5 M coordinates, M = 4, in blocks of 2^7 65.5 us, 66.8 with the sums in registers).
+__device__ __forceinline__ float wave_sum_shuffled(float s, int steps)
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        if (k < steps) s += __shfl_xor(s, 1 << k, 64);
+    return s;
 }
 
 // v_writelane_b32 as the compiler's own intrinsic (this toolchain has no clang builtin for it, so the LLVM

@@ -98,13 +98,13 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
             if constexpr (SC >= 8) {
                 acc += p;
                 if (((c + 1) & ((1 << (SC - 8)) - 1)) == 0) {
-                    const float s = wave_sum(acc, 6);
+                    const float s = wave_sum_shuffled(acc, 6);
                     if (lane == 0) blk[c >> (SC - 8)] = s;
                     acc = 0.f;
                 }
             } else {
                 constexpr int ll = SC < 8 ? SC - 2 : 5; // log2 of the lanes of a block: 16 or 32
-                const float s = wave_sum(p, ll);
+                const float s = wave_sum_shuffled(p, ll);
                 if ((lane & ((1u << ll) - 1u)) == 0u) blk[c * (256 >> SC) + (lane >> ll)] = s;
             }
         }

@@ -69,9 +69,7 @@ static __global__ __launch_bounds__(256) void k_shall_sumsq(const ShallArgs a, u
     for (int s = 0; s < 4; ++s) {
         const bool live = 4 * q + s < a.W;
         const int32_t v = live ? 2 * c[s] - (int32_t)a.M : 0;
-        uint32_t sq = (uint32_t)(v * v); // at most 64^2 per lane
-#pragma unroll
-        for (int k = 1; k < 64; k <<= 1) sq += __shfl_xor(sq, k, 64);
+        const uint32_t sq = wave_sum((uint32_t)(v * v), 6); // at most 64^2 per lane
         if (lane == 0) part[wave * 4 + s] = sq;
     }
     __syncthreads();
