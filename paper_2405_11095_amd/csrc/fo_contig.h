@@ -46,7 +46,7 @@ struct ContigArgs {
     uint32_t logb;          // log2 of the transform length
     uint32_t use_tab;       // IN_GRAD: take the source pointer of slot y from the pointer table
     uint32_t compute_scale; // IN_GRAD: derive lambda from the measured block norm (else read scales[])
-    const float *partials;  // IN_F32, optional: [slot][tiles] sums of squares of the strided pass's tiles; lambda comes from their sum
+    const float *partials;  // SUMS: [slot][tiles] sums of squares of the strided pass's tiles; lambda comes from their sum
     uint64_t partials_stride;
     const float *scales_up; // IN_GRAD, optional: [M][nblocks] the workers' amplitudes; lambda is coef_lambda times the largest
     uint32_t dither;        // 0 uniform, 1 none
@@ -125,7 +125,8 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 // c_i = #{k < K : z_i + tau_{k,i} >= 0} in {0..K}, i.e. q_i = 2 c_i - K = (K / lambda) Q_{lambda,K}(z)_i, stored as
 // `planes` bit planes of W words each (plane p holds bit p of every c_i).  OUT_PACK draws K dithers per
 // coordinate and writes the planes; IN_BITS reads them.  K = 1 is the plain sign message and uses MULTIK = false.
-// SEG: the tile is made of segments, a.seg says how (TileMap).
+// SEG: the tile is made of segments, a.seg says how (TileMap).  SUMS: the amplitude comes from a.partials, in this kernel (as a
+// run-time choice it cost the launches that do not want it 2 %: the low pass of 16 vectors of 2^25 517 -> 531 us).
 // The work of 512 threads (t = 0..511) on tile `tile` of party slot `slot`; lds has kLdsWords words.
 // PAIR (gradient in, transform length exactly 2^16): two such groups of 512 threads in one workgroup take the two
 // tiles of a block; lds_partner is the other group's LDS.  The stage on bit 15 pairs coordinate i of the lower
@@ -137,7 +138,7 @@ __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src
 // part of the next tile begins (any readable tile if there is none), and its loads go out while this tile is quantised, each
 // chunk into the four registers that the group of coordinates before it has left.
 template <int IN, int OUT, bool DITHER, bool SMALLB, int SC, bool MULTIK, bool STATS = false, bool PAIR = false, bool LOOP = false,
-          bool SEG = false>
+          bool SEG = false, bool SUMS = false>
 __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &tab, const uint32_t tile, const uint32_t slot,
                                             uint32_t *const lds, const uint32_t t, uint32_t *const lds_partner = nullptr,
                                             float *const held = nullptr, const float *const next = nullptr)
@@ -177,7 +178,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
         if constexpr (IN == IN_F32) {
             // The block's sum of squares, by every workgroup in the same order (at most 2^10 tiles of the strided pass): a
             // launch of its own for it took 1 to 2 us.  Published by the barrier before the amplitude.
-            if (a.partials) {
+            if constexpr (SUMS) {
                 const uint32_t hb = a.logb - (uint32_t)kTileLog2;
                 const float *const part = a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb);
                 double d = 0.0;
@@ -422,7 +423,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 }
                 l = a.coef_lambda * sqrtf(s);
                 if (gb < a.nblocks && !(PAIR && (tile & 1u))) a.scales[slot * a.scales_stride + gb] = l;
-            } else if (IN == IN_F32 && a.partials) {
+            } else if constexpr (SUMS) {
                 double s = 0.0;
                 for (uint32_t k = 0; k < 8u; ++k) s += reinterpret_cast<const double *>(red)[k];
                 l = a.coef_lambda * (float)sqrt(s);
@@ -669,12 +670,13 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     }
 }
 
-template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false, bool SEG = false>
+template <int IN, int OUT, bool DITHER = false, bool SMALLB = false, int SC = 0, bool MULTIK = false, bool STATS = false, bool SEG = false,
+          bool SUMS = false>
 __global__ __launch_bounds__(kThreads, 4) void k_contig(const ContigArgs a, const PtrTab tab)
 {
     __shared__ uint32_t lds[kLdsWords];
     const uint32_t tile = SEG ? seg_tile(a.seg, blockIdx.x) : blockIdx.x;
-    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, false, SEG>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
+    contig_tile<IN, OUT, DITHER, SMALLB, SC, MULTIK, STATS, false, false, SEG, SUMS>(a, tab, tile, blockIdx.y, lds, threadIdx.x);
 }
 
 // Encode of blocks of exactly 2^16 coordinates in one pass: 1024 threads, one block (two tiles) per workgroup.

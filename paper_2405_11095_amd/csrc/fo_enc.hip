@@ -115,9 +115,11 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
         s2.src = pl->buf_c; s2.dst = tmp; s2.src_stride = 0; s2.dst_stride = tmp_stride;
         FO_TRY(launch_strided<SM_MID_F32>(pl, KID_ENC_MID, grid, st, s2, none));
     }
-    // Up to 2^10 tiles a block, every workgroup of the low pass adds up the partial sums itself (n = 2^24: 51.4 -> 50.0 us; 2^22: 27.2 -> 25.4); beyond,
-    // and where the workers have to agree, a kernel does it.
-    if (!scales_given && !common && pl->npass == 1 && pl->hb[0] <= 10) {
+    // Up to four tiles for every compute unit in the plan's workers, every workgroup of the low pass adds up its block's partial sums
+    // itself (n = 2^24: 51.4 -> 50.0 us; 2^22: 27.2 -> 25.4).  Longer ones lose more to it than the launch of its own takes, and where
+    // the workers have to agree there has to be one.  The rule looks at the plan alone: the two forms add in different orders.
+    if (!scales_given && !common && pl->npass == 1 && c.K == 1 && c.dither == FO_DITHER_UNIFORM &&
+        pl->p.M * pl->ntiles <= 4u * (uint64_t)pl->num_cus) {
         c.partials = pl->partials;
         c.partials_stride = pl->ntiles;
     } else if (!scales_given) {

@@ -17,6 +17,9 @@ int launch_pack_v(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigA
         if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, true, STATS, SEG>, grid, block, st, c, tab);
         return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, true, STATS, SEG>, grid, block, st, c, tab);
     }
+    if constexpr (IN == IN_F32) {
+        if (c.partials) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS, SEG, true>, grid, block, st, c, tab);
+    }
     if (dither && c.S == 15) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS, SEG>, grid, block, st, c, tab);
     if constexpr (IN == IN_GRAD && !STATS) {
         // blocks inside a wave's 4096 coordinates, each length compiled for itself

@@ -199,3 +199,29 @@ def test_random_long_plans(oracle, cfg):
                            device=torch.device("cuda:0"), threads=16, K=cfg["K"], eps_mode=cfg["eps_mode"],
                            server_scale=cfg["server_scale"], dither=cfg["dither"], scale_rule=cfg["scale_rule"], Bnorm=bnorm)
     gates(rep)
+
+
+@pytest.mark.parametrize("M,blk", [(1, 17), (6, 17), (7, 17), (1, 22), (6, 22)])
+def test_amplitudes_of_two_pass_plans(M, blk):
+    """The low pass adds up the strided pass's partial sums in plans of up to four tiles for every compute unit (1024), a
+    kernel of its own beyond; either way every block has its norm's amplitude, a block of NaN its NaN."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    d = (160 << 15) - 77                                # 160 tiles of 2^15: six workers are within, seven are not
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(blk)
+    g = torch.randn(d, generator=gen, device=dev)
+    g[3] = float("nan")
+    plan = B.Plan(d=d, M=M, block_log2=blk, seed=5)
+    bits, lam = torch.zeros(plan.W, dtype=torch.int64, device=dev), torch.zeros(plan.nblocks, device=dev)
+    plan.fo_profile_begin()
+    plan.fo_encode(g, 1, 0, bits, lam)
+    torch.cuda.synchronize()
+    tiles = plan.ntot >> 15
+    assert ("scale kernels" in plan.fo_profile_end()) == (M * tiles > 1024)
+    norms = torch.nn.functional.pad(g.double(), (0, plan.ntot - d)).view(plan.nblocks, -1).norm(dim=1)
+    coef = 2.0 * (torch.log(torch.tensor(float(plan.b), dtype=torch.float64)) / plan.b).sqrt().item()
+    assert bool(lam[0].isnan())
+    assert plan.nblocks == 1 or float((lam[1:].double() / (coef * norms[1:]) - 1).abs().max()) < 1e-6
+    plan.close()
