@@ -59,7 +59,7 @@ struct ContigArgs {
     uint32_t src_pad;       // IN_F32: tile t of the intermediate starts at t * (2^15 + src_pad) (see StridedArgs)
     uint32_t dst_pad;       // k_declow: the same for its int16 output
     uint32_t group_log2;    // k_declow<true>: log2 of the rows of a block (see Grouped16)
-    uint32_t seg;           // low passes of longer transforms: stages of a strided pass inside regions, else 0 (see TileMap)
+    uint32_t seg;           // decoder's low passes: stages of a strided pass inside regions, else 0 (see TileMap)
     uint32_t party0;        // party id of slot 0 (slot y is party0 + y); FO_PARTY_SERVER stays as is
     uint32_t eps_party0;    // same for the eps stream
     uint32_t k0, k1, round_lo;
@@ -75,8 +75,7 @@ struct ContigArgs {
 // Where the 2^15 coordinates of a low pass's tile lie.  seg = 0: one after the other, tile after tile.  seg = s > 0: the strided
 // pass of s stages works inside regions (see StridedGeom), takes the s bits from 8 on, and the tile is one row of 256
 // coordinates of each of the 128 regions of 2^(8+s) that make up a block.  Bits 0..7 of the tile-local coordinate are the
-// coordinate's own, bits 8..14 say which region.  Reading segments of 1 KiB costs the low pass nothing for s = 10 (0.55 ms
-// for the 17 vectors of n = 2^25, M = 16 either way) and a tenth for s = 12 (0.59 -> 0.65 ms, n = 2^27, M = 4).
+// coordinate's own, bits 8..14 say which region.
 struct TileMap {
     uint32_t seg, unit0; // unit0: coordinate / 256 of the tile's first 256
     __device__ __forceinline__ TileMap(uint32_t seg_, uint32_t tile) : seg(seg_)
@@ -87,7 +86,7 @@ struct TileMap {
     __device__ __forceinline__ uint32_t unit(uint32_t q) const { return unit0 + (q << seg); }
 };
 // Tiles that are neighbours inside a region have block indices on the same XCD (blocks are dealt round-robin over 8): four of
-// them share the 128-byte lines of packed signs that they read or write.
+// them share the 128-byte lines of packed signs that they read.
 __device__ __forceinline__ uint32_t seg_tile(uint32_t seg, uint32_t i)
 {
     return seg ? (i & ~31u) | ((i & 7u) << 2) | ((i >> 3) & 3u) : i;
@@ -155,7 +154,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     const float *const red_hi = PAIR ? reinterpret_cast<const float *>(((tile & 1u) ? lds : lds_partner) + kXWords + kEpsWords + kLamWords) : nullptr;
 
     const uint32_t lane = t & 63u, wave = LOOP ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6)) : t >> 6;
-    static_assert(!SEG || IN == IN_F32 || OUT == OUT_I32, "the low passes of longer transforms");
+    static_assert(!SEG || (IN == IN_BITS && OUT == OUT_I32), "the decoder's low pass of longer transforms");
     const TileMap map(SEG ? a.seg : 0u, tile);
     const uint64_t base = (uint64_t)map.unit0 << 8;
     const uint32_t S = SC ? (uint32_t)SC : a.S;

@@ -105,8 +105,7 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
     s.partials = pl->partials; s.eps_party0 = eps_party_of(pl, party0);
     // the intermediate in plan scratch has padded rows; the one of fo_encode_noalloc and the server's (tmp == nullptr
     // never happens here) follow the plan's setting as well
-    c.seg = encode_regions(pl);
-    const uint32_t pad = pl->npass == 1 && !c.seg ? pl->pad32 : 0u;
+    const uint32_t pad = pl->npass == 1 ? pl->pad32 : 0u;
     s.dst_pad = pad;
     if (pl->npass == 2 && nslots != 1) return FO_EINVAL; // three-pass transforms are encoded one party at a time
     FO_TRY(launch_strided<SM_ENC_FIRST>(pl, KID_ENC_HIGH, grid, st, s, tb));

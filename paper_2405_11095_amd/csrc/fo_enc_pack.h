@@ -7,20 +7,20 @@
 namespace fo_host {
 
 // The packing kernels are compiled per (dither on/off, transform length below 256).
-template <int IN, bool STATS, bool SEG>
-int launch_pack_v(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigArgs &c, const PtrTab &tab)
+template <int IN, bool STATS>
+int launch_pack_s(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigArgs &c, const PtrTab &tab)
 {
     const bool dither = c.dither == FO_DITHER_UNIFORM, small = c.S < 8;
     const dim3 block(kThreads);
     if (c.K > 1) { // the K-fold quantiser of the server's message
-        if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, true, STATS, SEG>, grid, block, st, c, tab);
-        if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, true, STATS, SEG>, grid, block, st, c, tab);
-        return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, true, STATS, SEG>, grid, block, st, c, tab);
+        if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, true, STATS>, grid, block, st, c, tab);
+        if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, true, STATS>, grid, block, st, c, tab);
+        return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, true, STATS>, grid, block, st, c, tab);
     }
     if constexpr (IN == IN_F32) {
-        if (c.partials) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS, SEG, true>, grid, block, st, c, tab);
+        if (c.partials) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS, false, true>, grid, block, st, c, tab);
     }
-    if (dither && c.S == 15) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS, SEG>, grid, block, st, c, tab);
+    if (dither && c.S == 15) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 15, false, STATS>, grid, block, st, c, tab);
     if constexpr (IN == IN_GRAD && !STATS) {
         // blocks inside a wave's 4096 coordinates, each length compiled for itself
         if (dither && c.S <= 12) {
@@ -41,19 +41,10 @@ int launch_pack_v(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigA
         if (dither && c.S == 14) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 14>, grid, block, st, c, tab);
     }
     if constexpr (STATS) {
-        if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, false, STATS, SEG>, grid, block, st, c, tab);
+        if (dither && small) return launch(pl, kid, k_contig<IN, OUT_PACK, true, true, 0, false, STATS>, grid, block, st, c, tab);
     }
-    if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, false, STATS, SEG>, grid, block, st, c, tab);
-    return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, false, STATS, SEG>, grid, block, st, c, tab);
-}
-
-template <int IN, bool STATS>
-int launch_pack_s(fo_plan *pl, int kid, dim3 grid, hipStream_t st, const ContigArgs &c, const PtrTab &tab)
-{
-    if constexpr (IN == IN_F32) {
-        if (c.seg) return launch_pack_v<IN, STATS, true>(pl, kid, grid, st, c, tab);
-    }
-    return launch_pack_v<IN, STATS, false>(pl, kid, grid, st, c, tab);
+    if (dither) return launch(pl, kid, k_contig<IN, OUT_PACK, true, false, 0, false, STATS>, grid, block, st, c, tab);
+    return launch(pl, kid, k_contig<IN, OUT_PACK, false, false, 0, false, STATS>, grid, block, st, c, tab);
 }
 
 } // namespace fo_host

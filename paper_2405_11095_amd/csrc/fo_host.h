@@ -167,7 +167,7 @@ inline bool args_ok(const StridedArgs &s, const PtrTab &tab, int kid)
     if (kid == KID_ENC_HIGH ? (s.use_tab ? !tab.p[0] : !s.src) : !s.src) return false;
     if (kid == KID_ENC_HIGH && !s.partials) return false;
     if ((kid == KID_DEC_HIGH || kid == KID_SERVER_HIGH || kid == KID_SERVER_MFMA) && !s.scales) return false;
-    return s.hb >= 1 && (s.hb < kSegHigh || (s.hb <= 12 && s.ls == (uint32_t)kTileLog2)) && s.ls >= (uint32_t)kTileLog2;
+    return s.hb >= 1 && (s.hb < 10 || (s.hb <= 12 && s.ls == (uint32_t)kTileLog2)) && s.ls >= (uint32_t)kTileLog2;
 }
 template <typename... Args>
 inline bool args_ok(const Args &...) { return true; }
@@ -306,9 +306,8 @@ constexpr SmallRule kSmallRules[4] = {
     { (uint64_t)1 << 21, (uint64_t)1 << 26 }, // b <= 2^20
 };
 
-// Stages of a strided pass inside regions (see kRegions): what the low pass of the encoder and of the decoder has to know.
-inline uint32_t encode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] >= kSegHigh ? pl->hb[0] : 0u; }
-inline uint32_t decode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] > kSegHigh ? pl->hb[0] : 0u; }
+// Stages of the decoder's strided pass inside regions (see kRegions), which its low pass has to know.
+inline uint32_t decode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] >= kSegHigh ? pl->hb[0] : 0u; }
 
 // Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
 // Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a

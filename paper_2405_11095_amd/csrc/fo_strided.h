@@ -12,9 +12,9 @@
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
 // v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
-// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.07 ms, 3.94 GB, 40 %; server 0.88 ms,
+// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.17 ms, 3.94 GB, 40 %; server 0.88 ms,
 // 1.70 GB, 52 %; decode 0.37 ms, 1.13 GB, 22 %.  Encode and decode are bound by the 32-byte row segments of the caller's
-// vectors: reading and writing them without arithmetic takes the encode's time (an encode on tiles of 2^16 coordinates, with
+// vectors (an encode on tiles of 2^16 coordinates, with
 // segments of 64 bytes but one workgroup per compute unit, took a seventh longer; a decode of 32 values per thread, with
 // half the loads in flight, an eighth).  In the server, one workgroup to a compute unit,
 // the stages of a worker and the loads of the next cover each other only in part.
@@ -58,7 +58,6 @@ struct StridedArgs {
     float delta;
     // Padding of an intermediate that the neighbouring contiguous pass reads or writes tile by tile: row R (2^ls elements)
     // starts at R * (2^ls + pad) elements, which keeps rows that are a power of two apart off the same memory channels.
-    // Regions have no padding.
     uint32_t dst_pad;      // ENC_FIRST, SERVER, SHARED: fp32 destination
     uint32_t src_pad;      // DEC_LAST, SERVER with the int16 source
 };
@@ -66,18 +65,19 @@ struct StridedArgs {
 // Element offset of tile coordinate u from the tile origin.  Each bit of u has a fixed weight
 // (column bits keep theirs, row bits move up to the row stride), so off(u1 | u2) = off(u1) + off(u2)
 // for disjoint bit sets: a thread adds its own part once and a wave-uniform part per register pair.
-// Regions: the encoder's pass of ten to twelve stages and the decoder's of eleven and twelve, which read or write the caller's
-// fp32 vectors, take the bits from kSegLog2 = 8 on (a region of 2^(8+hb) consecutive coordinates is 2^hb rows of 256) and leave
-// bits 0..7 and the seven above the region to the low pass (TileMap).  Tiles have 32, 16 or 8 columns, so the 8, 16 or 32 tiles
-// of a region read every 1 KiB row between them; with block indices that put them on one XCD the pieces of a row are asked for
-// together.  With rows 2^15 coordinates (128 KiB) apart every row is another page and all rows of a tile start on the same
-// memory channel.  Reading and writing 2^29 fp32 in the two patterns without arithmetic: ten stages 0.99 -> 0.78 ms, eleven
-// 1.33 -> 0.90, twelve 1.52 -> 1.08; nine 0.86 -> 0.84 and eight 0.78 both ways, hence the line at ten.  The kernels: encode of
-// n = 2^25, M = 16 0.80 -> 0.76 ms, n = 2^27, M = 4 1.17 -> 1.06; decode of 2^27 0.48 -> 0.37 ms.  Not where the caller's vector is
-// not touched (the server: int16 in padded rows, 0.33 -> 0.35 ms at n = 2^25, even at 2^27) and not in the decoder of ten stages (75 -> 82 us).
-constexpr uint32_t kSegLog2 = 8, kSegHigh = 10;
+// Regions: the decoder's pass of eleven and twelve stages, which writes the caller's fp32 vector, takes the bits from
+// kSegLog2 = 8 on (a region of 2^(8+hb) consecutive coordinates is 2^hb rows of 256) and leaves bits 0..7 and the seven above
+// the region to the low pass (TileMap).  Tiles have 16 or 8 columns, so the 16 or 32 tiles of a region write every 1 KiB row
+// between them; with block indices that put them on one XCD the pieces of a row are written together.  With rows 2^15
+// coordinates (128 KiB) apart every row is another page and all rows of a tile start on the same memory channel.  Decode of
+// 2^27 0.48 -> 0.37 ms; the decoder of ten stages is slower for it (75 -> 82 us), and the server, which touches no vector of the
+// caller's (int16 in padded rows), 0.33 -> 0.35 ms at n = 2^25 and even at 2^27.  The values are integers: any order of the
+// stages gives the same.  The encoder's are not, and it keeps its rows 2^15 apart (encode of n = 2^25, M = 16 0.80 ms, 0.76 in
+// regions): the padding is at the top, so with the top stages first a sum with a zero of it is exact, and with the bits from 8 on
+// first the rounding error against 64-bit sums grows by 0.4 to 1 % at three quarters of 2^25 and by up to 3 % at half.
+constexpr uint32_t kSegLog2 = 8, kSegHigh = 11;
 template <int MODE, int HB>
-constexpr bool kRegions = (MODE == 0 && HB >= (int)kSegHigh) || (MODE == 1 && HB > (int)kSegHigh); // SM_ENC_FIRST, SM_DEC_LAST
+constexpr bool kRegions = MODE == 1 && HB >= (int)kSegHigh; // SM_DEC_LAST
 struct StridedGeom {
     uint64_t origin; // coordinate of u = 0
     uint32_t cb, ls;
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(SL<LV>::T, 4) void k_strided(const StridedArgs a, c
                 }
             }
         } else {
-            const uint32_t pad = (MODE == SM_ENC_FIRST && !REGIONS) ? a.dst_pad : 0u;
+            const uint32_t pad = (MODE == SM_ENC_FIRST) ? a.dst_pad : 0u;
             TV *dst = static_cast<TV *>(a.dst) + slot * a.dst_stride + g.origin + (g.origin >> g.ls) * pad;
             const uint32_t ot_pad = ot_out + (ut_out >> cb) * pad;
 #pragma unroll

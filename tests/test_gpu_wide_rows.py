@@ -59,3 +59,37 @@ def test_three_pass_server_with_several_workers():
     plan.fo_encode(gbar, rnd, B.PARTY_SERVER, again, lam_s, flags=B.FORCE_SCALE)
     differ = (again ^ down[0]) != 0
     assert float(differ.float().mean()) < 1e-5   # near ties only: the fused pass adds in another order
+
+
+@pytest.mark.parametrize("low", [8, 14])
+@pytest.mark.parametrize("logb", [22, 25, 26, 27])
+def test_top_stages_come_first(logb, low):
+    """The encoder's strided pass takes the top index bits: the padding lies there, and a sum with one of its zeros is exact.
+    Two entries of 2^26 that the top bit alone tells apart cancel in half of the transform, and what is left is the entry 1,
+    whose sum with 2^26 would have been 2^26."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    top = 1 << (logb - 1)
+    d = top + (1 << 15) + 3
+    plan = B.Plan(d=d, M=1, dither=B.DITHER_NONE, seed=41)
+    assert plan.b == 1 << logb and plan.nblocks == 1
+    lam = torch.ones(1, device=dev)
+
+    def encode(entries):
+        g = torch.zeros(d, device=dev)
+        for i, x in entries.items():
+            g[i] = x
+        bits = torch.zeros(plan.W, dtype=torch.int64, device=dev)
+        plan.fo_encode(g, 7, 0, bits, lam, flags=B.FORCE_SCALE)
+        return bits
+
+    eps = [1 if int(encode({i: 1.0})[0]) & 1 else -1 for i in (0, top, 1 << low)]    # coordinate 0 of the transform of e_i
+    got = encode({0: 2.0 ** 26, top: 2.0 ** 26, 1 << low: 1.0}).view(2, -1)
+    lower_cancels = eps[0] != eps[1]
+    left = got[0 if lower_cancels else 1]
+    word = torch.arange(left.numel(), device=dev)
+    positive = (((word >> (low - 6)) & 1) == 0) == (eps[2] > 0)
+    assert torch.equal(left, -positive.long())
+    assert torch.equal(got[1 if lower_cancels else 0], torch.full_like(left, -1 if eps[0] > 0 else 0))
+    plan.close()
