@@ -17,21 +17,14 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 
 // lambda_j = coef * sqrt(sum of the tile partials of block j)   (amplitude of Thm 5.5, B = ||g_block||)
-__global__ __launch_bounds__(256) void k_finalize_scales(const float *partials, uint64_t ntiles, uint32_t tiles_per_block,
+__global__ __launch_bounds__(kThreads) void k_finalize_scales(const float *partials, uint64_t ntiles, uint32_t tiles_per_block,
                                                           float coef, float *scales, uint64_t scales_stride)
 {
-    __shared__ double red[256];
+    __shared__ double part[kThreads / 64];
     const uint32_t j = blockIdx.x, slot = blockIdx.y, t = threadIdx.x;
-    const float *p = partials + (uint64_t)slot * ntiles + (uint64_t)j * tiles_per_block;
-    double s = 0.0;
-    for (uint32_t k = t; k < tiles_per_block; k += 256) s += (double)p[k];
-    red[t] = s;
+    sum_of_partials(part, partials + (uint64_t)slot * ntiles + (uint64_t)j * tiles_per_block, tiles_per_block, t);
     __syncthreads();
-    for (uint32_t h = 128; h > 0; h >>= 1) {
-        if (t < h) red[t] += red[t + h];
-        __syncthreads();
-    }
-    if (t == 0) scales[slot * scales_stride + j] = coef * (float)sqrt(red[0]);
+    if (t == 0) scales[slot * scales_stride + j] = coef * (float)sqrt(sum_of_waves(part));
 }
 
 __global__ void k_fill_scales(float *scales, uint64_t scales_stride, uint64_t nblocks, float value)
@@ -77,7 +70,7 @@ namespace fo_host {
 
 int launch_finalize_scales(fo_plan *pl, hipStream_t st, uint32_t nslots, float coef, float *scales, uint64_t scales_stride)
 {
-    return launch(pl, KID_SCALES, k_finalize_scales, dim3((unsigned)pl->nblocks, nslots), dim3(256), st, pl->partials, pl->ntiles,
+    return launch(pl, KID_SCALES, k_finalize_scales, dim3((unsigned)pl->nblocks, nslots), dim3(kThreads), st, pl->partials, pl->ntiles,
                   (uint32_t)(pl->b >> kTileLog2), coef, scales, scales_stride);
 }
 int launch_fill_scales(fo_plan *pl, hipStream_t st, uint32_t nslots, float *scales, uint64_t scales_stride, float value)

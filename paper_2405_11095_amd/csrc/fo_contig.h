@@ -179,11 +179,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             // launch of its own for it took 1 to 2 us.  Published by the barrier before the amplitude.
             if constexpr (SUMS) {
                 const uint32_t hb = a.logb - (uint32_t)kTileLog2;
-                const float *const part = a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb);
-                double d = 0.0;
-                for (uint32_t k = t; k < (1u << hb); k += kThreads) d += (double)part[k];
-                d = wave_sum(d, 6);
-                if (lane == 0u) reinterpret_cast<double *>(red)[wave] = d;
+                sum_of_partials(reinterpret_cast<double *>(red), a.partials + slot * a.partials_stride + ((uint64_t)(tile >> hb) << hb), 1u << hb, t);
             }
             const uint32_t ws = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave);
             src += (uint64_t)tile * a.src_pad;
@@ -423,9 +419,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 l = a.coef_lambda * sqrtf(s);
                 if (gb < a.nblocks && !(PAIR && (tile & 1u))) a.scales[slot * a.scales_stride + gb] = l;
             } else if constexpr (SUMS) {
-                double s = 0.0;
-                for (uint32_t k = 0; k < 8u; ++k) s += reinterpret_cast<const double *>(red)[k];
-                l = a.coef_lambda * (float)sqrt(s);
+                l = a.coef_lambda * (float)sqrt(sum_of_waves(reinterpret_cast<const double *>(red)));
                 if ((tile & ((1u << (a.logb - (uint32_t)kTileLog2)) - 1u)) == 0u) a.scales[slot * a.scales_stride + gb] = l;
             } else if (IN == IN_GRAD && !PAIR && a.scales_up) {
                 if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l = server_scale_of(a, gb);

@@ -195,7 +195,23 @@ __device__ __forceinline__ T wave_sum(T s, int steps) // butterfly sum over 2^st
     return s;
 }
 
-// The same by shuffles, for many independent sums in a kernel whose vector units are busier than its LDS (k_enc_wave; the step of
+// The sum of a block's n partial sums by a workgroup of kThreads: every wave's part, then, behind a barrier, the whole of `part`
+// (a double a wave).  Whoever wants an amplitude from partial sums takes it from here: the same one to the bit.
+__device__ __forceinline__ void sum_of_partials(double *part, const float *p, uint32_t n, uint32_t t)
+{
+    double d = 0.0;
+    for (uint32_t k = t; k < n; k += kThreads) d += (double)p[k];
+    d = wave_sum(d, 6);
+    if ((t & 63u) == 0u) part[t >> 6] = d;
+}
+__device__ __forceinline__ double sum_of_waves(const double *part)
+{
+    double s = 0.0;
+    for (uint32_t k = 0; k < kThreads / 64u; ++k) s += part[k];
+    return s;
+}
+
+// wave_sum by shuffles, for many independent sums in a kernel whose vector units are busier than its LDS (k_enc_wave; the step of
 // 5 M coordinates, M = 4, in blocks of 2^7 65.5 us, 66.8 with the sums in registers).
 __device__ __forceinline__ float wave_sum_shuffled(float s, int steps)
 {

@@ -116,7 +116,7 @@ int launch_encode(fo_plan *pl, const PtrTab *tab, const float *src, uint64_t src
     }
     // Up to four tiles for every compute unit in the plan's workers, every workgroup of the low pass adds up its block's partial sums
     // itself (n = 2^24: 51.4 -> 50.0 us; 2^22: 27.2 -> 25.4).  Longer ones lose more to it than the launch of its own takes, and where
-    // the workers have to agree there has to be one.  The rule looks at the plan alone: the two forms add in different orders.
+    // the workers have to agree there has to be one.  Both forms add in the same order (sum_of_partials).
     if (!scales_given && !common && pl->npass == 1 && c.K == 1 && c.dither == FO_DITHER_UNIFORM &&
         pl->p.M * pl->ntiles <= 4u * (uint64_t)pl->num_cus) {
         c.partials = pl->partials;

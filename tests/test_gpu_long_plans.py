@@ -6,7 +6,7 @@ one at every length."""
 import numpy as np
 import pytest
 
-from tests.parity import SERVER, check_round_trip, compare_bits, gates
+from tests.parity import SERVER, _peek, check_round_trip, compare_bits, gates
 
 pytestmark = pytest.mark.gpu
 
@@ -224,4 +224,40 @@ def test_amplitudes_of_two_pass_plans(M, blk):
     coef = 2.0 * (torch.log(torch.tensor(float(plan.b), dtype=torch.float64)) / plan.b).sqrt().item()
     assert bool(lam[0].isnan())
     assert plan.nblocks == 1 or float((lam[1:].double() / (coef * norms[1:]) - 1).abs().max()) < 1e-6
+    plan.close()
+
+
+def test_step_and_call_by_hand_add_partial_sums_alike():
+    """fo_encode adds up a block's partial sums in its low pass, fo_step with a shared eps in a kernel of its own.  Squares whose
+    sum is m^2 for an odd m of 25 bits, and two more of 0.4 ulp of it, which reach it in one addition or in two: the root rounds
+    to m - 1 or m + 1."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    d = 1 << 23                                            # 256 tiles of 128 columns; entries lie in the first row
+    coef = np.float32(2.0 * np.sqrt(np.log(d) / d))
+    m = 3 * (1 << 23) + 1                                  # an ulp of m^2 is an eighth and moves the root by 0.67 ulp
+    while (m // 2) % 2 or coef * np.float32(m - 1) == coef * np.float32(m + 1):    # a tie that goes down, and shows
+        m += 2
+    squares, rest = [], m * m
+    while rest:                                            # m^2 as squares of twelve bits
+        k = max(0, (rest.bit_length() - 23) // 2)
+        x = min(int(np.sqrt(float(rest))) >> k, 4095) << k
+        squares.append(x)
+        rest -= x * x
+    assert len(squares) < 64 and sum(x * x for x in squares) == m * m and squares[0] ** 2 > 1 << 49
+    g = torch.zeros(d, device=dev)
+    for tile, x in enumerate(squares):
+        g[128 * tile] = float(x)
+    for tile in (64, 192):
+        g[128 * tile] = 0.05 ** 0.5
+    plan = B.Plan(d=d, M=1, eps_mode=B.EPS_SHARED_WORKERS, seed=3)
+    assert plan.nblocks == 1 and plan.b == d
+    bits, lam = torch.zeros(plan.W, dtype=torch.int64, device=dev), torch.zeros(1, device=dev)
+    plan.fo_encode(g, 1, 0, bits, lam)
+    plan.fo_step([g], torch.zeros(d, device=dev), 0.1, 1)
+    torch.cuda.synchronize()
+    step = _peek(torch, plan.fo_step_messages()[1], 1, torch.float32, dev)
+    assert float(lam[0]) in (float(coef * np.float32(m - 1)), float(coef * np.float32(m + 1)))
+    assert float(step[0]) == float(lam[0])
     plan.close()
