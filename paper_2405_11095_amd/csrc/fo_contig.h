@@ -259,7 +259,11 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
     }
 
     if constexpr (IN == IN_GRAD) {
-        // per-block sum of squares of the raw gradient (sign flips do not change it)
+        // per-block sum of squares of the raw gradient (sign flips do not change it), spelled out: a block's amplitude is the
+        // same to the bit whichever kernel forms it (k_enc_wave has the same lines)
+        auto squares = [&](int c) -> float {
+            return fmaf(v[4 * c], v[4 * c], v[4 * c + 1] * v[4 * c + 1]) + fmaf(v[4 * c + 2], v[4 * c + 2], v[4 * c + 3] * v[4 * c + 3]);
+        };
         if (a.compute_scale) {
             const uint32_t G = S < 12u ? S : 12u;        // segment = 2^G coordinates, inside one wave and one block
             const uint32_t segs_per_wave = 4096u >> G;
@@ -268,12 +272,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 const uint32_t cps = 1u << (G - 8u);      // chunks per segment
 #pragma unroll
                 for (int c = 0; c < 16; ++c) {
-                    if constexpr (PAIR) // spelled out: a block's amplitude is the same to the bit whichever kernel forms it
-                        acc += fmaf(v[4 * c], v[4 * c], v[4 * c + 1] * v[4 * c + 1]) +
-                               fmaf(v[4 * c + 2], v[4 * c + 2], v[4 * c + 3] * v[4 * c + 3]);
-                    else
-                        acc += (v[4 * c] * v[4 * c] + v[4 * c + 1] * v[4 * c + 1]) +
-                               (v[4 * c + 2] * v[4 * c + 2] + v[4 * c + 3] * v[4 * c + 3]);
+                    acc += squares(c);
                     if (((c + 1) & (cps - 1u)) == 0u) {
                         const float s = wave_sum(acc, 6);
                         if (lane == 0) red[wave * segs_per_wave + ((uint32_t)c >> (G - 8u))] = s;
@@ -284,9 +283,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 const uint32_t lanes_log2 = S - 2u;       // lanes per segment: 16 or 32
 #pragma unroll
                 for (int c = 0; c < 16; ++c) {
-                    const float p = (v[4 * c] * v[4 * c] + v[4 * c + 1] * v[4 * c + 1]) +
-                                    (v[4 * c + 2] * v[4 * c + 2] + v[4 * c + 3] * v[4 * c + 3]);
-                    const float s = wave_sum(p, (int)lanes_log2);
+                    const float s = wave_sum(squares(c), (int)lanes_log2);
                     if ((lane & ((1u << lanes_log2) - 1u)) == 0u)
                         red[wave * segs_per_wave + c * (256u >> S) + (lane >> lanes_log2)] = s;
                 }

@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
     constexpr uint32_t nseg = 4096u >> SC;
     const uint64_t gb = (base >> SC) + lane; // block of lane l < nseg
     if (a.compute_scale) {
-        // sums of squares of the blocks (sign flips do not change them), spelled out so that every kernel that measures a
-        // block this way finds the same amplitude to the bit
+        // sums of squares of the blocks (sign flips do not change them), spelled out as in contig_tile, whose kernels measure
+        // the same blocks for a K-fold message, without dither and with counters: the same amplitude to the bit
         float acc = 0.f;
 #pragma unroll
         for (int c = 0; c < 16; ++c) {

@@ -46,3 +46,31 @@ def test_blocks_of_a_wave_are_independent(blk):
     again, _ = encode(g, lam)
     assert torch.equal(again, bits)
     plan.close()
+
+
+@pytest.mark.parametrize("blk", [6, 7, 8, 9, 10, 11, 12, 13, 15])
+def test_every_kernel_finds_the_same_amplitude(blk):
+    """Counters attached, a K-fold quantiser and none of the dither take another kernel than the plain message: the amplitudes
+    they measure are the same to the bit."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    d = (1 << 22) + 5 * 4096 + 333
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(100 + blk)
+    first = None
+    for kw in ({}, {"K": 3}, {"dither": 1}):
+        plan = B.Plan(d=d, M=1, block_log2=blk, seed=31, **kw)
+        if first is None:
+            g = torch.randn(plan.ntot, generator=gen, device=dev)
+        bits = torch.zeros(plan.planes, plan.W, dtype=torch.int64, device=dev)
+        for stats in (None, torch.zeros(2 * (B.MAX_WORKERS + 1), dtype=torch.int64, device=dev)):
+            plan.fo_set_stats(stats)
+            lam = torch.zeros(plan.nblocks, device=dev)
+            plan.fo_encode(g, 9, B.PARTY_SERVER, bits, lam)
+            torch.cuda.synchronize()
+            first = lam if first is None else first
+            print(f"2^{blk} {kw} counters {stats is not None}: {int((lam != first).sum())} of {plan.nblocks} differ", flush=True)
+            assert torch.equal(lam, first)
+        plan.fo_set_stats(None)
+        plan.close()
