@@ -554,6 +554,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 if ((uint32_t)p < a.planes) dst[(uint64_t)p * a.W] = ((uint64_t)hi[p] << 32) | lo[p];
         }
     } else if constexpr (OUT == OUT_PACK && DITHER && !STATS) {
+        static_assert(!SMALLB, "plain messages of blocks of 64 and 128 are k_enc_wave's");
         // Def. 3.2 with the dither u = (2 r + 1 - 2^24) 2^-24, r the top 24 bits of the 32-bit draw w:
         //   z + lambda' u >= 0  <=>  r >= ((2^24 - 1) - z 2^24 / lambda') / 2  <=>  w >= T,  T = 2^31 - 128 - 128 z 2^24 / lambda',
         // so a coordinate costs one multiply-add, one saturating conversion (T <= 0 -> 0: always +1; T >= 2^32 -> 2^32 - 1)
@@ -566,14 +567,11 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
             uint32_t w[4];
             const uint32_t lg = local_of(2 * g); // b6 = b7 = 0
             philox(dither_of(g) | lane, key_dit, w);
-            float kq_g = 0.f;
-            if constexpr (!SMALLB) kq_g = lam[lg >> S];
+            const float kq = lam[lg >> S];
             uint64_t word[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const int r = 2 * g + (s & 1) + 32 * (s >> 1); // slot s = b6 | b7 << 1
-                float kq = kq_g;
-                if constexpr (SMALLB) kq = lam[local_of(r) >> S];
                 uint32_t thr;
                 asm("v_cvt_u32_f32 %0, %1" : "=v"(thr) : "v"(fmaf(v[r], kq, 2147483520.f)));
                 word[s] = __ballot(w[s] >= thr) & __ballot(kq == kq);
