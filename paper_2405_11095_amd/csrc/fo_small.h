@@ -508,28 +508,77 @@ __global__ __launch_bounds__(kSmThreads) void k_small_decode(const SmallArgs a)
     }
 }
 
+// G groups of 256 threads share the workers of a tile: in every round each group transforms one worker's message, then every
+// group adds up its share of the registers over the round's workers, in the workers' order.  What the groups hand one another
+// are the transforms with the eps signs on, which are exact, and the amplitude comes in with the addition, so the mean has
+// the roundings, and the bits, of one group that takes one worker after the other.  (Sums of each group's own workers, added
+// up at the end, round every group's first product as well: the mean's error against 64-bit sums grew by up to 20 % for
+// two to seven workers of like amplitudes.)
+template <int G>
+struct SmallJoin {
+    static constexpr int R = 16 / G; // registers a group adds up: R grp ..
+    float4 value[G][4 * kSmThreads]; // registers 4 q .. 4 q + 3 of thread t at 256 q + t
+    __device__ __forceinline__ void put(uint32_t grp, uint32_t t, const float (&v)[16])
+    {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) value[grp][q * 256 + t] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+    }
+    // coef(g, r): amplitude of group g's worker for register r.  A group without a worker in the last round puts any finite
+    // values, and its amplitude is zero.  A barrier lies between put and this, and another between this and the next put.
+    template <typename F>
+    __device__ __forceinline__ void add(float (&part)[R], uint32_t grp, uint32_t t, F &&coef) const
+    {
+#pragma unroll
+        for (uint32_t g = 0; g < (uint32_t)G; ++g)
+#pragma unroll
+            for (int i = 0; i < R; i += 4) {
+                const float4 x = value[g][(grp * R + i) * 64u + t];
+                part[i] = fmaf(x.x, coef(g, grp * R + i), part[i]);
+                part[i + 1] = fmaf(x.y, coef(g, grp * R + i + 1), part[i + 1]);
+                part[i + 2] = fmaf(x.z, coef(g, grp * R + i + 2), part[i + 2]);
+                part[i + 3] = fmaf(x.w, coef(g, grp * R + i + 3), part[i + 3]);
+            }
+    }
+    // the groups' shares to the first one, through LDS that nothing else uses any more (16-byte aligned)
+    static __device__ __forceinline__ void hand_over(const float (&part)[R], float *x, uint32_t grp, uint32_t t)
+    {
+        if (grp)
+#pragma unroll
+            for (int i = 0; i < R; i += 4)
+                reinterpret_cast<float4 *>(x)[i * 64 + t] = make_float4(part[i], part[i + 1], part[i + 2], part[i + 3]);
+    }
+    template <typename F>
+    static __device__ __forceinline__ void take_over(float (&acc)[16], const float (&part)[R], F &&x_of, uint32_t t)
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = part[r];
+#pragma unroll
+        for (int r = R; r < 16; r += 4) {
+            const float4 x = reinterpret_cast<const float4 *>(x_of((uint32_t)(r / R)))[(r % R) * 64 + t];
+            acc[r] = x.x; acc[r + 1] = x.y; acc[r + 2] = x.z; acc[r + 3] = x.w;
+        }
+    }
+};
+
 // Server for b <= 2^12: the mean of the M messages in registers, its encode, and with UPDATE (fo_step) the decoder of
-// the server's own message with the update of x.  G > 1: G groups of 256 threads share the workers, as in k_small_high.
-// One wave on a SIMD waits out every exchange and generator chain of the workers one after the other; the step, us, one group
-// and four: d = 10^6 in blocks of 2^12, M = 8 36.4 and 30.6; 2 * 10^5, M = 32 76.7 and 48.4; 5 * 10^4, M = 4 20.4 and 18.2.
+// the server's own message with the update of x.  G > 1: G groups of 256 threads share the workers (see SmallJoin).  One wave
+// on a SIMD waits out every exchange and generator chain of the workers one after the other; the step, us, one group and four:
+// d = 10^6 in blocks of 2^12, M = 8 35.9 and 28.7; 2 * 10^5, M = 32 78.6 and 45.6; 5 * 10^4, M = 4 20.6 and 17.5.
 // The eps words come eight workers at a time, so that every thread has a generator block to draw (d = 3 * 10^6 in blocks of
 // 2^9, M = 5, K = 4: 53.5 us a step with one worker's at a time, 52.9 like this).
 template <bool DITHER, bool MULTIK, bool UPDATE, int G>
 __global__ __launch_bounds__(kSmThreads * G) void k_small_server(const SmallArgs a)
 {
-    __shared__ SmallLds ls[G];
+    __shared__ SmallLds l; // of the first group
     __shared__ __attribute__((aligned(16))) uint32_t eps8s[G][8 * kSmEpsWords];
     const uint32_t t = G > 1 ? threadIdx.x & (kSmThreads - 1u) : threadIdx.x, lane = t & 63u, wave = t >> 6, S = a.S;
     const uint32_t grp = G > 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kSmThreads)) : 0u;
-    SmallLds &l = ls[grp];
     uint32_t *const eps8 = eps8s[grp];
     const uint64_t tile = blockIdx.x, base = tile << kSmLog2;
     const uint32_t nblk = kSmTile >> S;
     uint32_t rk1, rlo;
     resolve_round(a.k1, a.round_lo, a.round_dev, rk1, rlo);
     float acc[16], v[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     const uint32_t nmsg = a.count ? 1u : a.M;
     auto word = [&](uint32_t p, uint32_t w) { const uint64_t gw = tile * 64u + w; return gw < a.W ? a.bits_in[(uint64_t)p * a.W + gw] : 0ull; };
     // a worker's words and amplitude are asked for one worker ahead
@@ -543,44 +592,62 @@ __global__ __launch_bounds__(kSmThreads * G) void k_small_server(const SmallArgs
             for (int q = 0; q < 4; ++q) wnext[q] = word(m, wave * 16u + (lane >> 4) + 4u * q);
         lnext = lam_mine ? a.scales_up[(uint64_t)m * a.nblocks + gb_mine] : 0.f;
     };
-    if (grp < nmsg) request(grp);
-    const uint32_t rounds = (nmsg + G - 1u) / G;
-    for (uint32_t k = 0; k < rounds; ++k) {
-        const uint32_t m = k * G + grp;
-        if (a.count) small_from_bits(v, a.M, true, 0.5f * (float)a.M, lane, wave, word);
-        else small_from_signs(v, wnext, lane);
-        const float lam = lnext * a.in_coef;
-        if (m + G < nmsg) request(m + G);
-        if ((k & 7u) == 0u) { // the eps words of eight workers, a generator block for every thread; the last use was before the barrier
-            const uint32_t w8 = m + (t >> 5) * G;
-            if (w8 < nmsg) {
-                const RngKey key = { a.k0, rk1, kDomainEps, rlo, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + w8 };
-                uint32_t w[4];
-                philox((uint32_t)(base >> 7) + (t & 31u), key, w);
-                *reinterpret_cast<uint4 *>(eps8 + 4u * t) = make_uint4(w[0], w[1], w[2], w[3]);
-            }
+    // the eps words of the group's next eight workers from m on, a generator block for every thread
+    auto draw_eps = [&](uint32_t m) {
+        const uint32_t w8 = m + (t >> 5) * G;
+        if (w8 < nmsg) {
+            const RngKey key = { a.k0, rk1, kDomainEps, rlo, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + w8 };
+            uint32_t w[4];
+            philox((uint32_t)(base >> 7) + (t & 31u), key, w);
+            *reinterpret_cast<uint4 *>(eps8 + 4u * t) = make_uint4(w[0], w[1], w[2], w[3]);
         }
-        if (t < nblk) l.lam[t] = lam;
-        small_transform(v, S, l.x, lane, wave);
+    };
+    if (grp < nmsg) request(grp);
+    if constexpr (G == 1) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (G == 1 || m < nmsg) acc[r] = fmaf(v[r], small_signed_lam(l, eps8 + (k & 7u) * kSmEpsWords, r, S, lane, wave), acc[r]);
-        __syncthreads(); // the tables and l.x are free
-    }
-    if constexpr (G > 1) {
-        if (grp)
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (uint32_t m = 0; m < nmsg; ++m) {
+            if (a.count) small_from_bits(v, a.M, true, 0.5f * (float)a.M, lane, wave, word);
+            else small_from_signs(v, wnext, lane);
+            const float lam = lnext * a.in_coef;
+            if (m + 1u < nmsg) request(m + 1u);
+            if ((m & 7u) == 0u) draw_eps(m); // the last use was before the barrier
+            if (t < nblk) l.lam[t] = lam;
+            small_transform(v, S, l.x, lane, wave);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) l.x[r * 256 + t] = acc[r];
+            for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], small_signed_lam(l, eps8 + (m & 7u) * kSmEpsWords, r, S, lane, wave), acc[r]);
+            __syncthreads(); // the tables and l.x are free
+        }
+    } else {
+        __shared__ __attribute__((aligned(16))) float xs[G - 1][kSmXWords];
+        __shared__ float lams[2][G][64];
+        __shared__ SmallJoin<G> join;
+        float *const x = grp ? xs[grp - 1u] : l.x;
+        float part[16 / G];
+#pragma unroll
+        for (int i = 0; i < 16 / G; ++i) part[i] = 0.f;
+        for (uint32_t m0 = 0, k = 0; m0 < nmsg; m0 += G, ++k) {
+            const uint32_t m = m0 + grp;
+            small_from_signs(v, wnext, lane);
+            if (t < nblk) lams[k & 1u][grp][t] = m < nmsg ? lnext * a.in_coef : 0.f; // last read two rounds ago
+            if (m + G < nmsg) request(m + G);
+            if ((k & 7u) == 0u) draw_eps(m); // the last use was before the barrier
+            small_transform(v, S, x, lane, wave);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                v[r] = flip_by_bit0(v[r], eps8[(k & 7u) * kSmEpsWords + (small_l2(r, wave) >> 5) + (lane >> 5)] >> (lane & 31u));
+            join.put(grp, t, v);
+            __syncthreads(); // the values are published, eps8 and x are free
+            join.add(part, grp, t, [&](uint32_t g, uint32_t r) { return lams[k & 1u][g][small_l2((int)r, wave) >> S]; });
+        }
+        SmallJoin<G>::hand_over(part, x, grp, t);
         __syncthreads();
         if (grp) { // the barriers of the first group: here, in small_encode_tile and small_transform, in small_pack, with the update
             const uint32_t left = 3u + (a.stat_clipped ? 1u : 0u) + (UPDATE ? 2u : 0u);
             for (uint32_t k = 0; k < left; ++k) __syncthreads();
             return;
         }
-#pragma unroll
-        for (int g = 1; g < G; ++g)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] += ls[g].x[r * 256 + t];
+        SmallJoin<G>::take_over(acc, part, [&](uint32_t g) { return xs[g - 1u]; }, t);
     }
     {
         float *const p = l.x + lane + wave * 272u;
@@ -635,10 +702,10 @@ __device__ __forceinline__ float small_sumsq(const float (&v)[16])
 // u = row << cb | column:
 //   A (loads): regs = (u8..u11), threads = (u0..u7)        B: regs = (u4..u7), threads = (u0..u3, u8..u11)
 // B is reached through LDS (word u + 16 (u / 256)) where some row bit lies below u8 (HB > 4).
-// G > 1 (SMH_SERVER): G groups of 256 threads share the workers, group g takes g, g + G, ..., and the first adds up the groups'
-// parts of the mean, in order, and goes on alone.  A vector of 2^20 has one tile for every compute unit, and one wave on a SIMD
-// waits out every exchange and every generator chain of the M workers one after the other.  The kernel, us, one group and four:
-// n = 2^16, M = 4 8.5 and 7.1; 2^17, M = 8 12.1 and 9.2; 2^18, M = 32 33 and 20; 2^20, M = 32 40 and 32.
+// G > 1 (SMH_SERVER): G groups of 256 threads share the workers (SmallJoin), and the first goes on alone with the mean.  A vector
+// of 2^20 has one tile for every compute unit, and one wave on a SIMD waits out every exchange and every generator chain of the M
+// workers one after the other.  The step, us, one group and four: n = 2^16, M = 4 25.9 and 24.9; 2^17, M = 8 32.6 and 30.4;
+// 2^18, M = 32 71.9 and 59.8; 2^20, M = 32 164.6 and 157.8.
 constexpr uint32_t small_server_groups(uint32_t nmsg) { return nmsg >= 4u ? 4u : nmsg >= 2u ? 2u : 1u; }
 template <int MODE, int HB, int G = 1>
 __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a, const PtrTab tab)
@@ -646,7 +713,7 @@ __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a
     static_assert(G == 1 || MODE == SMH_SERVER, "groups share the workers");
     constexpr uint32_t cb = kSmLog2 - HB;
     constexpr bool X = HB > 4;
-    __shared__ float xbs[G][kSmXWords];
+    __shared__ __attribute__((aligned(16))) float xbs[G][kSmXWords];
     __shared__ __attribute__((aligned(16))) uint32_t epss[G][2][kSmEpsWords];
     __shared__ float red[4];
     const uint32_t t = G > 1 ? threadIdx.x & (kSmThreads - 1u) : threadIdx.x, lane = t & 63u, wave = t >> 6, slot = blockIdx.y;
@@ -757,28 +824,15 @@ __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a
             if (off(uo(r)) < room) dst[off(uo(r))] = small_result(flip(c * v[r], eps[0], uo(r)), old[r], a.store_mode, a.delta);
     } else {
         float acc[16], next[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-        const uint32_t nmsg = a.count ? 1u : a.M, rounds = (nmsg + G - 1u) / G;
+        const uint32_t nmsg = a.count ? 1u : a.M;
         const float *src = a.src + origin;
         auto request = [&](uint32_t m) {
-            if (G > 1 && m >= nmsg) return;
 #pragma unroll
             for (int r = 0; r < 16; ++r) next[r] = src[m * a.src_stride + off(ua(r))];
         };
-        request(grp);
-        for (uint32_t k = 0; k < rounds; ++k) {
-            const uint32_t m = k * G + grp;
-            const bool mine = G == 1 || m < nmsg;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = next[r];
-            if (k + 1u < rounds) request(m + G);
-            uint32_t *const e = eps[k & 1u]; // last read one round ago, before that round's closing barrier
-            float c = 0.f;
-            if (mine) {
-                fill(e, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + m);
-                c = a.scales_up[(uint64_t)m * a.nblocks + gb] * a.in_coef;
-            }
+        // worker m (v in layout A on entry) transformed in layout `uo`, its eps words in e; one barrier
+        auto transform = [&](uint32_t *e, uint32_t m) {
+            fill(e, a.eps_in >= 0xFFFFFFFEu ? a.eps_in : a.eps_in + m);
             stages_hi(v);
             if constexpr (X) {
                 a_to_b(v); // its barrier publishes the eps table
@@ -786,15 +840,46 @@ __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a
             } else {
                 __syncthreads();
             }
-            if (mine)
+        };
+        auto coef_of = [&](uint32_t m) -> float { return a.scales_up[(uint64_t)m * a.nblocks + gb] * a.in_coef; };
+        if constexpr (G == 1) {
+            request(0u);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            for (uint32_t m = 0; m < nmsg; ++m) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = next[r];
+                if (m + 1u < nmsg) request(m + 1u);
+                uint32_t *const e = eps[m & 1u]; // last read one worker ago, before that worker's closing barrier
+                const float c = coef_of(m);
+                transform(e, m);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[r] = fmaf(v[r], flip(c, e, uo(r)), acc[r]);
-            __syncthreads(); // xb is free
-        }
-        if constexpr (G > 1) {
-            if (grp)
+                __syncthreads(); // xb is free
+            }
+        } else {
+            __shared__ SmallJoin<G> join;
+            float part[16 / G], c[G];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) xb[r * 256 + t] = acc[r];
+            for (int i = 0; i < 16 / G; ++i) part[i] = 0.f;
+            request(grp < nmsg ? grp : 0u);
+            for (uint32_t m0 = 0; m0 < nmsg; m0 += G) {
+                const uint32_t m = m0 + grp;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = next[r];
+                if (m + G < nmsg) request(m + G);
+#pragma unroll
+                for (int g = 0; g < G; ++g) c[g] = coef_of(m0 + g < nmsg ? m0 + g : m0);
+#pragma unroll
+                for (int g = 0; g < G; ++g) c[g] = m0 + g < nmsg ? c[g] : 0.f;
+                transform(eps[0], m); // the last read of eps was before the barrier
+#pragma unroll
+                for (int r = 0; r < 16; ++r) v[r] = flip(v[r], eps[0], uo(r));
+                join.put(grp, t, v);
+                __syncthreads(); // the values are published, xb and eps are free
+                join.add(part, grp, t, [&](uint32_t g, uint32_t) { return c[g]; });
+            }
+            SmallJoin<G>::hand_over(part, xb, grp, t);
             __syncthreads();
             if (grp) { // the barriers of the first group
                 if (a.partials) __syncthreads();
@@ -802,10 +887,7 @@ __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a
                 if constexpr (X) __syncthreads();
                 return;
             }
-#pragma unroll
-            for (int k = 1; k < G; ++k)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] += xbs[k][r * 256 + t];
+            SmallJoin<G>::take_over(acc, part, [&](uint32_t g) { return xbs[g]; }, t);
         }
         if (a.gbar)
 #pragma unroll

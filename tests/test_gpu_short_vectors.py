@@ -90,3 +90,33 @@ def test_counters_of_short_vectors(oracle, d, blk):
         assert h[0] == 0 and h[near] == 0 and h[B.MAX_WORKERS] == 0
     assert forced[1] > plan.ntot // 100
     plan.close()
+
+
+@pytest.mark.parametrize("M", [2, 3, 4, 5, 7, 8, 11])
+@pytest.mark.parametrize("blk,few,many", [(6, 700, 19_300), (9, 20, 2_400), (12, 250, 300), (16, 8, 32), (17, 1, 16), (20, 1, 2)])
+def test_groups_add_in_the_workers_order(blk, few, many, M):
+    """Up to a tile for every compute unit, groups of threads share the workers; beyond, one group takes them one after the
+    other.  The mean of a block is the same to the bit: the groups hand one another exact values only."""
+    import torch
+    from paper_2405_11095_amd import binding as B
+    dev = torch.device("cuda:0")
+    if M * (many << blk) > 1 << 24 and blk < 17:
+        pytest.skip("more workers than the short vectors' kernels take at this length")
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    assert (few << blk) / 4096 <= cus < (many << blk) / 4096
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(M)
+    bits = torch.randint(-(1 << 63), (1 << 63) - 1, (M, (many << blk) // 64), generator=gen, device=dev, dtype=torch.int64)
+    lam = torch.rand(M, many, generator=gen, device=dev) + 0.5
+    means = []
+    for nb in (few, many):
+        plan = B.Plan(d=nb << blk, M=M, block_log2=blk, seed=17)
+        down, lam_s = torch.zeros(1, plan.W, dtype=torch.int64, device=dev), torch.zeros(nb, device=dev)
+        gbar = torch.zeros(plan.ntot, device=dev)
+        plan.fo_profile_begin()
+        plan.fo_server_aggregate(bits[:, :plan.W].contiguous(), lam[:, :nb].contiguous(), 6, down, lam_s, gbar)
+        torch.cuda.synchronize()
+        assert any(k.startswith("k_small") for k in plan.fo_profile_end())
+        means.append(gbar)
+        plan.close()
+    assert torch.equal(means[0], means[1][:few << blk])
