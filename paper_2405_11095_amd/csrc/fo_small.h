@@ -706,7 +706,6 @@ __device__ __forceinline__ float small_sumsq(const float (&v)[16])
 // of 2^20 has one tile for every compute unit, and one wave on a SIMD waits out every exchange and every generator chain of the M
 // workers one after the other.  The step, us, one group and four: n = 2^16, M = 4 25.9 and 24.9; 2^17, M = 8 32.6 and 30.4;
 // 2^18, M = 32 71.9 and 59.8; 2^20, M = 32 164.6 and 157.8.
-constexpr uint32_t small_server_groups(uint32_t nmsg) { return nmsg >= 4u ? 4u : nmsg >= 2u ? 2u : 1u; }
 template <int MODE, int HB, int G = 1>
 __global__ __launch_bounds__(kSmThreads * G) void k_small_high(const SmallArgs a, const PtrTab tab)
 {

@@ -43,11 +43,14 @@ SmallArgs small_base(const fo_plan *pl, const Rng &r)
     return a;
 }
 
-// Groups of threads that share the workers in the server's kernels: a tile for every compute unit at most (512 tiles, M = 8,
-// b = 2^16: 79 us a step with one group, 81 with four; blocks of 2^9, d = 2 * 10^6, M = 4 34.3 and 41.4, in two groups 34.5).
-uint32_t server_groups(const fo_plan *pl, const SmallArgs &a)
+// Whether four groups of threads share the workers in the server's kernels: from four workers (three in two groups: n = 2^16 24.8
+// us a step and 24.8, d = 10^6 in blocks of 2^12 21.0 and 21.4; two: 2^20 35.7 and 35.4, otherwise the same) and a tile for every
+// compute unit at most (512 tiles, M = 8, b = 2^16: 79 us a step with one group, 81 with four; blocks of 2^9, d = 2 * 10^6, M = 4
+// 34.3 and 41.4).
+constexpr int kServerGroups = 4;
+bool share_workers(const fo_plan *pl, const SmallArgs &a)
 {
-    return pl->sm_tiles <= pl->num_cus ? small_server_groups(a.count ? 1u : a.M) : 1u;
+    return !a.count && a.M >= (uint32_t)kServerGroups && pl->sm_tiles <= pl->num_cus;
 }
 
 // Stages above the contiguous tile, b > 2^12.
@@ -55,9 +58,7 @@ template <int MODE, int G = 1>
 int launch_high(fo_plan *pl, uint32_t nslots, hipStream_t st, const SmallArgs &a, const PtrTab &tab)
 {
     if constexpr (MODE == SMH_SERVER && G == 1) {
-        const uint32_t groups = server_groups(pl, a);
-        if (groups == 4u) return launch_high<MODE, 4>(pl, nslots, st, a, tab);
-        if (groups == 2u) return launch_high<MODE, 2>(pl, nslots, st, a, tab);
+        if (share_workers(pl, a)) return launch_high<MODE, kServerGroups>(pl, nslots, st, a, tab);
     }
     const int kid = MODE == SMH_ENC ? KID_SM_ENC_HIGH : MODE == SMH_SERVER ? KID_SM_SERVER_HIGH : KID_SM_DEC_HIGH;
     const dim3 grid((unsigned)pl->sm_tiles, nslots), block(kSmThreads * G);
@@ -92,8 +93,7 @@ template <bool UPDATE, int G = 1>
 int launch_mean(fo_plan *pl, hipStream_t st, const SmallArgs &a)
 {
     if constexpr (G == 1) {
-        // from four workers (three in two groups: 21.0 -> 21.4 us a step of d = 10^6; two: the same time)
-        if (server_groups(pl, a) == 4u) return launch_mean<UPDATE, 4>(pl, st, a);
+        if (share_workers(pl, a)) return launch_mean<UPDATE, kServerGroups>(pl, st, a);
     }
     const dim3 grid((unsigned)pl->sm_tiles), block(kSmThreads * G);
     const bool dither = a.dither == FO_DITHER_UNIFORM;

@@ -30,7 +30,7 @@ CASES = [
     ((1 << 22) + 1, 2, 12, {}),
     (1 << 20, 2, 20, {}),                                        # the longest transform, and the next
     ((1 << 20) + 1, 2, 0, {}),
-    (9_001, 3, 0, {}),                                           # workers dealt to two groups, then to four, unevenly
+    (9_001, 3, 0, {}),                                           # workers one after the other, then dealt to four groups, unevenly
     (20_003, 5, 0, {"server_scale": 1}),
     (150_001, 7, 0, {"K": 3}),
     (1 << 20, 4, 0, {"server_scale": 1}),                        # a tile for every compute unit; one tile more
