@@ -38,14 +38,7 @@ __global__ void k_server_scales(const float *scales_up, uint64_t nblocks, uint32
 {
     const uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (j >= nblocks) return;
-    float m = 0.f;
-    bool nan = false;
-    for (uint32_t n = 0; n < M; ++n) {
-        const float l = scales_up[(uint64_t)n * nblocks + j];
-        nan |= (l != l);
-        m = fmaxf(m, l);
-    }
-    scales_down[j] = nan ? __builtin_nanf("") : coef_s * m;
+    scales_down[j] = coef_s * largest_scale(scales_up, nblocks, M, j);
 }
 
 // Shared-eps mode: every worker quantises with the largest of the workers' amplitudes, per block.
@@ -53,14 +46,7 @@ __global__ void k_common_scales(float *scales, uint64_t nblocks, uint32_t M)
 {
     const uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (j >= nblocks) return;
-    float m = 0.f;
-    bool nan = false;
-    for (uint32_t n = 0; n < M; ++n) {
-        const float l = scales[(uint64_t)n * nblocks + j];
-        nan |= (l != l);
-        m = fmaxf(m, l);
-    }
-    if (nan) m = __builtin_nanf("");
+    const float m = largest_scale(scales, nblocks, M, j);
     for (uint32_t n = 0; n < M; ++n) scales[(uint64_t)n * nblocks + j] = m;
 }
 

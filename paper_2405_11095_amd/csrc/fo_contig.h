@@ -92,20 +92,6 @@ __device__ __forceinline__ uint32_t seg_tile(uint32_t seg, uint32_t i)
     return seg ? (i & ~31u) | ((i & 7u) << 2) | ((i >> 3) & 3u) : i;
 }
 
-// The server's amplitude of block gb by the theorem's rule: coef_lambda times the largest of the workers', NaN if any is NaN.
-__device__ __forceinline__ float server_scale_of(const ContigArgs &a, uint64_t gb)
-{
-    float m = 0.f;
-    bool nan = false;
-#pragma unroll 8
-    for (uint32_t n = 0; n < a.M; ++n) {
-        const float l = a.scales_up[(uint64_t)n * a.nblocks + gb];
-        nan |= (l != l);
-        m = fmaxf(m, l);
-    }
-    return nan ? __builtin_nanf("") : a.coef_lambda * m;
-}
-
 // Chunk C of 16 of the 4096 coordinates at wave_src (the same address in every lane), into the registers of layout L0.
 template <int C>
 __device__ __forceinline__ void load_chunk(float (&v)[kV], const float *wave_src, uint32_t lane, std::integral_constant<int, C>)
@@ -419,7 +405,7 @@ __device__ __forceinline__ void contig_tile(const ContigArgs &a, const PtrTab &t
                 l = a.coef_lambda * (float)sqrt(sum_of_waves(reinterpret_cast<const double *>(red)));
                 if ((tile & ((1u << (a.logb - (uint32_t)kTileLog2)) - 1u)) == 0u) a.scales[slot * a.scales_stride + gb] = l;
             } else if (IN == IN_GRAD && !PAIR && a.scales_up) {
-                if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l = server_scale_of(a, gb);
+                if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l = a.coef_lambda * largest_scale(a.scales_up, a.nblocks, a.M, gb);
             } else if (gb < a.nblocks) {
                 l = a.scales[slot * a.scales_stride + gb];
             }

@@ -159,6 +159,24 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
+// Largest of the M workers' amplitudes of block gb ([M][nblocks]), NaN if any of them is NaN.
+__device__ __forceinline__ float largest_scale(const float *scales, uint64_t nblocks, uint32_t M, uint64_t gb)
+{
+    float m = 0.f;
+    bool nan = false;
+    for (uint32_t n = 0; n < M; n += 8u) { // eight loads on their way together; the last worker's again where there are fewer
+        float l[8];
+#pragma unroll
+        for (uint32_t i = 0; i < 8u; ++i) l[i] = scales[(uint64_t)(n + i < M ? n + i : M - 1u) * nblocks + gb];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            nan |= (l[i] != l[i]);
+            m = fmaxf(m, l[i]);
+        }
+    }
+    return nan ? __builtin_nanf("") : m;
+}
+
 // Step K of a butterfly sum: s plus the s of the lane whose number differs in bit K.  Lanes that differ below bit K only hold the
 // same sum, so mirroring 8 or 16 lanes reaches the partner as well; bits 4 and 5 are the row swaps.  In registers: a shuffle goes
 // through LDS, 100 cycles and more of a chain of six (step of 3 M coordinates in blocks of 2^9, M = 5, K = 4: 53.2 -> 48.9 us; of

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kWvThreads, 4) void k_enc_wave(const ContigArgs a, 
             if (gb < a.nblocks) a.scales[slot * a.scales_stride + gb] = l;
         } else if (gb < a.nblocks) {
             float *const at = a.scales + slot * a.scales_stride + gb;
-            if (a.scales_up) *at = l = server_scale_of(a, gb);
+            if (a.scales_up) *at = l = a.coef_lambda * largest_scale(a.scales_up, a.nblocks, a.M, gb);
             else l = *at;
         }
         blk[lane] = -128.f / (l * (a.sqrtb * 5.9604644775390625e-08f));

@@ -300,19 +300,6 @@ __device__ __forceinline__ void small_from_kept(float (&v)[16], const SmallArgs 
     }
 }
 
-// Largest amplitude of the M workers for block gb, NaN if any is NaN
-__device__ __forceinline__ float small_largest(const SmallArgs &a, uint64_t gb)
-{
-    float m = 0.f;
-    bool nan = false;
-    for (uint32_t n = 0; n < a.M; ++n) {
-        const float s = a.scales_up[(uint64_t)n * a.nblocks + gb];
-        nan |= (s != s);
-        m = fmaxf(m, s);
-    }
-    return nan ? __builtin_nanf("") : m;
-}
-
 // Encoder from the vector in L0 (b <= 2^12): block norms where measured, amplitudes into l.lam and memory, eps flip,
 // transform.  Leaves the tile in L2 with l.lam published; returns false if only the amplitudes were wanted.
 __device__ __forceinline__ bool small_encode_tile(float (&v)[16], const SmallArgs &a, SmallLds &l, uint32_t rk1, uint32_t rlo,
@@ -357,7 +344,7 @@ __device__ __forceinline__ bool small_encode_tile(float (&v)[16], const SmallArg
                 for (uint32_t k = 0; k < per; ++k) s += l.red[t * per + k];
                 *out = lam = a.coef * sqrtf(s);
             } else if (a.scale_mode == SMS_SERVER) {
-                *out = lam = a.coef * small_largest(a, gb);
+                *out = lam = a.coef * largest_scale(a.scales_up, a.nblocks, a.M, gb);
             } else {
                 lam = *out;
             }
@@ -439,7 +426,7 @@ __global__ __launch_bounds__(kSmThreads) void k_small_encode(const SmallArgs a, 
             }
             if (nan) lam = __builtin_nanf("");
         } else if (a.scale_mode == SMS_SERVER) {
-            lam = a.coef * small_largest(a, gb);
+            lam = a.coef * largest_scale(a.scales_up, a.nblocks, a.M, gb);
         } else {
             lam = a.scales[slot * a.scales_stride + gb];
         }
