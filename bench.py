@@ -148,18 +148,40 @@ def main():
     # intermediates are int16), i.e. what the kernels have to move through HBM; rocprofv3's counters agree with it.
     W8 = n // 8
     ind = args.eps_mode == "independent"
-    walk = "k_contig_pair_walk" in per_kernel
-    pair = walk or "k_contig_pair" in per_kernel
-    n_low = (M + 1) if not pair else 1                       # vectors through the encode's low pass
+    # One-pass encodes: which kernel takes the workers' gradients (read twice where the workers agree on an amplitude
+    # first) and which the server's mean.  A K-fold message of the mean is k_contig's (blocks of 2^16: k_contig_pair's).
+    # Blocks of 2^16: the walk takes the whole blocks, and a launch of k_contig_pair beside it the workers' ragged
+    # last ones, where there are more of them than compute units (ragged: five times as many).
+    one_pass = dict.fromkeys(("k_contig<IN_GRAD,OUT_PACK>", "k_enc_wave", "k_contig_pair", "k_contig_pair_walk"), 0)
+    pair = "k_contig_pair_walk" in per_kernel or "k_contig_pair" in per_kernel
+    logb = plan.b.bit_length() - 1
+    mean_bytes = 4 * n + plan.planes * W8
+    if pair:
+        cus = torch.cuda.get_device_properties(dev).multi_processor_count
+        whole = d >> 16
+        if M * whole > (5 if d & 0xFFFF else 1) * cus:
+            one_pass["k_contig_pair_walk"] += M * whole * (1 << 13) * 33
+            one_pass["k_contig_pair"] += M * (4 * (d & 0xFFFF) + 8192) if d & 0xFFFF else 0
+        else:
+            one_pass["k_contig_pair"] += M * (4 * d + W8)
+        if not ind:
+            one_pass["k_contig_pair"] += M * 4 * d
+        elif args.K == 1 and plan.nblocks > cus:
+            one_pass["k_contig_pair_walk"] += mean_bytes
+        else:
+            one_pass["k_contig_pair"] += mean_bytes
+    else:
+        plain = "k_enc_wave" if logb <= 12 else "k_contig<IN_GRAD,OUT_PACK>"
+        one_pass[plain] += M * (4 * d + W8) + (0 if ind else M * 4 * d)
+        if args.eps_mode != "all":
+            one_pass[plain if args.K == 1 else "k_contig<IN_GRAD,OUT_PACK>"] += mean_bytes
+    n_low = (0 if pair else M) + (args.eps_mode != "all")    # vectors through the encode's low pass
     n_dlow = (M + (0 if "k_decode_pair" in per_kernel else 1)) if ind else 1
     model = {
         "k_strided<ENC_FIRST>": M * (4 * d + 4 * n),
-        # with blocks of 2^16 the workers' encode is one pass (k_contig_pair); only the server re-encodes in two
+        # with blocks of 2^16 the workers' encode is one pass (k_contig_pair); the server's re-encode takes two with shared eps
         "k_contig<IN_F32,OUT_PACK>": n_low * (4 * n + W8),
-        # blocks of 2^16: the server's re-encode of the mean is one more vector through the pair kernel.  The walk takes
-        # the whole blocks (of the mean, all of them); what is left beside it are the workers' ragged last blocks.
-        "k_contig_pair_walk": M * ((d >> 16) << 16) * 33 // 8 + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
-        "k_contig_pair": M * (4 * (d & 0xFFFF) + 8192) if walk else M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
+        **one_pass,
         "k_declow": n_dlow * (W8 + 4 * n),
         "k_strided<SERVER>": (M * 4 * n + 4 * n) if ind else 8 * n,
         "k_server_mfma": M * 4 * n + 4 * n,
@@ -167,13 +189,11 @@ def main():
         "k_mean_mfma": M * W8 + 4 * n,
         "k_shall": M * W8 + W8,
         "k_strided<DEC_LAST>": 4 * n + 8 * d,
-        "k_contig<IN_GRAD,OUT_PACK>": M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
         "k_decode_tile": W8 + 8 * d,
         "k_decode_pair": W8 + 8 * d,
         # short vectors: fp32 intermediates on the decode side too; with independent eps a message goes straight on into
         # its decoder's low stages (one more intermediate written), and a mean in one tile never leaves the chip
         "k_small_high<ENC>": M * (4 * d + 4 * n),
-        "k_enc_wave": M * (4 * d + W8) + (4 * n + W8 if "k_mean_mfma" in per_kernel else 0),
         "k_small_encode<GRAD>": M * (4 * d + W8),
         "k_small_encode<MID>": (M + 1) * (8 * n + W8) if ind else M * (4 * n + W8) + (8 * n + W8 if args.eps_mode == "shared" else 0),
         "k_small_decode<LOW>": (M * W8 if args.eps_mode == "shared" else W8) + 4 * n,
