@@ -667,7 +667,7 @@ __global__ __launch_bounds__(2 * kThreads) void k_contig_pair(const ContigArgs a
 // compute unit (128 registers per thread, 148 KiB of LDS), so nothing else runs there while it waits for a block's 256
 // KiB; it walks over the blocks instead and loads the next one while it quantises the present one (the quantiser's
 // Philox rounds are a third of the arithmetic, and it gives up four registers at a time).  n = 2^27, eight workers: the step
-// takes 2.06 ms, with one workgroup per block 2.41.
+// takes 2.01 ms, with one workgroup per block 2.50.
 static __global__ __launch_bounds__(2 * kThreads) void k_contig_pair_walk(const ContigArgs a, const PtrTab tab, const uint32_t nblk,
                                                                    const uint32_t nslots)
 {

@@ -1,5 +1,6 @@
 // Encoder (Def. 3.7) for blocks of 2^6 .. 2^12 coordinates, plain messages (K = 1) with dither: every wave takes 4096
-// coordinates through the whole path by itself.  A workgroup is one wave with 8.25 KiB of LDS, nineteen to a compute unit.
+// coordinates through the whole path by itself.  A workgroup is one wave with 8.25 KiB of LDS (8.75 as it is dealt out),
+// eighteen to a compute unit.
 //
 // Layouts of a wave's 4096 coordinates (b0..b11):
 //   L0 (global loads, 16 B per lane): regs = (b0,b1,b8,b9,b10,b11)  lanes = (b2..b7)               stages b0,b1,b8..b11
@@ -10,9 +11,10 @@
 // differs in (b0, b1), and a word's bit is 4 (b2..b5) + (b0,b1): transposing the 4 x 4 bits of every nibble across the quad, a
 // dozen instructions for 64 values, leaves each lane with the packed word of its own number.
 //
-// What bounds it: 115 to 125 cycles of vector instructions a value and SIMD (Philox 48, butterflies 31, the eps flips 12, the
-// quantiser 17, the lane swaps 4; additions and shifts issue twice as fast as the rest), and the exchange: LDS takes a wave's
-// dword in 3.1 cycles of the compute unit (ds_write2_b32) and gives it back in 2.4, 22 cycles of each of the four SIMDs for a
+// What bounds it, by the instructions and the rates at which each was measured to issue (additions and shifts twice as fast as
+// the rest): 115 to 125 cycles of a SIMD for a value of its 64 lanes (Philox 48, butterflies 31, the eps flips 12, the quantiser
+// 17, the lane swaps 4) of the 140 it takes; the counters give 32.4 vector instructions a value.  And the exchange: LDS takes a
+// wave's dword in 3.1 cycles of the compute unit (ds_write2_b32) and gives it back in 2.4, 22 cycles of each of the four SIMDs for a
 // value through write and read, which the vector units overlap only in part.  A second exchange, packing through lane writes
 // and workgroup barriers cost a third more.  2^27 coordinates, eight workers and the server, us, k_contig before and this:
 // blocks of 2^6 1670 -> 1030, 2^8 1630 -> 1080, 2^10 1260 -> 1045, 2^12 1290 -> 1110; read and write of its 4.99 GB take 970.

@@ -310,9 +310,9 @@ constexpr SmallRule kSmallRules[4] = {
 inline uint32_t decode_regions(const fo_plan *pl) { return pl->npass == 1 && pl->hb[0] >= kSegHigh ? pl->hb[0] : 0u; }
 
 // Most stages that one strided pass takes; a transform with more stages above the contiguous tile takes two of them.
-// Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, which read at 3.2 TB/s instead of 4.9, but a
-// second strided pass moves every intermediate once more, and on the server's side in int32 instead of int16: a step of
-// n = 2^27 with four workers takes 3.39 ms with one pass of twelve stages and 5.43 ms with passes of six and six.
+// Eleven and twelve (blocks of 2^26 and 2^27) mean rows of 64 and 32 bytes, on which the encoder runs at 3.4 TB/s instead of 5.0,
+// but a second strided pass moves every intermediate once more, and on the server's side in int32 instead of int16: a step of
+// n = 2^27 with four workers takes 3.27 ms with one pass of twelve stages and 5.41 ms with passes of six and six.
 // Thirteen would leave rows of 4 columns, less than one line's worth per eight tiles.
 constexpr uint32_t kMaxHigh = 12;
 

@@ -6,10 +6,10 @@
 // vector occupies eight times as many workgroups, each with an eighth of the work.  Everything is fp32: on the decode
 // side the values are half integers below 2^23, so every sum is exact (the plan's rule sees to the bound).
 // Measured, general kernels before and these after: one encode of 1000 coordinates 12.0 -> 7.3 us (kernel 4.9 us), a step of
-// n = 2^16 with four workers 71.7 -> 24.9 us, n = 2^20 with eight 123 -> 55 us.  What bounds a kernel here is latency: one
+// n = 2^16 with four workers 71.7 -> 24.2 us, n = 2^20 with eight 123 -> 53.9 us.  What bounds a kernel here is latency: one
 // trip to memory, two exchanges and the generator's chain of ten rounds, 4 to 7 us each with few waves per SIMD.  At n = 2^20
-// with eight workers the joined low pass takes 21 us with the vector
-// units 47 % busy, at 59 instructions per value (the long kernels' encode and decode: 31 and 9).
+// with eight workers the joined low pass takes 19.6 us with the vector units 49 % busy, at 58 instructions per value (the long
+// kernels' encode and decode: 31 and 9).
 //
 // Transforms of up to 2^12 points (whole or blocked) take one pass, longer ones (up to 2^20 points) two: up to eight
 // stages over rows 2^12 apart (k_small_high), twelve inside the contiguous tile (k_small_encode, k_small_decode).

@@ -12,12 +12,11 @@
 // the server pass does it in one whole-tile pass); lanes keep their bits, so LDS accesses are conflict free and
 // stores are as coalesced as loads.  Row bits that fall on lane bits 4 and 5 (hb >= 9) are handled with
 // v_permlane16_swap / v_permlane32_swap, those on lane bits 2 and 3 (hb = 11, 12) with DPP moves.  With hb = 12 (n = 2^27,
-// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.17 ms, 3.94 GB, 40 %; server 0.88 ms,
-// 1.70 GB, 52 %; decode 0.37 ms, 1.13 GB, 22 %.  Encode and decode are bound by the 32-byte row segments of the caller's
-// vectors (an encode on tiles of 2^16 coordinates, with
-// segments of 64 bytes but one workgroup per compute unit, took a seventh longer; a decode of 32 values per thread, with
-// half the loads in flight, an eighth).  In the server, one workgroup to a compute unit,
-// the stages of a worker and the loads of the next cover each other only in part.
+// M = 4), times, bytes by the counters and share of the vector units' time: encode 1.17 ms, 3.93 GB, 39 %; server 0.88 ms,
+// 1.70 GB, 52 %; decode 0.37 ms, 1.09 GB, 28 %.  Encode and decode are bound by the 32-byte row segments of the caller's
+// vectors (an encode on tiles of 2^16 coordinates, with segments of 64 bytes but one workgroup per compute unit, took a
+// seventh longer; a decode of 32 values per thread, with half the loads in flight, an eighth).  In the server, one workgroup
+// to a compute unit, the stages of a worker and the loads of the next cover each other only in part.
 // Modes
 //   SM_ENC_FIRST : fp32 gradient (zero padded), eps flip on load, tile sum of squares -> fp32 intermediate
 //   SM_DEC_LAST  : integer intermediate -> lambda/sqrt(b) scaling, eps flip, store / SGD update (Def. 3.8)
@@ -155,8 +154,7 @@ __device__ __forceinline__ void fill_eps(uint32_t *epsw, const StridedGeom &g, c
 // words spends 2048 or 4096 draws on 2^15 bits, a fifth of the server's vector instructions; here every block is drawn once
 // and its bits are dealt out through LDS.  n = 2^27, four workers: 19 us for the five parties, server pass 1045 -> 903 us.
 // 256 threads: 128 rows by 256 columns.  blockIdx.x = column part (128 of them; one with REGIONS) of row part (2^HB / 128) of
-// block (region);
-// blockIdx.y = party party0 + y, the last one `last`.
+// block (region); blockIdx.y = party party0 + y, the last one `last`.
 template <int HB, bool REGIONS>
 __global__ __launch_bounds__(256) void k_eps_table(uint32_t k0, uint32_t k1, uint32_t round_lo, const unsigned long long *round_dev,
                                                    uint32_t party0, uint32_t last, uint32_t *table, uint64_t stride)
